@@ -2,7 +2,7 @@
 
 A case is a plain dict.  `prepare` makes what a program holds before the call (inputs, weights, output buffers and the
 tuned configurations, all on the GPU), `run` makes one pass through the public entry points, `work` and `tolerance` say
-what a pass cannot do without and how far another correct implementation may be off.
+what a pass cannot do without and how far another correct implementation may be off, `exact` gives a pass's results in 64 bits.
 
 Kinds of cases and what they stand for:
   gemm        one GEMM with its fused epilogue (optionally with a residual matrix), tuned or left to the built-in rule
@@ -127,6 +127,9 @@ def draw(rng):
 # ----------------------------------------------------------------------------------------------------------------
 # what a program holds before the call
 # ----------------------------------------------------------------------------------------------------------------
+_untuned = False  # set while exact() makes the inputs: it has no use for a configuration
+
+
 class _Make:
     """Seeded tensors.  Activations are U[-1, 1] (behind a ReLU where `relu`), weights N(0, 2 / fan_in), biases small."""
 
@@ -152,6 +155,8 @@ class _Make:
 
 def _tuned(op, d0, d1, tensors):
     """The configuration a program keeps for a problem, and the workspace it needs (None if it needs none)."""
+    if _untuned:
+        return None, None
     most = bolt.bolt_workspace_bytes(op, d0, d1)
     scratch = torch.empty(most, dtype=torch.uint8, device="cuda") if most else None
     config = bolt.bolt_tune(op, d0, d1, tensors, scratch).config
@@ -351,6 +356,77 @@ def work(case):
         return dict(bytes=total_b, flops=total_f)
     b, f, _, _ = _conv_work(c["batch"], c["H"], c["W"], 3, c["K"], c["R"], c["R"], 2, c["R"] // 2, c["R"] // 2)
     return dict(bytes=b + 4 * c["batch"] * c["out_hw"] ** 2 * c["out_c"], flops=f)
+
+
+# ----------------------------------------------------------------------------------------------------------------
+# the same pass in 64 bits
+# ----------------------------------------------------------------------------------------------------------------
+def _act64(v, act):
+    name = {number: text for text, number in bolt.ACT.items()}[act]
+    if name == "relu":
+        return v.clamp_(min=0)
+    if name == "gelu":
+        return 0.5 * v * torch.erfc(v * -math.sqrt(0.5))
+    if name == "hardswish":
+        return v * (v + 3).clamp_(0, 6) / 6
+    return torch.logaddexp(v, torch.zeros((), dtype=v.dtype, device=v.device)) if name == "softplus" else v
+
+
+def _gemm64(d, a, w, b, skip=None):
+    v = a @ (w.double() if d.b_layout == bolt.LAYOUT_KN else w.double().t()) + b.double()
+    return _act64(v if skip is None else v + skip.double(), d.act)
+
+
+def _conv64(d, x, w, b, skip=None):
+    """x: NHWC, 64 bits.  Each filter tap is a matrix product over the pixels that it meets."""
+    p, q = (d.H + 2 * d.pad_h - d.R) // d.stride_h + 1, (d.W + 2 * d.pad_w - d.S) // d.stride_w + 1
+    x = torch.nn.functional.pad(x, (0, 0, d.pad_w, d.pad_w, d.pad_h, d.pad_h))
+    v = b.double().expand(d.N * p * q, d.K).clone()
+    for r in range(d.R):
+        for s in range(d.S):
+            tap = x[:, r:r + (p - 1) * d.stride_h + 1:d.stride_h, s:s + (q - 1) * d.stride_w + 1:d.stride_w]
+            v.addmm_(tap.reshape(-1, d.C), w[:, r, s].double().t())
+    v = v.view(d.N, p, q, d.K)
+    return _act64(v if skip is None else v + skip, d.act)
+
+
+def exact(case, seed):
+    """What `run` returns, in 64 bits from the same half inputs; nothing is rounded between two ops."""
+    global _untuned
+    _untuned = True
+    try:
+        calls, outputs = _PREPARE[case["kind"]](case, _Make(seed))
+    finally:
+        _untuned = False
+    have = {}  # results so far, by the address of the buffer that the pass writes them to
+
+    def get(t):
+        return have.get(t.data_ptr(), t)
+
+    for call, a, _ in calls:
+        if call is bolt.bolt_gemm_epilogue:
+            out, v = a[4], _gemm64(a[0], a[1].double(), a[2], a[3])
+        elif call is bolt.bolt_gemm_epilogue_residual:
+            out, v = a[5], _gemm64(a[0], a[1].double(), a[2], a[3], a[4])
+        elif call is bolt.bolt_b2b_gemm:
+            out, v = a[7], _gemm64(a[1], _gemm64(a[0], a[2].double(), a[3], a[4]), a[5], a[6])
+        elif call is bolt.bolt_b2b_gemm_chain:
+            out, v = a[4], a[1].double()
+            for d, w, b in zip(a[0], a[2], a[3]):
+                v = _gemm64(d, v, w, b)
+        elif call is bolt.bolt_conv2d_fprop_nhwc:
+            x = get(a[1]).double()
+            out, v = a[4], _conv64(a[0], x.permute(0, 2, 3, 1) if a[0].x_layout == bolt.TENSOR_NCHW else x, a[2], a[3])
+        elif call is bolt.bolt_conv2d_fprop_nhwc_residual:
+            out, v = a[5], _conv64(a[0], get(a[1]).double(), a[2], a[3], get(a[4]).double())
+        elif call is bolt.bolt_b2b_conv:
+            out, v = a[7], _conv64(a[1], _conv64(a[0], get(a[2]).double(), a[3], a[4]), a[5], a[6])
+        elif call is bolt.bolt_b2b_conv_residual:
+            out, v = a[8], _conv64(a[1], _conv64(a[0], get(a[2]).double(), a[3], a[4]), a[5], a[6], get(a[7]).double())
+        else:
+            out, v = a[1], get(a[0]).double().permute(0, 3, 1, 2).contiguous()
+        have[out.data_ptr()] = v
+    return [have[t.data_ptr()] for t in outputs]
 
 
 def tolerance(case):
