@@ -19,9 +19,10 @@
  *   - Alignment (Section 3.2.3, "Kernel padding"): 128-bit accesses need every channel count,
  *     reduction length and leading dimension to be a multiple of 8, else BOLT_ERR_ALIGNMENT;
  *     pad with bolt_pad_channels_nhwc first.  The one exception is the input channel count of
- *     bolt_conv2d_fprop_nhwc: an even C that is not a multiple of 8 is accepted and runs on slow
- *     alignment-2 kernels (32-bit accesses), the "unpadded" case that Table 3 measures padding
- *     against.  An odd C is BOLT_ERR_ALIGNMENT.
+ *     bolt_conv2d_fprop_nhwc: an even C that is not a multiple of 8 is accepted, the "unpadded" case that
+ *     Table 3 measures padding against.  From C = 10 on it runs on kernels that pad the channels on the way to
+ *     LDS, where the patch of a tile fits there; else on slow alignment-2 kernels (32-bit accesses).  An odd C
+ *     is BOLT_ERR_ALIGNMENT.
  */
 #ifndef BOLT_H_
 #define BOLT_H_
@@ -138,8 +139,8 @@ bolt_status bolt_gemm_epilogue(const bolt_gemm_desc* desc, const void* A, const 
 
 /* Implicit-GEMM NHWC forward convolution + fused epilogue (Section 3.2.3: NHWC only; workloads of
  * Section 4.1.1).  x: N*H*W*C, w: K*R*S*C, bias: K halves or NULL, y: N*P*Q*K.  Requires K a
- * multiple of 8.  C a multiple of 8: the fast (128-bit) kernels; another even C: the alignment-2
- * kernels (Table 3's "unpadded" side); C <= 4 of either parity, e.g. the 3 colour planes of a first
+ * multiple of 8.  C a multiple of 8: the fast (128-bit) kernels; another even C: the kernels
+ * for unpadded channels (Table 3's "unpadded" side); C <= 4 of either parity, e.g. the 3 colour planes of a first
  * layer: the first-layer kernels, which read x without channel padding and, with
  * desc->x_layout = BOLT_TENSOR_NCHW, in NCHW (they need R * C <= 24, S <= 8, stride_w <= 2, else
  * BOLT_ERR_UNSUPPORTED; an odd C > 4 is BOLT_ERR_ALIGNMENT: pad it with bolt_pad_channels_nhwc). */

@@ -242,6 +242,7 @@ struct Tables {
     register_conv_align2_instances(conv);  // even channel counts that are not multiples of 8
     register_conv_smallc_instances(conv);  // first layers: at most 4 channels, unpadded NHWC or NCHW
     register_conv_nchw_out_instances(conv);  // last layers: the output written as NCHW
+    register_conv_even_instances(conv);  // even channel counts again (appended: the older families keep their kernel ids)
     register_b2b_gemm_instances(b2b_gemm);
     register_b2b_gemm_dma_instances(b2b_gemm);
     register_b2b_gemm_dma_kn_instances(b2b_gemm);
@@ -413,6 +414,12 @@ static int fprop_heuristic(const std::vector<FpropInstance>& tab, const FpropPro
     if (!fprop_supports(in, pr)) continue;
     if (need_split_k && !fprop_can_split_k(in)) continue;
     const FpropParams& p = pr.p;
+    if (in.estimate) {  // a family with a cost model of its own, in the same microseconds
+      const double cost = in.estimate(p);
+      if (tune_log_enabled()) std::fprintf(stderr, "[bolt_pick] candidate %d %s cost %.4g\n", i, in.name, cost);
+      if (best < 0 || cost < best_cost) { best = i; best_cost = cost; }
+      continue;
+    }
     const double tiles = (double)ceil_div(p.M, in.bm) * ceil_div(p.N, in.bn);
     const int kg = std::max(1, in.kgroups);
     const int lds = in.dyn_lds_bytes ? in.dyn_lds_bytes(p) : in.lds_bytes;

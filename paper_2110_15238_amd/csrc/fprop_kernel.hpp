@@ -215,6 +215,7 @@ struct FpropInstance {
   bool no_split_k;  // the kernel has no partial-sum output
   bool nchw_out;    // writes its output as [N][K][P][Q] (and only that)
   bool kn_dma;      // row-major weights fetched through one 32-bit-offset buffer descriptor over the whole matrix
+  double (*estimate)(const FpropParams&);  // the pick rule's cost of this family, in us (null: the common model)
 };
 
 template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int XMODE, int WMODE>

@@ -327,6 +327,70 @@ def test_conv_alignment2_integer_bit_exact_split_k_and_padding_equivalence(bolt)
     assert_bit_equal(got_p, want, "padded integer conv")
 
 
+EVEN_EDGES = [
+    # N H W C K R S stride pad: one valid dword, two, three in a pixel's last 16 bytes; an odd and an even number of them per pixel;
+    # one tap; more taps than k-steps per wave; strides; a filter as large as the image; columns split (Q > a tile's pixels);
+    # channels past 64 and ragged against 16; the last pixel of the tensor inside the last tile
+    (1, 1, 1, 10, 8, 1, 1, 1, 0),
+    (3, 9, 11, 12, 24, 3, 3, 1, 1),
+    (2, 12, 10, 22, 72, 5, 7, (2, 1), (2, 3)),
+    (1, 6, 7, 54, 16, 6, 7, 1, 0),
+    (1, 3, 290, 18, 40, 3, 5, (1, 2), (1, 2)),
+    (2, 13, 9, 174, 64, 3, 3, 2, (0, 1)),
+]
+
+
+@pytest.mark.parametrize("case", EVEN_EDGES)
+def test_conv_even_channels_integer_bit_exact_every_instance(bolt, case):
+    """Integer sums stay exact in FP32 in any order, so the kernels that pad on the way to LDS equal the oracle bit for bit."""
+    N, H, W, Cc, K, R, S, stride, pad = case
+    x = wl.integer_fp16(213, 0, (N, H, W, Cc), -2, 2)
+    w = wl.integer_fp16(213, 1, (K, R, S, Cc), -1, 1)
+    bias = wl.integer_fp16(213, 2, (K,), -3, 3)
+    sh, sw = (stride, stride) if isinstance(stride, int) else stride
+    ph, pw = (pad, pad) if isinstance(pad, int) else pad
+    P, Q = (H + 2 * ph - R) // sh + 1, (W + 2 * pw - S) // sw + 1
+    res = wl.integer_fp16(213, 3, (N, P, Q, K), -4, 4)
+    want = ref.conv2d_nhwc(x, w, bias, stride=stride, pad=pad)
+    want_res = ref.conv2d_nhwc_residual(x, w, bias, res, stride=stride, pad=pad)
+    d = bolt.conv_desc(N, H, W, Cc, K, R, S, stride, pad)
+    ids = [k for k in _pingpong_ids(bolt, bolt.OP_CONV2D) if bolt.bolt_instance_supports(bolt.OP_CONV2D, k, d)]
+    assert len(ids) >= 12
+    y = torch.empty(want.shape, dtype=torch.float16, device="cuda")
+    tx, tw, tb, tr = dev(x), dev(w), dev(bias), dev(res)
+    for kid in ids:
+        _say("even channels %s instance %d" % (case, kid))
+        y.fill_(float("nan"))
+        bolt.bolt_conv2d_fprop_nhwc(d, tx, tw, tb, y, config={"kernel_id": kid})
+        assert_bit_equal(host(y), want, "even channels %s instance %d" % (case, kid))
+        y.fill_(float("nan"))
+        bolt.bolt_conv2d_fprop_nhwc_residual(d, tx, tw, tb, tr, y, config={"kernel_id": kid})
+        assert_bit_equal(host(y), want_res, "even channels + residual %s instance %d" % (case, kid))
+    bolt.bolt_conv2d_fprop_nhwc(d, tx, tw, tb, y)  # built-in pick rule
+    assert_bit_equal(host(y), want, "even channels %s pick rule" % (case,))
+
+
+def test_conv_even_channels_infinities_stay_where_they_belong(bolt):
+    """An infinite weight (or input) must not meet the zeros that stand for missing channels: 0 * inf is not 0."""
+    x = torch.ones((1, 4, 5, 10), dtype=torch.float16, device="cuda")
+    w = torch.ones((16, 2, 2, 10), dtype=torch.float16, device="cuda")
+    w[3, 0, 1, 0] = w[5, 1, 1, 9] = float("inf")
+    d = bolt.conv_desc(1, 4, 5, 10, 16, 2, 2, 1, 0)
+    for kid in _pingpong_ids(bolt, bolt.OP_CONV2D):
+        if bolt.bolt_instance_supports(bolt.OP_CONV2D, kid, d):
+            y = torch.empty((1, 3, 4, 16), dtype=torch.float16, device="cuda")
+            bolt.bolt_conv2d_fprop_nhwc(d, x, w, None, y, config={"kernel_id": kid})
+            want = torch.full_like(y, 40)
+            want[..., 3] = want[..., 5] = float("inf")
+            assert torch.equal(y, want), kid
+            xi = x.clone()
+            xi[0, 0, 1, 0] = float("inf")  # the pixel behind pixel (0, 0): the latter's padding must not see it
+            bolt.bolt_conv2d_fprop_nhwc(d, xi, torch.ones_like(w), None, y, config={"kernel_id": kid})
+            want = torch.full_like(y, 40)
+            want[0, 0, 0] = want[0, 0, 1] = float("inf")
+            assert torch.equal(y, want), kid
+
+
 def test_conv_integer_inputs_bit_exact(bolt):
     N, H, W, Cc, K, R, S, stride, pad = 2, 13, 11, 8, 24, 3, 3, 1, 1
     x = wl.integer_fp16(202, 0, (N, H, W, Cc), -2, 2)
