@@ -283,13 +283,15 @@ hipError_t launch_conv_even(const FpropParams& p, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// In the instance table: x mode and w mode 2 (even channel counts), tile = 16 FM pixels x 16 FN channels, tile K = the 32
-// of one matrix instruction, NW k-groups of one wave.
-#define BOLT_CONV_EVEN_INSTANCE(NW, FM, FN)                                                               \
-  {                                                                                                       \
-    "even_" #NW "w_" #FM "x" #FN, 16 * FM, 16 * FN, 32, 1, 1, 2, 2, 2, 0, &bolt::launch_conv_even<NW, FM, FN>, \
-        &bolt::ConvEvenTraits<NW, FM, FN>::supports, &bolt::ConvEvenTraits<NW, FM, FN>::lds_bytes, NW, 16, \
-        false, false, false, &bolt::ConvEvenTraits<NW, FM, FN>::estimate                                  \
+// In the instance table: x mode and w mode 2 (even channel counts), tile = 16 FM pixels x 16 FN channels, stated as the
+// multiple of 32 that holds it (the unit of every tile in the table), tile K = the 32 of one matrix instruction, NW
+// waves as k-groups of 4.
+#define BOLT_CONV_EVEN_INSTANCE(NW, FM, FN)                                                                      \
+  {                                                                                                              \
+    "even_" #NW "w_" #FM "x" #FN, (16 * FM + 31) / 32 * 32, (16 * FN + 31) / 32 * 32, 32, 4, 1, 2, 2, 2, 0,       \
+        &bolt::launch_conv_even<NW, FM, FN>, &bolt::ConvEvenTraits<NW, FM, FN>::supports,                        \
+        &bolt::ConvEvenTraits<NW, FM, FN>::lds_bytes, NW / 4, 16, false, false, false,                           \
+        &bolt::ConvEvenTraits<NW, FM, FN>::estimate                                                              \
   }
 
 }  // namespace bolt
