@@ -243,6 +243,8 @@ struct Tables {
     register_conv_smallc_instances(conv);  // first layers: at most 4 channels, unpadded NHWC or NCHW
     register_conv_nchw_out_instances(conv);  // last layers: the output written as NCHW
     register_conv_even_instances(conv);  // even channel counts again (appended: the older families keep their kernel ids)
+    register_gemm_ws_instances(gemm);  // small problems (appended, as above)
+    register_conv_ws_instances(conv);
     register_b2b_gemm_instances(b2b_gemm);
     register_b2b_gemm_dma_instances(b2b_gemm);
     register_b2b_gemm_dma_kn_instances(b2b_gemm);
@@ -450,6 +452,35 @@ static int fprop_heuristic(const std::vector<FpropInstance>& tab, const FpropPro
   return best;
 }
 
+// The rule's answer for a problem, remembered per thread in a small direct-mapped table: estimating every instance costs
+// 0.8 us of host time per call, as much as a quarter of the smallest launch.  The key is every number that the rule and
+// the instances' legality tests read (sizes, leading dimensions, geometry, modes), no address; a collision replaces.
+static int fprop_pick(const std::vector<FpropInstance>& tab, const FpropProblem& pr, bool need_split_k) {
+  if (tune_log_enabled()) return fprop_heuristic(tab, pr, need_split_k);
+  struct Key {
+    const void* tab;
+    int flags, M, N, K, ldx, ldw, ldy;
+    ConvGeom cg;
+  };
+  static_assert(sizeof(Key) == sizeof(void*) + (7 + 11) * sizeof(int), "compared as bytes: no padding");
+  const FpropParams& p = pr.p;
+  const Key key{&tab, pr.xmode | pr.wmode << 4 | (pr.residual ? 256 : 0) | (p.x_nchw ? 512 : 0) | (p.y_nchw ? 1024 : 0) | (need_split_k ? 2048 : 0),
+                p.M, p.N, p.K, p.ldx, p.ldw, p.ldy, p.cg};
+  struct Entry {
+    Key key;
+    int id;
+  };
+  static thread_local Entry memo[64];  // (zero: no table at a null address)
+  unsigned h = (unsigned)key.flags;
+  for (int v : {key.M, key.N, key.K, key.ldx, key.cg.H, key.cg.R, key.cg.stride_h}) h = (h ^ (unsigned)v) * 0x9E3779B1u;
+  Entry& e = memo[h >> 26];
+  if (std::memcmp(&e.key, &key, sizeof(key)) != 0) {
+    e.id = fprop_heuristic(tab, pr, need_split_k);
+    e.key = key;
+  }
+  return e.id;
+}
+
 static size_t splitk_bytes(int M, int N, int split_k) {
   return split_k > 1 ? (size_t)split_k * (size_t)M * (size_t)N * sizeof(float) : 0;
 }
@@ -540,7 +571,7 @@ static bolt_status resolve_fprop(const std::vector<FpropInstance>& tab, const Fp
     return BOLT_OK;
   }
   if (cfg && cfg->kernel_id < -1) return BOLT_ERR_INVALID_ARG;
-  *id = fprop_heuristic(tab, pr, *split_k > 1);
+  *id = fprop_pick(tab, pr, *split_k > 1);
   if (*id < 0) return BOLT_ERR_UNSUPPORTED;
   // No config at all: the XCD-aware tile order with bands of 4 where the tile grid has more than one column (measured
   // over 27 problems under the rule's own picks: 6 % less time in total; the halo kernels, whose neighbouring row

@@ -134,12 +134,9 @@ struct EpilogueArgs {
   float gamma = 0.f;  // scale of the residual quad (Eq. 1 with a full matrix C), epilogue_quad_res only
 };
 
+// The arithmetic for a quad whose bias (zeros for columns beyond N) is already in registers.
 template <bool SLOW, bool RES>
-__device__ __forceinline__ half4 epilogue_quad4_impl(floatx4 a4, int n, const EpilogueArgs& ep, half4 res) {
-  // columns beyond N (the zero-padded part of a compiled width) take a zero bias: their value is act(0), finite
-  // whatever beta * bias is, so a fused op that multiplies them by zero weights never sees inf * 0
-  const half4 hb_in = *(const half4*)(ep.bias + (n < ep.N ? n : 0) * ep.bias_on);
-  const half4 hb = n < ep.N ? hb_in : half4{0, 0, 0, 0};
+__device__ __forceinline__ half4 epilogue_quad4_values(floatx4 a4, half4 hb, const EpilogueArgs& ep, half4 res) {
   half4 o;
   floatx4 v;
 #pragma unroll
@@ -159,6 +156,13 @@ __device__ __forceinline__ half4 epilogue_quad4_impl(floatx4 a4, int n, const Ep
 #pragma unroll
   for (int e = 0; e < 4; ++e) o[e] = (half_t)v[e];
   return o;
+}
+template <bool SLOW, bool RES>
+__device__ __forceinline__ half4 epilogue_quad4_impl(floatx4 a4, int n, const EpilogueArgs& ep, half4 res) {
+  // columns beyond N (the zero-padded part of a compiled width) take a zero bias: their value is act(0), finite
+  // whatever beta * bias is, so a fused op that multiplies them by zero weights never sees inf * 0
+  const half4 hb_in = *(const half4*)(ep.bias + (n < ep.N ? n : 0) * ep.bias_on);
+  return epilogue_quad4_values<SLOW, RES>(a4, n < ep.N ? hb_in : half4{0, 0, 0, 0}, ep, res);
 }
 template <bool SLOW, bool RES>
 __device__ __forceinline__ half4 epilogue_quad_impl(const floatx16& acc, int q, int n, const EpilogueArgs& ep, half4 res) {

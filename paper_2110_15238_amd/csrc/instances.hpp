@@ -19,6 +19,7 @@
 #include "fprop_dma_kernel.hpp"
 #include "fprop_kernel.hpp"
 #include "fprop_pp_kernel.hpp"
+#include "fprop_ws_kernel.hpp"
 
 // The lists below are what survived a measurement: every tile shape tried during development was
 // timed by bolt_tune on the workloads of Section 4 (the ResNet-50 layers at batch 32, the GEMM and
@@ -122,6 +123,8 @@ void register_conv_instances(std::vector<FpropInstance>& v);
 void register_conv_halo_instances(std::vector<FpropInstance>& v);
 void register_conv_align2_instances(std::vector<FpropInstance>& v);
 void register_conv_even_instances(std::vector<FpropInstance>& v);
+void register_gemm_ws_instances(std::vector<FpropInstance>& v);
+void register_conv_ws_instances(std::vector<FpropInstance>& v);
 void register_conv_smallc_instances(std::vector<FpropInstance>& v);
 void register_conv_nchw_out_instances(std::vector<FpropInstance>& v);
 void register_b2b_gemm_instances(std::vector<B2bInstance>& v);

@@ -391,6 +391,76 @@ def test_conv_even_channels_infinities_stay_where_they_belong(bolt):
             assert torch.equal(y, want), kid
 
 
+def _wave_split_ids(bolt, op, *descs):
+    """Instances that split the reduction over their waves: tile K of one matrix instruction, nothing else to split."""
+    cfg = lambda k: bolt.bolt_instance_config(op, k)
+    return [k for k in _pingpong_ids(bolt, op) if cfg(k).tile_k == 32 and bolt.bolt_instance_supports(op, k, *descs)]
+
+
+@pytest.mark.parametrize("layout", ["nk", "kn"])
+@pytest.mark.parametrize("shape", [(1, 8, 8), (16, 16, 64), (17, 24, 72), (33, 40, 520), (49, 136, 1096), (200, 72, 264), (5, 1000, 4104)])
+def test_gemm_wave_split_integer_bit_exact_with_gaps_and_residual(bolt, layout, shape):
+    """Edges of the 16 and 32-wide tiles, units of 64 with a tail, waves without work; rows end in poisoned gaps."""
+    M, N, K = shape
+    A, B = wl.integer_fp16(241, 0, (M, K), -2, 2), wl.integer_fp16(241, 1, (K, N), -1, 1)
+    bias, C = wl.integer_fp16(241, 2, (N,), -3, 3), wl.integer_fp16(241, 3, (M, N), -4, 4)
+    want, want_res = ref.gemm(A, B, bias), ref.gemm_residual(A, B, bias, C)
+    W = B if layout == "kn" else np.ascontiguousarray(B.T)
+
+    def gap(a):
+        t = np.full((a.shape[0], a.shape[1] + 16), np.nan, np.float16)
+        t[:, :a.shape[1]] = a
+        return dev(t)
+
+    d = bolt.gemm_desc(M, N, K, lda=K + 16, ldb=W.shape[1] + 16, ldd=N + 16,
+                       b_layout=bolt.LAYOUT_NK if layout == "nk" else bolt.LAYOUT_KN)
+    ids = _wave_split_ids(bolt, bolt.OP_GEMM, d)
+    assert len(ids) >= 8
+    tA, tW, tb, tC = gap(A), gap(W), dev(bias), dev(C)
+    D = torch.empty((M, N + 16), dtype=torch.float16, device="cuda")
+    for kid in ids + [-1]:  # and the built-in pick
+        _say("wave split %s %s instance %d" % (layout, shape, kid))
+        D.fill_(float("nan"))
+        bolt.bolt_gemm_epilogue(d, tA, tW, tb, D, config={"kernel_id": kid})
+        assert_bit_equal(host(D)[:, :N], want, "wave split %s %s instance %d" % (layout, shape, kid))
+        D.fill_(float("nan"))
+        bolt.bolt_gemm_epilogue_residual(d, tA, tW, tb, tC, D, config={"kernel_id": kid})
+        assert_bit_equal(host(D)[:, :N], want_res, "wave split + residual %s %s instance %d" % (layout, shape, kid))
+        assert torch.isnan(D[:, N:]).all()
+
+
+@pytest.mark.parametrize("case", [
+    # N H W C K R S stride pad: one pixel; a unit of 64 that holds eight taps; taps that begin inside a unit; strides and
+    # windows over every edge; more taps than units per wave; rows of several images in one tile
+    (1, 1, 1, 8, 8, 1, 1, 1, 0),
+    (2, 5, 7, 8, 24, 3, 3, 1, 1),
+    (1, 9, 8, 40, 16, 5, 3, (2, 1), (2, 0)),
+    (3, 4, 4, 72, 40, 3, 3, 1, 1),
+    (1, 14, 14, 128, 64, 1, 1, 2, 0),
+    (1, 6, 6, 16, 48, 6, 7, 1, (3, 3)),
+])
+def test_conv_wave_split_integer_bit_exact(bolt, case):
+    N, H, W, Cc, K, R, S, stride, pad = case
+    x, w = wl.integer_fp16(242, 0, (N, H, W, Cc), -2, 2), wl.integer_fp16(242, 1, (K, R, S, Cc), -1, 1)
+    bias = wl.integer_fp16(242, 2, (K,), -3, 3)
+    want = ref.conv2d_nhwc(x, w, bias, stride=stride, pad=pad)
+    res = wl.integer_fp16(242, 3, want.shape, -4, 4)
+    want_res = ref.conv2d_nhwc_residual(x, w, bias, res, stride=stride, pad=pad)
+    d = bolt.conv_desc(N, H, W, Cc, K, R, S, stride, pad)
+    ids = _wave_split_ids(bolt, bolt.OP_CONV2D, d)
+    assert len(ids) >= 8
+    y = torch.empty(want.shape, dtype=torch.float16, device="cuda")
+    tx, tw, tb, tr = dev(x), dev(w), dev(bias), dev(res)
+    for kid in ids + [-1]:
+        _say("wave split conv %s instance %d" % (case, kid))
+        y.fill_(float("nan"))
+        bolt.bolt_conv2d_fprop_nhwc(d, tx, tw, tb, y, config={"kernel_id": kid})
+        assert_bit_equal(host(y), want, "wave split conv %s instance %d" % (case, kid))
+        y.copy_(tr)  # the output buffer may be the residual itself
+        bolt.bolt_conv2d_fprop_nhwc_residual(d, tx, tw, tb, y, y, config={"kernel_id": kid})
+        assert_bit_equal(host(y), want_res, "wave split conv + residual %s instance %d" % (case, kid))
+
+
 def test_conv_integer_inputs_bit_exact(bolt):
     N, H, W, Cc, K, R, S, stride, pad = 2, 13, 11, 8, 24, 3, 3, 1, 1
     x = wl.integer_fp16(202, 0, (N, H, W, Cc), -2, 2)
