@@ -1,4 +1,5 @@
-"""Thin ctypes binding of libbolt.so (include/bolt.h).  Argument marshalling only.
+"""Thin binding of libbolt.so (include/bolt.h).  Argument marshalling only: through ctypes, and for the launch calls
+with plain arguments through the extension _fastcall (csrc/fastcall.cpp), which does the same in C++.
 
 Every function takes torch CUDA (ROCm) float16 tensors, passes their device pointers and the
 current HIP stream to the C ABI, and raises BoltError on a non-zero status.  There is no fallback:
@@ -63,6 +64,11 @@ class BoltError(RuntimeError):
 if not os.path.exists(LIB_PATH):
     raise ImportError("libbolt.so is not built: run `python -c 'import __graft_entry__ as g; g.build()'` "
                       "(or `make -C paper_2110_15238_amd/csrc`) first; there is no fallback path")
+
+FASTCALL_PATH = os.path.join(_HERE, "_fastcall.so")
+if not os.path.exists(FASTCALL_PATH):
+    raise ImportError("_fastcall.so is not built: run `python -c 'import __graft_entry__ as g; g.build()'` "
+                      "(or `make -C paper_2110_15238_amd/csrc`) first")
 
 _lib = C.CDLL(LIB_PATH)
 _vp, _i32, _sz = C.c_void_p, C.c_int32, C.c_size_t
@@ -165,6 +171,19 @@ def _load_torch():
     return torch
 
 
+_fast = None
+
+
+def _load_fast():
+    """The extension needs torch in the process, which this module loads with the first tensor."""
+    global _fast
+    _load_torch()
+    from . import _fastcall
+    _fastcall.types(GemmDesc, ConvDesc, BoltConfig)
+    _fast = _fastcall
+    return _fastcall
+
+
 def _stream() -> int:
     torch = _torch or _load_torch()
     if _raw_stream is not None:
@@ -249,6 +268,11 @@ def workspace_bytes(op: int, desc0, desc1=None, config=None) -> int:
 
 
 def gemm_epilogue(desc: GemmDesc, A, B, bias, D, config=None, workspace=None):
+    status = (_fast or _load_fast()).gemm(desc, A, B, bias, D, config, workspace)
+    if status == 0:
+        return D
+    if status is not None:
+        raise BoltError(status, "bolt_gemm_epilogue")
     c = _cfg(config)
     wp, wb = _ws(workspace)
     _check(_lib.bolt_gemm_epilogue(C.byref(desc), _ptr(A), _ptr(B), _ptr(bias), _ptr(D),
@@ -265,6 +289,11 @@ def gemm_epilogue_noalloc(desc: GemmDesc, A, B, bias, D, config=None):
 
 
 def conv2d_fprop_nhwc(desc: ConvDesc, x, w, bias, y, config=None, workspace=None):
+    status = (_fast or _load_fast()).conv(desc, x, w, bias, y, config, workspace)
+    if status == 0:
+        return y
+    if status is not None:
+        raise BoltError(status, "bolt_conv2d_fprop_nhwc")
     c = _cfg(config)
     wp, wb = _ws(workspace)
     _check(_lib.bolt_conv2d_fprop_nhwc(C.byref(desc), _ptr(x), _ptr(w), _ptr(bias), _ptr(y),
@@ -275,6 +304,11 @@ def conv2d_fprop_nhwc(desc: ConvDesc, x, w, bias, y, config=None, workspace=None
 
 def gemm_epilogue_residual(desc: GemmDesc, A, B, bias, Cres, D, gamma: float = 1.0, config=None, workspace=None):
     """D = act(alpha A.B + beta bias + gamma Cres); Cres is a contiguous M x N tensor."""
+    status = (_fast or _load_fast()).gemm_residual(desc, A, B, bias, Cres, D, gamma, config, workspace)
+    if status == 0:
+        return D
+    if status is not None:
+        raise BoltError(status, "bolt_gemm_epilogue_residual")
     c = _cfg(config)
     wp, wb = _ws(workspace)
     _check(_lib.bolt_gemm_epilogue_residual(C.byref(desc), _ptr(A), _ptr(B), _ptr(bias), _ptr(Cres), Cres.shape[-1], gamma,
@@ -284,6 +318,11 @@ def gemm_epilogue_residual(desc: GemmDesc, A, B, bias, Cres, D, gamma: float = 1
 
 
 def conv2d_fprop_nhwc_residual(desc: ConvDesc, x, w, bias, residual, y, gamma: float = 1.0, config=None, workspace=None):
+    status = (_fast or _load_fast()).conv_residual(desc, x, w, bias, residual, y, gamma, config, workspace)
+    if status == 0:
+        return y
+    if status is not None:
+        raise BoltError(status, "bolt_conv2d_fprop_nhwc_residual")
     c = _cfg(config)
     wp, wb = _ws(workspace)
     _check(_lib.bolt_conv2d_fprop_nhwc_residual(C.byref(desc), _ptr(x), _ptr(w), _ptr(bias), _ptr(residual), gamma, _ptr(y),
@@ -293,6 +332,11 @@ def conv2d_fprop_nhwc_residual(desc: ConvDesc, x, w, bias, residual, y, gamma: f
 
 
 def b2b_gemm(g0: GemmDesc, g1: GemmDesc, A0, W0, b0, W1, b1, D1, config=None):
+    status = (_fast or _load_fast()).gemm_pair(g0, g1, A0, W0, b0, W1, b1, D1, config)
+    if status == 0:
+        return D1
+    if status is not None:
+        raise BoltError(status, "bolt_b2b_gemm")
     c = _cfg(config)
     _check(_lib.bolt_b2b_gemm(C.byref(g0), C.byref(g1), _ptr(A0), _ptr(W0), _ptr(b0), _ptr(W1), _ptr(b1), _ptr(D1),
                               None if c is None else C.byref(c), None, 0, _stream()), "bolt_b2b_gemm")
@@ -300,6 +344,11 @@ def b2b_gemm(g0: GemmDesc, g1: GemmDesc, A0, W0, b0, W1, b1, D1, config=None):
 
 
 def b2b_conv(c0: ConvDesc, c1: ConvDesc, x, w0, b0, w1, b1, y, config=None):
+    status = (_fast or _load_fast()).conv_pair(c0, c1, x, w0, b0, w1, b1, y, config)
+    if status == 0:
+        return y
+    if status is not None:
+        raise BoltError(status, "bolt_b2b_conv")
     c = _cfg(config)
     _check(_lib.bolt_b2b_conv(C.byref(c0), C.byref(c1), _ptr(x), _ptr(w0), _ptr(b0), _ptr(w1), _ptr(b1), _ptr(y),
                               None if c is None else C.byref(c), None, 0, _stream()), "bolt_b2b_conv")
@@ -350,6 +399,11 @@ def _ptr_array(tensors):
 
 def b2b_gemm_chain(descs, A0, weights, biases, D, config=None):
     """descs: GemmDesc list; weights / biases: lists of device tensors (a bias may be None)."""
+    status = (_fast or _load_fast()).gemm_chain(descs, A0, weights, biases, D, config)
+    if status == 0:
+        return D
+    if status is not None:
+        raise BoltError(status, "bolt_b2b_gemm_chain")
     c = _cfg(config)
     _check(_lib.bolt_b2b_gemm_chain(len(descs), _desc_array(descs), _ptr(A0), _ptr_array(weights), _ptr_array(biases),
                                     _ptr(D), None if c is None else C.byref(c), _stream()), "bolt_b2b_gemm_chain")
@@ -357,6 +411,11 @@ def b2b_gemm_chain(descs, A0, weights, biases, D, config=None):
 
 
 def b2b_conv_chain(descs, x, weights, biases, y, config=None):
+    status = (_fast or _load_fast()).conv_chain(descs, x, weights, biases, y, config)
+    if status == 0:
+        return y
+    if status is not None:
+        raise BoltError(status, "bolt_b2b_conv_chain")
     c = _cfg(config)
     _check(_lib.bolt_b2b_conv_chain(len(descs), _desc_array(descs), _ptr(x), _ptr_array(weights), _ptr_array(biases),
                                     _ptr(y), None if c is None else C.byref(c), _stream()), "bolt_b2b_conv_chain")

@@ -170,3 +170,53 @@ def test_random_conv_chain_built_in_pick_and_tuned(bolt, seed):
     bolt.bolt_b2b_conv_chain(descs, xd, wd, bd, y, res.config)
     torch.cuda.synchronize()
     assert_close(host(y), want, "random conv chain %d, tuned %s" % (seed, res.config.as_dict()))
+
+
+def test_plain_and_general_argument_paths_agree(bolt):
+    """Calls whose arguments are all of the plain kinds are marshalled in C++, others in Python (a dict as configuration):
+    the same results, and the same errors with the same status."""
+    from paper_2110_15238_amd import binding
+    fast = binding._load_fast()
+    h = lambda *s: torch.randn(s, device="cuda").half()
+    g0, g1, g2 = (bolt.gemm_desc(200, n, k) for n, k in ((32, 64), (64, 32), (32, 64)))
+    c0, c1 = bolt.conv_desc(2, 9, 9, 64, 32, 3, 3, 1, 1), bolt.conv_desc(2, 9, 9, 32, 64, 1, 1)
+    c2 = bolt.conv_desc(2, 9, 9, 64, 32, 1, 1)
+    A, W0, W1, W2 = h(200, 64), h(64, 32), h(32, 64), h(64, 32)
+    x, v0, v1, v2 = h(2, 9, 9, 64), h(32, 3, 3, 64), h(64, 1, 1, 32), h(32, 1, 1, 64)
+    b32, b64 = h(32), h(64)
+    calls = [
+        (bolt.bolt_gemm_epilogue, (g0, A, W0, b32), (200, 32)),
+        (bolt.bolt_gemm_epilogue_residual, (g0, A, W0, None, h(200, 32)), (200, 32)),
+        (bolt.bolt_conv2d_fprop_nhwc, (c0, x, v0, b32), (2, 9, 9, 32)),
+        (bolt.bolt_conv2d_fprop_nhwc_residual, (c0, x, v0, b32, h(2, 9, 9, 32)), (2, 9, 9, 32)),
+        (bolt.bolt_b2b_gemm, (g0, g1, A, W0, b32, W1, None), (200, 64)),
+        (bolt.bolt_b2b_conv, (c0, c1, x, v0, b32, v1, b64), (2, 9, 9, 64)),
+        (bolt.bolt_b2b_gemm_chain, ([g0, g1, g2], A, [W0, W1, W2], [b32, None, b32]), (200, 32)),
+        (bolt.bolt_b2b_conv_chain, ([c0, c1, c2], x, [v0, v1, v2], [b32, b64, None]), (2, 9, 9, 32)),
+    ]
+    for fn, args, shape in calls:
+        out = [torch.full(shape, float("nan"), dtype=torch.float16, device="cuda") for _ in range(3)]
+        for y, config in zip(out, (None, bolt.BoltConfig(kernel_id=-1), {"kernel_id": -1})):
+            assert fn(*args, y, config=config) is y
+        assert not torch.isnan(out[0]).any() and torch.equal(out[1], out[2]), fn
+        for config in (bolt.BoltConfig(kernel_id=10 ** 6), {"kernel_id": 10 ** 6}):
+            with pytest.raises(bolt.BoltError) as e:
+                fn(*args, out[0], config=config)
+            assert e.value.status == 1, fn
+        with pytest.raises(AssertionError):
+            fn(*args, out[0].float())
+    # what is not plain goes the general way
+    y = torch.empty((200, 32), dtype=torch.float16, device="cuda")
+    assert fast.gemm(g0, A, W0, b32, y, {"kernel_id": -1}, None) is None
+    assert fast.gemm(g0, A.cpu(), W0, b32, y, None, None) is None
+    assert fast.gemm(g0, A.t(), W0, b32, y, None, None) is None
+    assert fast.gemm(c0, A, W0, b32, y, None, None) is None
+    assert fast.gemm(g0, None, W0, b32, y, None, None) is None
+    # the current stream is the one that the call uses
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        bolt.bolt_gemm_epilogue(g0, A, W0, b32, y)
+        done = torch.cuda.Event()
+        done.record()
+    done.synchronize()
+    assert torch.equal(y, bolt.bolt_gemm_epilogue(g0, A, W0, b32, torch.empty_like(y)))
