@@ -245,6 +245,7 @@ struct Tables {
     register_conv_even_instances(conv);  // even channel counts again (appended: the older families keep their kernel ids)
     register_gemm_ws_instances(gemm);  // small problems (appended, as above)
     register_conv_ws_instances(conv);
+    register_conv_first_instances(conv);  // first layers of 3 or 4 channels
     register_b2b_gemm_instances(b2b_gemm);
     register_b2b_gemm_dma_instances(b2b_gemm);
     register_b2b_gemm_dma_kn_instances(b2b_gemm);

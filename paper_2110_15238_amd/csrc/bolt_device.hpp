@@ -87,9 +87,8 @@ __device__ __forceinline__ float hardswish_fast(float v) {
   return v * fminf(fmaxf(v + 3.f, 0.f), 6.f) * (1.f / 6.f);
 }
 
-// The fully unrolled epilogues call this once per 4 outputs; out of line so that they stay small.
 // act is wave-uniform: the switch is scalar branches.
-__device__ __attribute__((noinline)) floatx4 apply_act_slow4(floatx4 v, int act) {
+__device__ __forceinline__ floatx4 apply_act_slow4_inline(floatx4 v, int act) {
   switch (act) {
     case ACT_GELU:
 #pragma unroll
@@ -107,6 +106,9 @@ __device__ __attribute__((noinline)) floatx4 apply_act_slow4(floatx4 v, int act)
   }
   return v;
 }
+// The fully unrolled epilogues call this once per 4 outputs; out of line so that they stay small.  (A kernel that keeps
+// more than half of its registers across the epilogue takes the inline form: a call leaves it half of them.)
+__device__ __attribute__((noinline)) floatx4 apply_act_slow4(floatx4 v, int act) { return apply_act_slow4_inline(v, act); }
 
 __device__ __forceinline__ float apply_act(float v, int act) {
   switch (act) {

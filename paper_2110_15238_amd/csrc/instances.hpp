@@ -12,6 +12,7 @@
 #include "b2b_dma_kernel.hpp"
 #include "b2b_kernel.hpp"
 #include "conv_even_kernel.hpp"
+#include "conv_first_kernel.hpp"
 #include "conv_halo_kernel.hpp"
 #include "conv_smallc_kernel.hpp"
 #include "b2b_chain_kernel.hpp"
@@ -125,6 +126,7 @@ void register_conv_align2_instances(std::vector<FpropInstance>& v);
 void register_conv_even_instances(std::vector<FpropInstance>& v);
 void register_gemm_ws_instances(std::vector<FpropInstance>& v);
 void register_conv_ws_instances(std::vector<FpropInstance>& v);
+void register_conv_first_instances(std::vector<FpropInstance>& v);
 void register_conv_smallc_instances(std::vector<FpropInstance>& v);
 void register_conv_nchw_out_instances(std::vector<FpropInstance>& v);
 void register_b2b_gemm_instances(std::vector<B2bInstance>& v);

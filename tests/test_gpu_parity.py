@@ -1143,6 +1143,45 @@ def test_first_layer_conv_every_instance(bolt, shape, layout):
     assert_close(host(y), ref.conv2d_nhwc(x, w, None, stride=stride, pad=pad, act="hardswish"), "first layer %s %s heuristic" % (shape, layout))
 
 
+@pytest.mark.parametrize("layout", ["nhwc", "nchw"])
+@pytest.mark.parametrize("case", [
+    # N H W C K R S stride pad: one pixel; odd widths (rows at 2-byte boundaries); strips with a ragged last one; columns in
+    # two strips; several blocks of 64 channels, ragged; odd and even filter widths, one row, one column; windows over edges
+    (1, 1, 1, 3, 8, 1, 1, 1, 0),
+    (2, 19, 23, 3, 64, 7, 7, 2, 3),
+    (1, 40, 277, 3, 72, 3, 3, 2, 1),
+    (3, 13, 150, 4, 136, 5, 5, 1, 2),
+    (2, 9, 33, 4, 24, 3, 4, (1, 2), (1, 3)),
+    (1, 30, 17, 3, 16, 1, 7, (3, 1), (0, 3)),
+    (32, 33, 31, 3, 40, 3, 2, 1, 1),
+])
+def test_first_layer_strips_integer_bit_exact(bolt, case, layout):
+    N, H, W, Cc, K, R, S, stride, pad = case
+    x, w = wl.integer_fp16(251, 0, (N, H, W, Cc), -3, 3), wl.integer_fp16(251, 1, (K, R, S, Cc), -2, 2)
+    bias = wl.integer_fp16(251, 2, (K,), -3, 3)
+    want = ref.conv2d_nhwc(x, w, bias, stride=stride, pad=pad)
+    tx = dev(np.ascontiguousarray(x.transpose(0, 3, 1, 2)) if layout == "nchw" else x)
+    d = bolt.conv_desc(N, H, W, Cc, K, R, S, stride, pad, x_layout=layout)
+    ids = [k for k in range(bolt.bolt_num_instances(bolt.OP_CONV2D)) if bolt.bolt_instance_supports(bolt.OP_CONV2D, k, d)]
+    assert any(bolt.bolt_instance_config(bolt.OP_CONV2D, k).stages == 1 for k in ids)
+    y = torch.empty(want.shape, dtype=torch.float16, device="cuda")
+    yt = torch.empty((N, K) + want.shape[1:3], dtype=torch.float16, device="cuda")
+    dt = bolt.conv_desc(N, H, W, Cc, K, R, S, stride, pad, x_layout=layout, y_layout="nchw")
+    for kid in ids + [-1]:
+        _say("first layer %s %s instance %d" % (case, layout, kid))
+        y.fill_(float("nan"))
+        bolt.bolt_conv2d_fprop_nhwc(d, tx, dev(w), dev(bias), y, config={"kernel_id": kid})
+        assert_bit_equal(host(y), want, "first layer %s %s instance %d" % (case, layout, kid))
+        if kid < 0 or bolt.bolt_instance_supports(bolt.OP_CONV2D, kid, dt):
+            yt.fill_(float("nan"))
+            bolt.bolt_conv2d_fprop_nhwc(dt, tx, dev(w), dev(bias), yt, config={"kernel_id": kid})
+            assert_bit_equal(host(yt).transpose(0, 2, 3, 1), want, "first layer to NCHW %s %s instance %d" % (case, layout, kid))
+    for act in ("none", "gelu", "hardswish", "softplus"):
+        d.act = bolt.ACT[act]
+        bolt.bolt_conv2d_fprop_nhwc(d, tx, dev(w), dev(bias), y)
+        assert_close(host(y), ref.conv2d_nhwc(x, w, bias, stride=stride, pad=pad, act=act), "first layer %s %s" % (case, act))
+
+
 def test_first_layer_conv_equals_the_padded_path_and_ignores_infinite_neighbours(bolt):
     """Channel padding is a pure re-scheduling (Section 3.2.3): the unpadded first-layer kernel and the padded C = 8
     convolution agree bit for bit on integers.  A tap past the filter's width reads the neighbouring pixel's data
