@@ -783,17 +783,31 @@ static bolt_status make_chain_problem(bolt_op op, int32_t n_ops, const void* con
   return BOLT_OK;
 }
 
+// GEMM chains whose rows stream through independent waves (chain_stream_kernel): the only ones with a legality rule of their own.
+static bool chain_streams(const ChainInstance& in) { return in.xmode == 0 && in.dyn_supports; }
+
 static int chain_heuristic(const std::vector<ChainInstance>& tab, const B2bProblem& pr) {
   int best = -1;
   double best_cost = 0;
   for (int i = 0; i < (int)tab.size(); ++i) {
-    if (!chain_supports(tab, i, pr)) continue;
+    if (chain_streams(tab[i]) || !chain_supports(tab, i, pr)) continue;
     // the tightest widths; the halo main loop where it applies; 64-row wave tiles (as for the fused pairs)
     double cost = (double)tab[i].n0t * tab[i].n1t + (double)tab[i].n1t * tab[i].n2t + 1e-3 * tab[i].lds_bytes;
     cost *= (tab[i].dyn_supports ? 0.75 : 1.0) * (1.0 + 32.0 / ((double)tab[i].bm / tab[i].waves));
     if (tune_log_enabled()) std::fprintf(stderr, "[bolt_pick] candidate %d %s cost %.4g\n", i, tab[i].name, cost);
     if (best < 0 || cost < best_cost) { best = i; best_cost = cost; }
   }
+  // The streaming kernel of the same widths where the tiled workgroups do not fit on the chip at once: they then run in
+  // rounds, each all fill and drain.  Over 36 problems (7 width sets, 1000 to 128320 rows, us, tiled / streaming): two rounds
+  // and more 12.2-27.9 / 9.5-16.5, no loss; one round 5.5-8.5 / 5.4-9.0, streaming up to 14 % behind or 7 % ahead.
+  if (best >= 0 && !tab[best].dyn_supports &&
+      ceil_div(pr.p.M, tab[best].bm) > 256 * std::max(1, kLdsPerCU / tab[best].lds_bytes))
+    for (int i = 0; i < (int)tab.size(); ++i)
+      if (chain_streams(tab[i]) && tab[i].n0t == tab[best].n0t && tab[i].n1t == tab[best].n1t && tab[i].n2t == tab[best].n2t &&
+          chain_supports(tab, i, pr)) {
+        best = i;
+        break;
+      }
   if (tune_log_enabled() && best >= 0) std::fprintf(stderr, "[bolt_pick] -> %d %s\n", best, tab[best].name);
   return best;
 }

@@ -1323,6 +1323,37 @@ def test_gemm_chain3_every_instance(bolt, shape, layout):
     assert_close(host(D), want, "gemm chain %s heuristic" % (shape,))
 
 
+@pytest.mark.parametrize("layout", ["nk", "kn"])
+@pytest.mark.parametrize("shape", [(65537, 128, 32, 128, 32), (65569, 104, 56, 64, 72), (131200, 8, 64, 24, 64), (40, 120, 40, 72, 40)])
+def test_gemm_chain3_rows_streamed_in_rounds(bolt, shape, layout):
+    """Instances that walk 32-row tiles: one tile, one row more than one round, several rounds; K0 to the bound, residual in place."""
+    M, K0, N0, N1, N2 = shape
+    L = bolt.LAYOUT_NK if layout == "nk" else bolt.LAYOUT_KN
+    A = wl.uniform_fp16(311, 0, (M, K0), -0.5, 0.5)
+    Ws = [wl.uniform_fp16(311, 1 + i, s, -0.5, 0.5) for i, s in enumerate([(K0, N0), (N0, N1), (N1, N2)])]
+    bs = [None, wl.uniform_fp16(311, 5, (N1,), -1, 1), wl.uniform_fp16(311, 6, (N2,), -1, 1)]
+    C = wl.uniform_fp16(311, 7, (M, N2), -1, 1)
+    acts = ["hardswish", "relu", "relu"]
+    want, want_res = ref.gemm_chain(A, Ws, bs, acts), ref.gemm_chain_residual(A, Ws, bs, acts, C, gamma=0.5)
+    descs = [bolt.gemm_desc(M, n, k, act=a, b_layout=L) for (k, n), a in zip([(K0, N0), (N0, N1), (N1, N2)], acts)]
+    Ad, bd = dev(A), [None if b is None else dev(b) for b in bs]
+    Wd = [dev(np.ascontiguousarray(W.T)) if layout == "nk" else dev(W) for W in Ws]
+    for kid in range(bolt.bolt_num_instances(bolt.OP_GEMM_CHAIN3)):
+        if not bolt.bolt_chain_instance_supports(bolt.OP_GEMM_CHAIN3, kid, descs):
+            continue
+        _say("gemm chain %s weights %s instance %d" % (shape, layout, kid))
+        D, R = torch.full((M, N2), float("nan"), dtype=torch.float16, device="cuda"), dev(C)
+        bolt.bolt_b2b_gemm_chain(descs, Ad, Wd, bd, D, {"kernel_id": kid})
+        bolt.bolt_b2b_gemm_chain_residual(descs, Ad, Wd, bd, R, R, gamma=0.5, config={"kernel_id": kid})
+        torch.cuda.synchronize()
+        assert_close(host(D), want, "gemm chain %s instance %d" % (shape, kid))
+        assert_close(host(R), want_res, "gemm chain %s residual in place, instance %d" % (shape, kid))
+    D = torch.full((M, N2), float("nan"), dtype=torch.float16, device="cuda")
+    bolt.bolt_b2b_gemm_chain(descs, Ad, Wd, bd, D)  # built-in pick rule, on either side of its line
+    torch.cuda.synchronize()
+    assert_close(host(D), want, "gemm chain %s heuristic" % (shape,))
+
+
 CONV_CHAINS = [  # (N, H, W, C, K0, R, S, stride, pad, K1, K2)
     (2, 12, 12, 64, 64, 3, 3, 1, 1, 64, 64), (1, 17, 13, 24, 48, 3, 3, 2, 1, 48, 48), (2, 23, 23, 8, 64, 7, 7, 2, 3, 64, 256),
     (3, 9, 11, 64, 64, 1, 1, 1, 0, 256, 64), (1, 10, 9, 16, 128, 5, 3, (1, 2), (2, 0), 64, 128),
