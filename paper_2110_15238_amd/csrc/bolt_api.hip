@@ -249,6 +249,7 @@ struct Tables {
     register_b2b_gemm_instances(b2b_gemm);
     register_b2b_gemm_dma_instances(b2b_gemm);
     register_b2b_gemm_dma_kn_instances(b2b_gemm);
+    register_b2b_gemm_stream_instances(b2b_gemm);
     register_b2b_conv_instances(b2b_conv);
     register_b2b_conv_dma_instances(b2b_conv);
     register_b2b_conv_halo_instances(b2b_conv);
@@ -623,11 +624,15 @@ static void b2b_fill_config(const B2bInstance& in, int id, bolt_config* c) {
   c->mfma_shape = 32; c->stages = in.stages; c->swizzle = 0; c->split_k = 1; c->b2b_mode = in.mode;
 }
 
+// GEMM pairs whose rows stream through independent waves (chain_stream_kernel): the only GEMM pairs with a legality rule of
+// their own.
+static bool b2b_streams(const B2bInstance& in) { return in.xmode == 0 && in.dyn_supports; }
+
 static int b2b_heuristic(const std::vector<B2bInstance>& tab, const B2bProblem& pr) {
   int best = -1;
   double best_cost = 0;
   for (int i = 0; i < (int)tab.size(); ++i) {
-    if (!b2b_supports(tab, i, pr)) continue;
+    if (b2b_streams(tab[i]) || !b2b_supports(tab, i, pr)) continue;
     const B2bInstance& in = tab[i];
     const double tiles = ceil_div(pr.p.M, in.bm);
     const int lds = in.dyn_lds_bytes ? in.dyn_lds_bytes(pr.p) : in.lds_bytes(pr.p.K0);
@@ -643,6 +648,17 @@ static int b2b_heuristic(const std::vector<B2bInstance>& tab, const B2bProblem& 
     cost *= 1.0 + 0.5 / std::min<double>(per_cu, std::max(1.0, std::ceil(tiles / kNumCU)));
     if (tune_log_enabled()) std::fprintf(stderr, "[bolt_pick] candidate %d %s cost %.4g\n", i, in.name, cost);
     if (best < 0 || cost < best_cost) { best = i; best_cost = cost; }
+  }
+  // More 128-row tiles than two per compute unit: the tiled kernels go round again, the streaming one overlaps the rounds.  Over
+  // 40 problems (8 width pairs, K0 32 to 128, 1000 to 131072 rows, us, best tiled / streaming): 131072 rows 8.4-17.5 / 7.0-14.4, no
+  // loss; 65536 rows 5.6-9.0 / 5.1-9.5, up to 10 % behind where op1 is wide.
+  if (best >= 0 && ceil_div(pr.p.M, 128) > 2 * kNumCU) {
+    int stream = -1;
+    for (int i = 0; i < (int)tab.size(); ++i)
+      if (b2b_streams(tab[i]) && b2b_supports(tab, i, pr) &&
+          (stream < 0 || tab[i].n0t * tab[i].n1t < tab[stream].n0t * tab[stream].n1t))
+        stream = i;
+    if (stream >= 0) best = stream;
   }
   if (tune_log_enabled() && best >= 0) std::fprintf(stderr, "[bolt_pick] -> %d %s\n", best, tab[best].name);
   return best;

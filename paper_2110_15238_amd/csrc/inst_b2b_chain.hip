@@ -14,6 +14,14 @@ namespace bolt {
 #define BOLT_CHAIN_STREAM_WIDTHS(WKN)                                                                   \
   BOLT_CHAIN_STREAM_INSTANCE(4, 128, 32, 128, 32, WKN), BOLT_CHAIN_STREAM_INSTANCE(4, 128, 64, 64, 64, WKN), \
   BOLT_CHAIN_STREAM_INSTANCE(4, 128, 64, 128, 64, WKN), BOLT_CHAIN_STREAM_INSTANCE(4, 128, 64, 64, 128, WKN)
+#define BOLT_PAIR_STREAM_WIDTHS(WKN)                                                                 \
+  BOLT_PAIR_STREAM_INSTANCE(4, 128, 32, 128, WKN), BOLT_PAIR_STREAM_INSTANCE(4, 128, 64, 32, WKN),     \
+  BOLT_PAIR_STREAM_INSTANCE(4, 128, 64, 64, WKN), BOLT_PAIR_STREAM_INSTANCE(4, 128, 64, 128, WKN),     \
+  BOLT_PAIR_STREAM_INSTANCE(4, 128, 128, 64, WKN)
+void register_b2b_gemm_stream_instances(std::vector<B2bInstance>& v) {
+  static const B2bInstance table[] = {BOLT_PAIR_STREAM_WIDTHS(false), BOLT_PAIR_STREAM_WIDTHS(true)};
+  for (const auto& t : table) v.push_back(t);
+}
 void register_gemm_chain_instances(std::vector<ChainInstance>& v) {
   static const ChainInstance table[] = {BOLT_CHAIN_WIDTHS(CH, 0), BOLT_CHAIN_WIDTHS(CHK, 0),  // [N][K], then [K][N] weights
                                         BOLT_CHAIN_STREAM_WIDTHS(false), BOLT_CHAIN_STREAM_WIDTHS(true)};

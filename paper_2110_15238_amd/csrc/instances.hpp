@@ -133,6 +133,7 @@ void register_b2b_gemm_instances(std::vector<B2bInstance>& v);
 void register_b2b_conv_instances(std::vector<B2bInstance>& v);
 void register_b2b_gemm_dma_instances(std::vector<B2bInstance>& v);
 void register_b2b_gemm_dma_kn_instances(std::vector<B2bInstance>& v);
+void register_b2b_gemm_stream_instances(std::vector<B2bInstance>& v);
 void register_b2b_conv_dma_instances(std::vector<B2bInstance>& v);
 void register_b2b_conv_halo_instances(std::vector<B2bInstance>& v);
 void register_gemm_chain_instances(std::vector<ChainInstance>& v);

@@ -1354,6 +1354,30 @@ def test_gemm_chain3_rows_streamed_in_rounds(bolt, shape, layout):
     assert_close(host(D), want, "gemm chain %s heuristic" % (shape,))
 
 
+@pytest.mark.parametrize("layout", ["nk", "kn"])
+@pytest.mark.parametrize("shape", [(32768, 96, 64, 32), (65537, 128, 64, 128), (65569, 104, 24, 72), (131200, 8, 128, 64), (65600, 120, 40, 56)])
+def test_b2b_gemm_rows_streamed_in_rounds(bolt, shape, layout):
+    """The pair's instances that walk 32-row tiles, on either side of the pick rule's line, and the residual in place."""
+    M, K0, N0, N1 = shape
+    L = bolt.LAYOUT_NK if layout == "nk" else bolt.LAYOUT_KN
+    A, C = wl.uniform_fp16(321, 0, (M, K0), -0.5, 0.5), wl.uniform_fp16(321, 5, (M, N1), -1, 1)
+    W0, W1 = wl.uniform_fp16(321, 1, (K0, N0), -0.5, 0.5), wl.uniform_fp16(321, 2, (N0, N1), -0.5, 0.5)
+    b0, b1 = wl.uniform_fp16(321, 3, (N0,), -1, 1), wl.uniform_fp16(321, 4, (N1,), -1, 1)
+    want, want_res = ref.b2b_gemm(A, W0, b0, W1, b1), ref.b2b_gemm_residual(A, W0, b0, W1, b1, C, gamma=0.5)
+    g0, g1 = bolt.gemm_desc(M, N0, K0, b_layout=L), bolt.gemm_desc(M, N1, N0, b_layout=L)
+    Wd = [dev(np.ascontiguousarray(W.T)) if layout == "nk" else dev(W) for W in (W0, W1)]
+    Ad, bd = dev(A), [dev(b0), dev(b1)]
+    kids = [k for k in range(bolt.bolt_num_instances(bolt.OP_B2B_GEMM)) if bolt.bolt_instance_supports(bolt.OP_B2B_GEMM, k, g0, g1)]
+    for kid in kids + [-1]:  # -1: the built-in pick rule
+        _say("b2b gemm %s weights %s instance %d" % (shape, layout, kid))
+        D, R = torch.full((M, N1), float("nan"), dtype=torch.float16, device="cuda"), dev(C)
+        bolt.bolt_b2b_gemm(g0, g1, Ad, Wd[0], bd[0], Wd[1], bd[1], D, {"kernel_id": kid})
+        bolt.bolt_b2b_gemm_residual(g0, g1, Ad, Wd[0], bd[0], Wd[1], bd[1], R, R, 0.5)
+        torch.cuda.synchronize()
+        assert_close(host(D), want, "b2b gemm %s instance %d" % (shape, kid))
+    assert_close(host(R), want_res, "b2b gemm %s residual in place" % (shape,))
+
+
 CONV_CHAINS = [  # (N, H, W, C, K0, R, S, stride, pad, K1, K2)
     (2, 12, 12, 64, 64, 3, 3, 1, 1, 64, 64), (1, 17, 13, 24, 48, 3, 3, 2, 1, 48, 48), (2, 23, 23, 8, 64, 7, 7, 2, 3, 64, 256),
     (3, 9, 11, 64, 64, 1, 1, 1, 0, 256, 64), (1, 10, 9, 16, 128, 5, 3, (1, 2), (2, 0), 64, 128),
