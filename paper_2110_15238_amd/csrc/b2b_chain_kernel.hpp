@@ -137,8 +137,7 @@ struct ChainStreamTraits {
   static constexpr int WGS_PER_CU = 160 * 1024 / LDS_BYTES < 8 / NW ? 160 * 1024 / LDS_BYTES : 8 / NW;  // 2 waves per SIMD
   static_assert(KT % 64 == 0 && N0T % 32 == 0 && N1T % 32 == 0 && (NLT == 32 || NLT == 64 || NLT == 128), "tile shape");
   static_assert(WGS_PER_CU >= 1, "LDS");
-  // (a pair from 32768 rows: no pair below that was faster than the weights-resident and multi-stage kernels by more than 5 %)
-  static bool supports(const B2bParams& p) { return p.K0 <= KT && (N2T > 0 || p.M >= 32768); }
+  static bool supports(const B2bParams& p) { return p.K0 <= KT; }
   static int lds_bytes(const B2bParams&) { return LDS_BYTES; }
   static int grid(const B2bParams& p) {  // every wave the same number of 32-row tiles, give or take one
     const int64_t tiles = ((int64_t)p.M + 31) / 32, most = 256 * WGS_PER_CU * NW;

@@ -415,7 +415,7 @@ static int fprop_heuristic(const std::vector<FpropInstance>& tab, const FpropPro
   double best_cost = 0;
   for (int i = 0; i < (int)tab.size(); ++i) {
     const FpropInstance& in = tab[i];
-    if (!fprop_supports(in, pr)) continue;
+    if (!fprop_supports(in, pr) || (in.worth_trying && !in.worth_trying(pr.p))) continue;
     if (need_split_k && !fprop_can_split_k(in)) continue;
     const FpropParams& p = pr.p;
     if (in.estimate) {  // a family with a cost model of its own, in the same microseconds
@@ -934,7 +934,7 @@ static std::vector<Candidate> fprop_candidates(const std::vector<FpropInstance>&
   std::vector<Candidate> out;
   for (int i = 0; i < (int)tab.size(); ++i) {
     const FpropInstance& in = tab[i];
-    if (!fprop_supports(in, pr)) continue;
+    if (!fprop_supports(in, pr) || (in.worth_trying && !in.worth_trying(pr.p))) continue;
     const int tiles_m = ceil_div(pr.p.M, in.bm), tiles_n = ceil_div(pr.p.N, in.bn);
     const int64_t tiles = (int64_t)tiles_m * tiles_n;
     const int nk = ceil_div(pr.p.K, in.bk);

@@ -216,6 +216,9 @@ struct FpropInstance {
   bool nchw_out;    // writes its output as [N][K][P][Q] (and only that)
   bool kn_dma;      // row-major weights fetched through one 32-bit-offset buffer descriptor over the whole matrix
   double (*estimate)(const FpropParams&);  // the pick rule's cost of this family, in us (null: the common model)
+  // Where the pick rule and bolt_tune consider this instance (null: wherever it is legal).  Not a matter of legality: a
+  // configuration that was tuned for one number of rows keeps working at any other.
+  bool (*worth_trying)(const FpropParams&);
 };
 
 template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int XMODE, int WMODE>

@@ -39,14 +39,13 @@ struct FpropWsTraits {
   static_assert(LDS_BYTES <= 160 * 1024, "partial tiles of all waves");
 
   static int64_t workgroups(const FpropParams& p) {
-    return (int64_t)((p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN);
+    return (((int64_t)p.M + BM - 1) / BM) * (((int64_t)p.N + BN - 1) / BN);
   }
+  // (The small divisions in the kernel are exact up to 2^20; a launch has fewer than 2^32 threads.)
+  static bool supports(const FpropParams& p) { return p.K <= (1 << 20) && workgroups(p) * NT < (1ll << 32); }
   // Up to 512 tiles, two per compute unit: with more of them the kernels with larger tiles and LDS staging read less (over
   // 70 problems of 1 to 8 images the last win was at 392 tiles of 32 x 32, 7.6 against 7.7 us; at 784 it was 29 against 14).
-  // (The small divisions in the kernel are exact up to 2^20.)
-  static bool supports(const FpropParams& p) {
-    return workgroups(p) <= 512 && p.K <= (1 << 20);
-  }
+  static bool worth_trying(const FpropParams& p) { return workgroups(p) <= 512; }
   static int lds_bytes(const FpropParams&) { return LDS_BYTES; }
   // Pick rule: estimated time in us.  A fit to 612 timings of 76 problems (rms 16 %): operand traffic of the tiles a compute
   // unit runs in turn; per round of co-resident workgroups one latency, the units of a wave, the sum over the waves and,
@@ -300,7 +299,7 @@ hipError_t launch_fprop_ws(const FpropParams& p, hipStream_t stream) {
     "ws_" #NW "w_" #FM "x" #FN, (16 * FM + 31) / 32 * 32, (16 * FN + 31) / 32 * 32, 32, 4, 1, XMODE, WKN ? 1 : 0, 2, \
         bolt::FpropWsTraits<NW, FM, FN>::LDS_BYTES, &bolt::launch_fprop_ws<NW, FM, FN, XMODE, WKN>,                \
         &bolt::FpropWsTraits<NW, FM, FN>::supports, &bolt::FpropWsTraits<NW, FM, FN>::lds_bytes, NW / 4, 16, true, \
-        false, WKN, &bolt::FpropWsTraits<NW, FM, FN>::estimate                                                     \
+        false, WKN, &bolt::FpropWsTraits<NW, FM, FN>::estimate, &bolt::FpropWsTraits<NW, FM, FN>::worth_trying      \
   }
 
 }  // namespace bolt

@@ -398,9 +398,10 @@ def _wave_split_ids(bolt, op, *descs):
 
 
 @pytest.mark.parametrize("layout", ["nk", "kn"])
-@pytest.mark.parametrize("shape", [(1, 8, 8), (16, 16, 64), (17, 24, 72), (33, 40, 520), (49, 136, 1096), (200, 72, 264), (5, 1000, 4104)])
+@pytest.mark.parametrize("shape", [(1, 8, 8), (16, 16, 64), (17, 24, 72), (33, 40, 520), (49, 136, 1096), (200, 72, 264), (5, 1000, 4104), (1057, 536, 72)])
 def test_gemm_wave_split_integer_bit_exact_with_gaps_and_residual(bolt, layout, shape):
-    """Edges of the 16 and 32-wide tiles, units of 64 with a tail, waves without work; rows end in poisoned gaps."""
+    """Edges of the 16 and 32-wide tiles, units of 64 with a tail, waves without work, more tiles than the built-in pick would
+    use them for; rows end in poisoned gaps."""
     M, N, K = shape
     A, B = wl.integer_fp16(241, 0, (M, K), -2, 2), wl.integer_fp16(241, 1, (K, N), -1, 1)
     bias, C = wl.integer_fp16(241, 2, (N,), -3, 3), wl.integer_fp16(241, 3, (M, N), -4, 4)
@@ -438,6 +439,7 @@ def test_gemm_wave_split_integer_bit_exact_with_gaps_and_residual(bolt, layout, 
     (3, 4, 4, 72, 40, 3, 3, 1, 1),
     (1, 14, 14, 128, 64, 1, 1, 2, 0),
     (1, 6, 6, 16, 48, 6, 7, 1, (3, 3)),
+    (70, 15, 15, 8, 72, 3, 3, 1, 1),
 ])
 def test_conv_wave_split_integer_bit_exact(bolt, case):
     N, H, W, Cc, K, R, S, stride, pad = case
@@ -1355,7 +1357,7 @@ def test_gemm_chain3_rows_streamed_in_rounds(bolt, shape, layout):
 
 
 @pytest.mark.parametrize("layout", ["nk", "kn"])
-@pytest.mark.parametrize("shape", [(32768, 96, 64, 32), (65537, 128, 64, 128), (65569, 104, 24, 72), (131200, 8, 128, 64), (65600, 120, 40, 56)])
+@pytest.mark.parametrize("shape", [(32768, 96, 64, 32), (65537, 128, 64, 128), (65569, 104, 24, 72), (131200, 8, 128, 64), (65600, 120, 40, 56), (1, 8, 64, 128), (33, 120, 40, 24)])
 def test_b2b_gemm_rows_streamed_in_rounds(bolt, shape, layout):
     """The pair's instances that walk 32-row tiles, on either side of the pick rule's line, and the residual in place."""
     M, K0, N0, N1 = shape

@@ -223,6 +223,28 @@ def test_chain_legality(bolt):
                           else True for i in ok)
 
 
+def test_a_configuration_is_not_bound_to_the_row_count(bolt):
+    """An id that bolt_tune may return for one batch stays legal for every other: how many rows a kernel is worth using at
+    is a matter of the pick rule and of the tuner's candidates."""
+    G, Cd, rows = bolt.gemm_desc, bolt.conv_desc, (1, 32, 1000, 30000, 131072)
+    sets = []
+    for layout in (bolt.LAYOUT_KN, bolt.LAYOUT_NK):
+        for n, k in ((1000, 2048), (64, 256)):
+            sets.append([{i for i in range(bolt.bolt_num_instances(bolt.OP_GEMM))
+                          if bolt.bolt_instance_supports(bolt.OP_GEMM, i, G(m, n, k, b_layout=layout))} for m in rows])
+        for n0, n1, k in ((64, 32, 96), (64, 128, 128), (128, 64, 576)):
+            sets.append([{i for i in range(bolt.bolt_num_instances(bolt.OP_B2B_GEMM)) if bolt.bolt_instance_supports(
+                bolt.OP_B2B_GEMM, i, G(m, n0, k, b_layout=layout), G(m, n1, n0, b_layout=layout))} for m in rows])
+        sets.append([{i for i in range(bolt.bolt_num_instances(bolt.OP_GEMM_CHAIN3)) if bolt.bolt_chain_instance_supports(
+            bolt.OP_GEMM_CHAIN3, i, [G(m, 32, 96, b_layout=layout), G(m, 96, 32, b_layout=layout), G(m, 32, 96, b_layout=layout)])}
+            for m in rows])
+    for h, c, r, stride in ((14, 256, 3, 1), (56, 64, 1, 2), (12, 46, 3, 1), (32, 3, 3, 2)):
+        sets.append([{i for i in range(bolt.bolt_num_instances(bolt.OP_CONV2D)) if bolt.bolt_instance_supports(
+            bolt.OP_CONV2D, i, Cd(n, h, h, c, 256, r, r, stride, r // 2))} for n in (1, 2, 8, 32, 128)])
+    for found in sets:
+        assert found[0] and all(ids == found[0] for ids in found[1:]), found
+
+
 def test_workspace_bytes(bolt):
     d = bolt.conv_desc(32, 7, 7, 512, 512, 3, 3, 1, 1)
     assert bolt.bolt_workspace_bytes(bolt.OP_CONV2D, d, None, {"kernel_id": 0, "split_k": 4}) == 4 * 1568 * 512 * 4
