@@ -232,6 +232,7 @@ struct Tables {
   std::vector<ChainInstance> gemm_chain, conv_chain;
   Tables() {
     register_gemm_chain_instances(gemm_chain);
+    register_gemm_chain_stream_instances(gemm_chain);
     register_conv_chain_instances(conv_chain);
     register_gemm_kn_instances(gemm);
     register_gemm_nk_instances(gemm);

@@ -10,21 +10,8 @@ namespace bolt {
   X(64, 128, 128, 2, XMODE), X(128, 128, 64, 2, XMODE), X(128, 128, 128, 2, XMODE), X(32, 128, 32, 2, XMODE)
 #define CH(N0T, N1T, N2T, NS, XMODE) BOLT_B2B_CHAIN_INSTANCE(128, 64, 4, N0T, N1T, N2T, NS, XMODE)
 #define CHK(N0T, N1T, N2T, NS, XMODE) BOLT_B2B_CHAIN_KN_INSTANCE(128, 64, 4, N0T, N1T, N2T, NS)
-// Thin first ops, K0 <= 128; widths that the list above has too, so that what the chains accept does not depend on K0
-#define BOLT_CHAIN_STREAM_WIDTHS(WKN)                                                                   \
-  BOLT_CHAIN_STREAM_INSTANCE(4, 128, 32, 128, 32, WKN), BOLT_CHAIN_STREAM_INSTANCE(4, 128, 64, 64, 64, WKN), \
-  BOLT_CHAIN_STREAM_INSTANCE(4, 128, 64, 128, 64, WKN), BOLT_CHAIN_STREAM_INSTANCE(4, 128, 64, 64, 128, WKN)
-#define BOLT_PAIR_STREAM_WIDTHS(WKN)                                                                 \
-  BOLT_PAIR_STREAM_INSTANCE(4, 128, 32, 128, WKN), BOLT_PAIR_STREAM_INSTANCE(4, 128, 64, 32, WKN),     \
-  BOLT_PAIR_STREAM_INSTANCE(4, 128, 64, 64, WKN), BOLT_PAIR_STREAM_INSTANCE(4, 128, 64, 128, WKN),     \
-  BOLT_PAIR_STREAM_INSTANCE(4, 128, 128, 64, WKN)
-void register_b2b_gemm_stream_instances(std::vector<B2bInstance>& v) {
-  static const B2bInstance table[] = {BOLT_PAIR_STREAM_WIDTHS(false), BOLT_PAIR_STREAM_WIDTHS(true)};
-  for (const auto& t : table) v.push_back(t);
-}
 void register_gemm_chain_instances(std::vector<ChainInstance>& v) {
-  static const ChainInstance table[] = {BOLT_CHAIN_WIDTHS(CH, 0), BOLT_CHAIN_WIDTHS(CHK, 0),  // [N][K], then [K][N] weights
-                                        BOLT_CHAIN_STREAM_WIDTHS(false), BOLT_CHAIN_STREAM_WIDTHS(true)};
+  static const ChainInstance table[] = {BOLT_CHAIN_WIDTHS(CH, 0), BOLT_CHAIN_WIDTHS(CHK, 0)};  // [N][K], then [K][N] weights
   for (const auto& t : table) v.push_back(t);
 }
 // CHH(BM, WAVES, N0T, N1T, N2T, STAGES, XI): first op on the halo main loop (stride-1 "same" filters, C % 64 == 0)

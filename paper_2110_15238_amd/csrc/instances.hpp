@@ -16,6 +16,7 @@
 #include "conv_halo_kernel.hpp"
 #include "conv_smallc_kernel.hpp"
 #include "b2b_chain_kernel.hpp"
+#include "chain_stream_kernel.hpp"
 #include "b2b_halo_kernel.hpp"
 #include "fprop_dma_kernel.hpp"
 #include "fprop_kernel.hpp"
@@ -137,5 +138,6 @@ void register_b2b_gemm_stream_instances(std::vector<B2bInstance>& v);
 void register_b2b_conv_dma_instances(std::vector<B2bInstance>& v);
 void register_b2b_conv_halo_instances(std::vector<B2bInstance>& v);
 void register_gemm_chain_instances(std::vector<ChainInstance>& v);
+void register_gemm_chain_stream_instances(std::vector<ChainInstance>& v);
 void register_conv_chain_instances(std::vector<ChainInstance>& v);
 }  // namespace bolt
