@@ -1356,6 +1356,16 @@ def test_gemm_chain3_rows_streamed_in_rounds(bolt, shape, layout):
     assert_close(host(D), want, "gemm chain %s heuristic" % (shape,))
 
 
+def test_chain_tuner_times_the_tightest_streaming_instance_only(bolt):
+    """A chain that two streaming widths fit: both are legal, the one without a tighter neighbour is timed."""
+    g = [bolt.gemm_desc(4000, n, k) for k, n in ((96, 32), (32, 96), (96, 32))]
+    legal = [k for k in range(bolt.bolt_num_instances(bolt.OP_GEMM_CHAIN3)) if bolt.bolt_chain_instance_supports(bolt.OP_GEMM_CHAIN3, k, g)]
+    h = lambda *s: torch.randn(s, device="cuda").half()
+    t = [h(4000, 96), h(96, 32), h(32), h(32, 96), h(96), h(96, 32), h(32), h(4000, 32)]
+    assert len(legal) == 4
+    assert bolt.bolt_tune_chain(bolt.OP_GEMM_CHAIN3, g, t).tried == 3
+
+
 @pytest.mark.parametrize("layout", ["nk", "kn"])
 @pytest.mark.parametrize("shape", [(32768, 96, 64, 32), (65537, 128, 64, 128), (65569, 104, 24, 72), (131200, 8, 128, 64), (65600, 120, 40, 56), (1, 8, 64, 128), (33, 120, 40, 24)])
 def test_b2b_gemm_rows_streamed_in_rounds(bolt, shape, layout):
