@@ -49,15 +49,21 @@ struct FpropWsTraits {
   static int lds_bytes(const FpropParams&) { return LDS_BYTES; }
   // Pick rule: estimated time in us.  A fit to 612 timings of 76 problems (rms 16 %): operand traffic of the tiles a compute
   // unit runs in turn; per round of co-resident workgroups one latency, the units of a wave, the sum over the waves and,
-  // for a convolution, the addresses; no faster than every tensor once from memory.
+  // for a convolution, the addresses; no faster than every tensor once from memory.  Rows run fastest over the tiles, so the
+  // activations are read again for every column of tiles: from memory where they are more than the L2s keep (half of 32 MB).
+  // (Without the activations 7 of 106 tall problems, 1024 to 16384 rows x 8 to 64 x 512 to 8192, went from the tiled kernels
+  // to slower ones: 8192 x 64 x 2048 10.0 -> 14.2 us, 16384 x 32 x 8192 42.1 -> 44.8.  The 0.02 ranks the tiles among each other.)
   static double estimate(const FpropParams& p) {
+    const bool window = p.cg.R > 0 && p.ldx == 0;
     const double wgs = (double)workgroups(p), units = (p.K + 63) / 64, upw = std::ceil(units / NW);
     const double seq = std::ceil(wgs / 256);
     const double per_cu = std::max(1, std::min(160 * 1024 / LDS_BYTES, 16 / NW));
     const double fill = seq * units * 128.0 * (BM + BN) / 6.06e4;
-    const double chain = std::ceil(wgs / (256 * per_cu)) * (1.41 + upw * 0.105 + NW * FM * FN * 0.0274 + (p.cg.R > 0 && p.ldx == 0 ? 0.89 : 0.0)) +
+    const double chain = std::ceil(wgs / (256 * per_cu)) * (1.41 + upw * 0.105 + NW * FM * FN * 0.0274 + (window ? 0.89 : 0.0)) +
                          (seq - 1) * 0.66;
-    const double mem = 2.0 * ((double)p.N * p.K + (double)p.M * p.N) / 5.0e6;
+    double x = (double)p.M * (window ? std::min<double>(p.K, (double)p.cg.C * p.cg.stride_h * p.cg.stride_w) : p.K);
+    if (x * 2 > (16 << 20)) x *= (p.N + BN - 1) / BN;
+    const double mem = 2.0 * (x + (double)p.N * p.K + (double)p.M * p.N) / 5.0e6 + 0.02 * fill;
     return 2.0 + std::max(std::sqrt(fill * fill + chain * chain), mem);
   }
 };

@@ -338,6 +338,29 @@ def test_streaming_chains_are_compiled_apart_from_the_tiled_ones():
     assert sum(map(len, held)) == 3
 
 
+def test_pick_rule_counts_the_activations_of_tall_thin_problems():
+    """The kernels for small problems may not be estimated below the time that reading the activations takes: thousands of
+    rows times a deep reduction, where the tiled kernels are up to 1.4 times faster.  Small problems stay with them."""
+    import os
+    import re
+    import subprocess
+    import sys
+    code = """
+import sys
+sys.path.insert(0, %r)
+import paper_2110_15238_amd as b
+for m, n, k in ((16384, 8, 8192), (16384, 16, 8192), (16384, 32, 8192), (8192, 64, 2048), (32, 1000, 2048)):
+    for layout in (b.LAYOUT_KN, b.LAYOUT_NK):
+        assert b.bolt_check(b.OP_GEMM, b.gemm_desc(m, n, k, b_layout=layout)) == 0
+""" % os.path.abspath(ROOT)
+    r = subprocess.run([sys.executable, "-c", code], env=dict(os.environ, BOLT_TUNE_LOG="1"), capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    picks = re.findall(r"\[bolt_pick\] -> \d+ (\S+)", r.stderr)
+    assert len(picks) == 10 and not any(p.startswith("ws_") for p in picks[:8]) and all(p.startswith("ws_") for p in picks[8:]), picks
+    costs = [float(c) for c in re.findall(r"candidate \d+ ws_\S+ cost (\S+)", r.stderr.split("->")[0])]
+    assert costs and min(costs) >= 2 * 16384 * 8192 / 6.5e6, costs  # the activations at 6.5 TB/s
+
+
 def test_built_in_pick_rule_families():
     """What a call without a config runs (no GPU needed: bolt_check resolves the pick, BOLT_TUNE_LOG=1 names it): the
     halo kernel for a 3x3 stride-1 layer, the ping-pong kernels for a GEMM that fills the chip in either weight layout,
