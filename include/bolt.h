@@ -142,8 +142,9 @@ bolt_status bolt_gemm_epilogue(const bolt_gemm_desc* desc, const void* A, const 
  * multiple of 8.  C a multiple of 8: the fast (128-bit) kernels; another even C: the kernels
  * for unpadded channels (Table 3's "unpadded" side); C <= 4 of either parity, e.g. the 3 colour planes of a first
  * layer: the first-layer kernels, which read x without channel padding and, with
- * desc->x_layout = BOLT_TENSOR_NCHW, in NCHW (they need R * C <= 24, S <= 8, stride_w <= 2, else
- * BOLT_ERR_UNSUPPORTED; an odd C > 4 is BOLT_ERR_ALIGNMENT: pad it with bolt_pad_channels_nhwc). */
+ * desc->x_layout = BOLT_TENSOR_NCHW, in NCHW (R * C <= 24, S <= 8 and stride_w <= 2 always run;
+ * beyond that most filters are BOLT_ERR_UNSUPPORTED, see bolt_check, but for C = 2 and 4 from NHWC to NHWC, which have
+ * the kernels of other even C; an odd C > 4 is BOLT_ERR_ALIGNMENT: pad it with bolt_pad_channels_nhwc). */
 bolt_status bolt_conv2d_fprop_nhwc(const bolt_conv_desc* desc, const void* x, const void* w, const void* bias,
                                    void* y, const bolt_config* config, void* workspace, size_t workspace_bytes,
                                    void* stream);

@@ -19,7 +19,7 @@
 // are output), conv_smallc_kernel -> this one: 29 -> 21.5 us (NHWC 24.3 -> 19.7), 3 x 3 / 2 24.5 -> 14.5; 32 of 96 x 96, 7 x 7 / 2,
 // 32 channels 15.0 -> 8.7; 1 of 224 x 224 7.5 -> 6.2.
 #pragma once
-#include "fprop_dma_kernel.hpp"
+#include "conv_smallc_kernel.hpp"
 
 namespace bolt {
 
@@ -69,6 +69,9 @@ struct ConvFirstTraits {
   }
   static bool supports(const FpropParams& p) {
     const ConvGeom& g = p.cg;
+    // No call runs only here: which first layers are accepted stays what bolt.h says (conv_smallc_kernel's limits; 4 channels
+    // from NHWC to NHWC also run on the alignment-2 kernels).
+    if (!(g.C == 4 && !p.x_nchw && !p.y_nchw) && !ConvSmallCTraits<6, SW>::supports(p)) return false;
     return (g.C == 3 || g.C == 4) && g.stride_w == SW && g.R * ((g.S + 1) / 2) <= 4 * T && (int64_t)p.N * p.ldw * 2 < (1ll << 31) &&
            plan(p).lds_bytes > 0;
   }

@@ -1184,6 +1184,34 @@ def test_first_layer_strips_integer_bit_exact(bolt, case, layout):
         assert_close(host(y), ref.conv2d_nhwc(x, w, bias, stride=stride, pad=pad, act=act), "first layer %s %s" % (case, act))
 
 
+@pytest.mark.parametrize("case", [
+    # N H W C K R S stride pad; 28 fragments in use, a filter of one wide row, of 11 rows, of 14
+    (2, 21, 23, 4, 72, 7, 7, 2, 3),
+    (2, 21, 23, 4, 72, 7, 8, 1, 3),
+    (2, 9, 40, 4, 24, 1, 15, 1, (0, 7)),
+    (1, 30, 19, 3, 16, 11, 2, 1, (5, 1)),
+    (2, 30, 19, 4, 64, 14, 4, (3, 2), (1, 2)),
+])
+def test_first_layer_strips_with_long_filters_integer_bit_exact(bolt, case):
+    """Every fragment of the k-steps in use (7 x 7 with 4 channels), and an infinity outside of a window must not leak into it."""
+    N, H, W, Cc, K, R, S, stride, pad = case
+    x, w = wl.integer_fp16(252, 0, (N, H, W, Cc), -2, 2), wl.integer_fp16(252, 1, (K, R, S, Cc), -1, 1)
+    xinf = x.copy()
+    xinf[0, H // 2, W // 2, 0] = np.inf
+    d = bolt.conv_desc(N, H, W, Cc, K, R, S, stride, pad, act="none")
+    ids = [k for k in range(bolt.bolt_num_instances(bolt.OP_CONV2D)) if bolt.bolt_instance_supports(bolt.OP_CONV2D, k, d)]
+    ids = [k for k in ids if bolt.bolt_instance_config(bolt.OP_CONV2D, k).stages == 1]  # the strip kernels
+    assert ids
+    for xs in (x, xinf):
+        want = ref.conv2d_nhwc(xs, np.abs(w) + 1 if xs is xinf else w, None, stride=stride, pad=pad, act="none")
+        assert xs is xinf or np.abs(want.astype(np.float64)).max() < 2048
+        y = torch.empty(want.shape, dtype=torch.float16, device="cuda")
+        for kid in ids + [-1]:
+            y.fill_(float("nan"))
+            bolt.bolt_conv2d_fprop_nhwc(d, dev(xs), dev(np.abs(w) + 1 if xs is xinf else w), None, y, config={"kernel_id": kid})
+            assert_bit_equal(host(y), want, "first layer %s instance %d" % (case, kid))
+
+
 def test_first_layer_conv_equals_the_padded_path_and_ignores_infinite_neighbours(bolt):
     """Channel padding is a pure re-scheduling (Section 3.2.3): the unpadded first-layer kernel and the padded C = 8
     convolution agree bit for bit on integers.  A tap past the filter's width reads the neighbouring pixel's data

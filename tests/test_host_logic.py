@@ -143,6 +143,20 @@ def test_conv_validation(bolt):
     assert bolt.conv_out_hw(Cd(1, 224, 224, 8, 64, 7, 7, 2, 3)) == (112, 112)
 
 
+def test_first_layer_limits(bolt):
+    """bolt.h's limits of the first layers (R * C <= 24, S <= 8, stride_w <= 2): what lies within runs in both layouts, and
+    the strip kernels, which could run more, do not widen them.  4 channels from NHWC to NHWC have the alignment-2 kernels."""
+    Cd = lambda c, r, s, sw, xl, yl="nhwc": bolt.bolt_check(bolt.OP_CONV2D, bolt.conv_desc(2, 40, 48, c, 64, r, s, (1, sw), 1, x_layout=xl, y_layout=yl))
+    for c, r, s in ((3, 8, 8), (4, 6, 8), (1, 24, 8), (2, 12, 8), (3, 7, 7), (3, 1, 1)):
+        for sw in (1, 2):
+            for xl in ("nhwc", "nchw"):
+                assert Cd(c, r, s, sw, xl) == OK and Cd(c, r, s, sw, xl, "nchw") == OK, (c, r, s, sw, xl)
+    for c, r, s in ((4, 7, 7), (3, 9, 5), (3, 11, 2), (3, 9, 6)):  # within the strip kernels' 28 fragments
+        assert Cd(c, r, s, 2, "nchw") == UNSUPPORTED and Cd(c, r, s, 2, "nhwc", "nchw") == UNSUPPORTED, (c, r, s)
+        assert Cd(c, r, s, 2, "nhwc") == (OK if c == 4 else UNSUPPORTED), (c, r, s)
+    assert Cd(4, 1, 15, 1, "nhwc") == OK
+
+
 def test_b2b_fusion_legality(bolt):
     G, Cd, chk = bolt.gemm_desc, bolt.conv_desc, bolt.bolt_check
     assert chk(bolt.OP_B2B_GEMM, G(16384, 64, 256), G(16384, 128, 64)) == OK
