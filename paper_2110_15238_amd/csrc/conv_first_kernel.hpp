@@ -335,6 +335,7 @@ __global__ __launch_bounds__(256, 2) void conv_first_kernel(const FpropParams p,
           auto place = [](int pix, int ch) { return pix * 128 + ((ch ^ ((pix >> 1) & 7)) << 4); };
 #pragma unroll
           for (int hb = 0; hb < 2; ++hb) *(half8*)(mine + place(l16, hb * 4 + kg)) = o[hb];
+          asm volatile("" ::: "memory");  // reads of what other lanes wrote stay behind the writes, the next block's writes behind them
 #pragma unroll
           for (int h = 0; h < 2; ++h) {
             const int pix = h * 8 + (lane >> 3), ch = lane & 7;
@@ -342,6 +343,7 @@ __global__ __launch_bounds__(256, 2) void conv_first_kernel(const FpropParams p,
             half_t* const y = p.Y + (((int64_t)img * cg.P + prow) * cg.Q + q0 + qb) * p.ldy + n0;  // (the same in all lanes)
             if (n0 + ch * 8 < p.N && q0 + qb + pix < cg.Q) __builtin_nontemporal_store(v, (half8*)(y + (unsigned)(pix * p.ldy + ch * 8)));
           }
+          asm volatile("" ::: "memory");
         } else if (q < cg.Q) {  // [N][K][P][Q]: 8 channel planes, 16 consecutive pixels of each
 #pragma unroll
           for (int hb = 0; hb < 2; ++hb) {

@@ -240,7 +240,7 @@ __global__ __launch_bounds__(64 * NW) void fprop_ws_kernel(const FpropParams p) 
           if constexpr (WKN) *(uintx4*)(wstage + kn_at(a * KROWS + krow, kch >> 1) + (kch & 1) * 16) = wv[k][a];
           else *(uintx4*)(wstage + (a >> 1) * 2048 + put[a & 1]) = wv[k][a];
         }
-        if constexpr (WKN) asm volatile("" ::: "memory");  // the transposing read is an intrinsic
+        asm volatile("" ::: "memory");  // reads of what other lanes wrote stay behind the writes (and the next unit's writes behind them)
         fetch(i + k + D, k);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -261,7 +261,7 @@ __global__ __launch_bounds__(64 * NW) void fprop_ws_kernel(const FpropParams p) 
 #pragma unroll
             for (int b = 0; b < FM; ++b) acc[a][b] = mfma_16x16x32(wf[a], xf[b], acc[a][b]);
         }
-        if constexpr (WKN) asm volatile("" ::: "memory");
+        asm volatile("" ::: "memory");
       }
     }
   }
