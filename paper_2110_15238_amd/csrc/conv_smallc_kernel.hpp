@@ -106,15 +106,15 @@ __global__ __launch_bounds__(256, 3) void conv_smallc_kernel(const FpropParams p
   };
   // What does not depend on the tile is worked out once per item i of this thread and kept in two registers:
   //   rel[i]: first half of the item relative to the tile's first half in the tensor (TileAt::base);
-  //   dsx[i]: LDS half index of its destination | filter row r << 16 | first half inside the run x0 << 21, or -1 for
-  //           an item past the last run.
+  //   dsx[i]: LDS half index of its destination | filter row r << 16 | first half inside the run x0 / 8 << 21, or -1 for
+  //           an item past the last run.  (In items: x0 itself reaches 1040, 4 channels at stride 2, and bit 31 is the sign.)
   int rel[NI], dsx[NI];
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
     const int w = tid + 256 * i, seg = fdiv(w, rcp_ipr), x0 = (w - seg * ipr) * 8;
     const int r = p.x_nchw ? fdiv(seg, rcp_c) : seg, c = p.x_nchw ? seg - r * cg.C : 0;
     rel[i] = r * stride_r + c * stride_c + x0;
-    dsx[i] = seg < nseg ? (r * RS + (p.x_nchw ? x0 * cg.C + c : x0)) | (r << 16) | (x0 << 21) : -1;
+    dsx[i] = seg < nseg ? (r * RS + (p.x_nchw ? x0 * cg.C + c : x0)) | (r << 16) | (x0 >> 3 << 21) : -1;
   }
   auto fetch = [&](const TileAt& t) {
 #pragma unroll
@@ -148,7 +148,7 @@ __global__ __launch_bounds__(256, 3) void conv_smallc_kernel(const FpropParams p
       unsigned o[4];
 #pragma unroll
       for (int n = 0; n < 4; ++n) o[n] = __builtin_amdgcn_alignbit(v[i][n + 1], v[i][n], sh);
-      const int x0 = dsx[i] >> 21;
+      const int x0 = dsx[i] >> 21 << 3;
       if ((x0 < lo) | (x0 + 8 > hi)) {  // an item on the image's edge: zero the halves outside
 #pragma unroll
         for (int n = 0; n < 4; ++n) {

@@ -1212,6 +1212,24 @@ def test_first_layer_strips_with_long_filters_integer_bit_exact(bolt, case):
             assert_bit_equal(host(y), want, "first layer %s instance %d" % (case, kid))
 
 
+@pytest.mark.parametrize("layout", ["nhwc", "nchw"])
+@pytest.mark.parametrize("case", [(2, 3, 262, 3, 3), (1, 2, 300, 1, 4), (1, 5, 289, 1, 7), (1, 9, 518, 6, 8)])  # N H W R S
+def test_first_layer_four_channels_wide_rows_integer_bit_exact(bolt, case, layout):
+    """4 channels at stride 2, more than 127 output columns: a tile's row of input is longer than 1024 halves."""
+    N, H, W, R, S = case
+    x, w, bias = wl.integer_fp16(253, 0, (N, H, W, 4), -2, 2), wl.integer_fp16(253, 1, (24, R, S, 4), -1, 1), wl.integer_fp16(253, 2, (24,), -3, 3)
+    want = ref.conv2d_nhwc(x, w, bias, stride=2, pad=(R // 2, 0))
+    d = bolt.conv_desc(N, H, W, 4, 24, R, S, 2, (R // 2, 0), x_layout=layout)
+    tx = dev(x if layout == "nhwc" else np.ascontiguousarray(x.transpose(0, 3, 1, 2)))
+    ids = [k for k in range(bolt.bolt_num_instances(bolt.OP_CONV2D)) if bolt.bolt_instance_supports(bolt.OP_CONV2D, k, d)]
+    assert want.shape[2] >= 128 and ids
+    y = torch.empty(want.shape, dtype=torch.float16, device="cuda")
+    for kid in ids + [-1]:
+        y.fill_(float("nan"))
+        bolt.bolt_conv2d_fprop_nhwc(d, tx, dev(w), dev(bias), y, config={"kernel_id": kid})
+        assert_bit_equal(host(y), want, "first layer %s %s instance %d" % (case, layout, kid))
+
+
 def test_first_layer_conv_equals_the_padded_path_and_ignores_infinite_neighbours(bolt):
     """Channel padding is a pure re-scheduling (Section 3.2.3): the unpadded first-layer kernel and the padded C = 8
     convolution agree bit for bit on integers.  A tap past the filter's width reads the neighbouring pixel's data
