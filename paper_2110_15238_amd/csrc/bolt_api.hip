@@ -629,6 +629,21 @@ static void b2b_fill_config(const B2bInstance& in, int id, bolt_config* c) {
 // their own.
 static bool b2b_streams(const B2bInstance& in) { return in.xmode == 0 && in.dyn_supports; }
 
+// How the 32-row tiles of a streaming kernel fall on the waves that the chip holds: tiles per wave, and how full that many
+// rounds are (1: every wave has the same number).
+struct StreamRounds {
+  int rounds;
+  double full;
+};
+static StreamRounds stream_rounds(int M, int waves, int lds_bytes) {
+  const int per_cu = std::max(1, std::min(kLdsPerCU / lds_bytes, 8 / waves));
+  const int tiles = ceil_div(M, 32), most = kNumCU * per_cu * waves, rounds = ceil_div(tiles, most);
+  return {rounds, (double)tiles / ((double)rounds * most)};
+}
+// Activations whose arithmetic is a large part of a thin pair's or chain's time: the streaming kernels, two waves per SIMD,
+// hide less of it than the tiled ones.
+static bool heavy_act(int act) { return act == BOLT_ACT_GELU || act == BOLT_ACT_SOFTPLUS; }
+
 static int b2b_heuristic(const std::vector<B2bInstance>& tab, const B2bProblem& pr) {
   int best = -1;
   double best_cost = 0;
@@ -650,16 +665,29 @@ static int b2b_heuristic(const std::vector<B2bInstance>& tab, const B2bProblem& 
     if (tune_log_enabled()) std::fprintf(stderr, "[bolt_pick] candidate %d %s cost %.4g\n", i, in.name, cost);
     if (best < 0 || cost < best_cost) { best = i; best_cost = cost; }
   }
-  // More 128-row tiles than two per compute unit: the tiled kernels go round again, the streaming one overlaps the rounds.  Over
-  // 40 problems (8 width pairs, K0 32 to 128, 1000 to 131072 rows, us, best tiled / streaming): 131072 rows 8.4-17.5 / 7.0-14.4, no
-  // loss; 65536 rows 5.6-9.0 / 5.1-9.5, up to 10 % behind where op1 is wide.
+  // More 128-row tiles than two per compute unit: the tiled kernels go round again, the streaming one overlaps the rounds.  Of
+  // the widths that hold the pair the least work takes the rows, then the fewest columns to activate.
+  // A 32-wide op1 gains at any number of rows.  The others gain where the last round is three quarters full, or nothing but
+  // cheap activations stands against tiles of the same widths; (32, 128), whose tiles are three to a compute unit, in two rounds
+  // only.  GELU and softplus outweigh the rest: never over more padded columns than the tiled kernel's.  Over 150 problems with
+  // five activations each (20000 to 400000 rows, K0 8 to 128), time against the tiled kernels' pick: mean 0.86, 6 of 750 more
+  // than 3 % slower, none more than 10; streamed from 65537 rows on whatever the rest, 115 and 92 (78392 x 32 -> 24 -> 48 with
+  // GELU 13.2 -> 25.2 us).
   if (best >= 0 && ceil_div(pr.p.M, 128) > 2 * kNumCU) {
     int stream = -1;
+    auto rank = [](const B2bInstance& in) { return (in.n0t * in.n1t << 10) + in.n0t + in.n1t; };
     for (int i = 0; i < (int)tab.size(); ++i)
-      if (b2b_streams(tab[i]) && b2b_supports(tab, i, pr) &&
-          (stream < 0 || tab[i].n0t * tab[i].n1t < tab[stream].n0t * tab[stream].n1t))
-        stream = i;
-    if (stream >= 0) best = stream;
+      if (b2b_streams(tab[i]) && b2b_supports(tab, i, pr) && (stream < 0 || rank(tab[i]) < rank(tab[stream]))) stream = i;
+    if (stream >= 0) {
+      const B2bInstance &st = tab[stream], &ti = tab[best];
+      const bool heavy0 = heavy_act(pr.p.act0), heavy1 = heavy_act(pr.p.act1);
+      auto heavy_columns = [&](const B2bInstance& in) { return (heavy0 ? in.n0t : 0) + (heavy1 ? in.n1t : 0); };
+      const StreamRounds r = stream_rounds(pr.p.M, st.waves_m * st.waves_n, st.dyn_lds_bytes(pr.p));
+      bool gains = heavy_columns(st) <= heavy_columns(ti);
+      if (st.n1t > 64 && st.n0t <= 32) gains &= !heavy0 && !heavy1 && r.rounds == 2 && r.full >= 0.75;
+      else if (st.n1t > 32) gains &= r.full >= 0.75 || (!heavy0 && !heavy1 && st.n0t == ti.n0t && st.n1t == ti.n1t);
+      if (gains) best = stream;
+    }
   }
   if (tune_log_enabled() && best >= 0) std::fprintf(stderr, "[bolt_pick] -> %d %s\n", best, tab[best].name);
   return best;

@@ -375,6 +375,35 @@ for m, n, k in ((16384, 8, 8192), (16384, 16, 8192), (16384, 32, 8192), (8192, 6
     assert costs and min(costs) >= 2 * 16384 * 8192 / 6.5e6, costs  # the activations at 6.5 TB/s
 
 
+def _picks(calls):
+    """The kernels that the built-in rule picks for a list of expressions over `b`, the package (BOLT_TUNE_LOG=1 names them)."""
+    import os
+    import re
+    import subprocess
+    import sys
+    code = "import sys\nsys.path.insert(0, %r)\nimport paper_2110_15238_amd as b\n" % os.path.abspath(ROOT)
+    code += "\n".join("assert %s == 0" % c for c in calls)
+    r = subprocess.run([sys.executable, "-c", code], env=dict(os.environ, BOLT_TUNE_LOG="1"), capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    picks = re.findall(r"\[bolt_pick\] -> \d+ (\S+)", r.stderr)
+    assert len(picks) == len(calls), picks
+    return picks
+
+
+def test_pairs_stream_where_their_rounds_are_full_or_activations_cheap():
+    """Streaming pairs cost up to 1.9 times the tiled ones with GELU or a short last round; (64, 32) and full rounds gain."""
+    def pair(m, k0, n0, n1, a0, a1):
+        return "b.bolt_check(b.OP_B2B_GEMM, b.gemm_desc(%d, %d, %d, act=%r), b.gemm_desc(%d, %d, %d, act=%r))" % (m, n0, k0, a0, m, n1, n0, a1)
+    tiled = [pair(78392, 32, 24, 48, "gelu", "gelu"), pair(78392, 32, 24, 48, "relu", "relu"), pair(66211, 96, 16, 72, "relu", "relu"),
+             pair(152820, 48, 8, 104, "relu", "relu"), pair(109942, 48, 8, 104, "gelu", "gelu"), pair(68365, 80, 16, 16, "gelu", "none"),
+             pair(78816, 40, 64, 64, "gelu", "gelu"), pair(65536, 96, 64, 32, "relu", "relu")]
+    streamed = [pair(131072, 96, 64, 32, "relu", "relu"), pair(74538, 96, 64, 32, "gelu", "gelu"), pair(78816, 40, 64, 64, "relu", "hardswish"),
+                pair(109000, 40, 64, 64, "gelu", "gelu"), pair(109942, 48, 8, 104, "relu", "relu"), pair(120995, 40, 128, 64, "softplus", "softplus")]
+    picks = _picks(tiled + streamed)
+    assert [p.startswith("pairstream") for p in picks] == [False] * len(tiled) + [True] * len(streamed), picks
+    assert picks[len(tiled)].endswith("n64_32") and picks[len(tiled) + 3].endswith("n64_64")
+
+
 def test_built_in_pick_rule_families():
     """What a call without a config runs (no GPU needed: bolt_check resolves the pick, BOLT_TUNE_LOG=1 names it): the
     halo kernel for a 3x3 stride-1 layer, the ping-pong kernels for a GEMM that fills the chip in either weight layout,
