@@ -856,16 +856,23 @@ static int chain_heuristic(const std::vector<ChainInstance>& tab, const B2bProbl
     if (best < 0 || cost < best_cost) { best = i; best_cost = cost; }
   }
   // The streaming kernel of the same widths where the tiled workgroups do not fit on the chip at once: they then run in
-  // rounds, each all fill and drain.  Over 36 problems (7 width sets, 1000 to 128320 rows, us, tiled / streaming): two rounds
-  // and more 12.2-27.9 / 9.5-16.5, no loss; one round 5.5-8.5 / 5.4-9.0, streaming up to 14 % behind or 7 % ahead.
-  if (best >= 0 && !tab[best].dyn_supports &&
-      ceil_div(pr.p.M, tab[best].bm) > 256 * std::max(1, kLdsPerCU / tab[best].lds_bytes))
-    for (int i = 0; i < (int)tab.size(); ++i)
-      if (chain_streams(tab[i]) && tab[i].n0t == tab[best].n0t && tab[i].n1t == tab[best].n1t && tab[i].n2t == tab[best].n2t &&
-          chain_supports(tab, i, pr)) {
-        best = i;
-        break;
-      }
+  // rounds, each all fill and drain.  With one tiled workgroup to a compute unit it is 1.2 to 2.4 times as fast; with more of
+  // them it gains where its own last round is three quarters full, or hardswish, which it does better, is not outweighed by GELU
+  // or softplus.  Over 150 problems with five activations each (20000 to 400000 rows), time against the tiled kernels' pick: mean
+  // 0.84, 4 of 750 more than 3 % slower (at most 9); without the second condition 49 (at most 12).
+  if (best >= 0 && !tab[best].dyn_supports) {
+    const int per_cu = std::max(1, kLdsPerCU / tab[best].lds_bytes);
+    const int acts[3] = {pr.p.act0, pr.p.act1, pr.p.act2};
+    const bool heavy = std::any_of(acts, acts + 3, heavy_act), hard = std::count(acts, acts + 3, (int)BOLT_ACT_HARDSWISH) > 0;
+    if (ceil_div(pr.p.M, tab[best].bm) > kNumCU * per_cu)
+      for (int i = 0; i < (int)tab.size(); ++i)
+        if (chain_streams(tab[i]) && tab[i].n0t == tab[best].n0t && tab[i].n1t == tab[best].n1t && tab[i].n2t == tab[best].n2t &&
+            chain_supports(tab, i, pr)) {
+          const StreamRounds r = stream_rounds(pr.p.M, tab[i].waves, tab[i].dyn_lds_bytes(pr.p));
+          if (per_cu == 1 || r.full >= 0.75 || (hard && !heavy)) best = i;
+          break;
+        }
+  }
   if (tune_log_enabled() && best >= 0) std::fprintf(stderr, "[bolt_pick] -> %d %s\n", best, tab[best].name);
   return best;
 }

@@ -404,6 +404,19 @@ def test_pairs_stream_where_their_rounds_are_full_or_activations_cheap():
     assert picks[len(tiled)].endswith("n64_32") and picks[len(tiled) + 3].endswith("n64_64")
 
 
+def test_chains_with_heavy_activations_stream_only_in_full_rounds():
+    """Where two tiled workgroups fit on a compute unit; with one (64, 128, 64) the streaming kernel always gains."""
+    def chain(m, widths, *acts):
+        return "b.bolt_check_chain(b.OP_GEMM_CHAIN3, [%s])" % ", ".join(
+            "b.gemm_desc(%d, %d, %d, act=%r)" % (m, n, k, a) for k, n, a in zip(widths, widths[1:], acts))
+    tiled = [chain(69774, (48, 48, 48, 48), "gelu", "gelu", "gelu"), chain(69774, (48, 48, 48, 48), "none", "none", "softplus"),
+             chain(83006, (8, 48, 16, 8), "relu", "relu", "relu"), chain(65536, (48, 48, 48, 48), "hardswish", "relu", "relu")]
+    streamed = [chain(69774, (48, 48, 48, 48), "relu", "hardswish", "none"), chain(110000, (48, 48, 48, 48), "gelu", "gelu", "gelu"),
+                chain(69100, (40, 64, 72, 56), "gelu", "gelu", "gelu"), chain(128320, (96, 32, 96, 32), "relu", "relu", "relu")]
+    picks = _picks(tiled + streamed)
+    assert [p.startswith("chainstream") for p in picks] == [False] * len(tiled) + [True] * len(streamed), picks
+
+
 def test_built_in_pick_rule_families():
     """What a call without a config runs (no GPU needed: bolt_check resolves the pick, BOLT_TUNE_LOG=1 names it): the
     halo kernel for a 3x3 stride-1 layer, the ping-pong kernels for a GEMM that fills the chip in either weight layout,
