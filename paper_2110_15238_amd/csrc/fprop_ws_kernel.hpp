@@ -53,6 +53,10 @@ struct FpropWsTraits {
   // activations are read again for every column of tiles: from memory where they are more than the L2s keep (half of 32 MB).
   // (Without the activations 7 of 106 tall problems, 1024 to 16384 rows x 8 to 64 x 512 to 8192, went from the tiled kernels
   // to slower ones: 8192 x 64 x 2048 10.0 -> 14.2 us, 16384 x 32 x 8192 42.1 -> 44.8.  The 0.02 ranks the tiles among each other.)
+  // A deep reduction over more than one tile per compute unit is a second round of nothing but operand traffic: the fit errs by
+  // up to 45 % to this side there and the tiled kernels are close, so a quarter on top, 15 % for filter windows.  The depth where
+  // that begins, of 107 problems with 257 to 512 tiles (time against the tiled pick): GEMM and 1x1 up to 600 0.77-1.09, from 1224
+  // on 0.94-1.46 (4677 x 40 x 3272 13.0 -> 18.5 us); windows up to 3024 0.75-1.12, beyond 0.97-1.48.
   static double estimate(const FpropParams& p) {
     const bool window = p.cg.R > 0 && p.ldx == 0;
     const double wgs = (double)workgroups(p), units = (p.K + 63) / 64, upw = std::ceil(units / NW);
@@ -64,7 +68,8 @@ struct FpropWsTraits {
     double x = (double)p.M * (window ? std::min<double>(p.K, (double)p.cg.C * p.cg.stride_h * p.cg.stride_w) : p.K);
     if (x * 2 > (16 << 20)) x *= (p.N + BN - 1) / BN;
     const double mem = 2.0 * (x + (double)p.N * p.K + (double)p.M * p.N) / 5.0e6 + 0.02 * fill;
-    return 2.0 + std::max(std::sqrt(fill * fill + chain * chain), mem);
+    const double second_round = wgs <= 256 ? 1.0 : window ? (p.K > 3200 ? 1.15 : 1.0) : p.K > 1200 ? 1.25 : 1.0;
+    return (2.0 + std::max(std::sqrt(fill * fill + chain * chain), mem)) * second_round;
   }
 };
 

@@ -417,6 +417,17 @@ def test_chains_with_heavy_activations_stream_only_in_full_rounds():
     assert [p.startswith("chainstream") for p in picks] == [False] * len(tiled) + [True] * len(streamed), picks
 
 
+def test_deep_reductions_over_many_small_tiles_stay_with_the_tiled_kernels():
+    """More than 256 tiles of 32 x 32: the kernels for small problems are up to 1.45 times slower with a deep reduction, faster with a short one."""
+    gemm = lambda m, n, k, lay: "b.bolt_check(b.OP_GEMM, b.gemm_desc(%d, %d, %d, b_layout=b.LAYOUT_%s))" % (m, n, k, lay)
+    conv = lambda *a: "b.bolt_check(b.OP_CONV2D, b.conv_desc%r)" % (a,)
+    tiled = [gemm(4677, 40, 3272, "KN"), gemm(2986, 80, 2000, "NK"), gemm(759, 608, 4784, "KN"), conv(1, 56, 56, 1568, 128, 1, 1),
+             conv(3, 14, 14, 408, 648, 3, 3, 1, 1)]
+    split = [gemm(989, 440, 384, "KN"), gemm(32, 1000, 2048, "KN"), conv(12, 7, 7, 40, 504, 5, 5, 1, 2), conv(7, 28, 28, 40, 48, 5, 5, 1, 2)]
+    picks = _picks(tiled + split)
+    assert [p.startswith("ws_") for p in picks] == [False] * len(tiled) + [True] * len(split), picks
+
+
 def test_built_in_pick_rule_families():
     """What a call without a config runs (no GPU needed: bolt_check resolves the pick, BOLT_TUNE_LOG=1 names it): the
     halo kernel for a 3x3 stride-1 layer, the ping-pong kernels for a GEMM that fills the chip in either weight layout,
