@@ -428,6 +428,14 @@ def test_deep_reductions_over_many_small_tiles_stay_with_the_tiled_kernels():
     assert [p.startswith("ws_") for p in picks] == [False] * len(tiled) + [True] * len(split), picks
 
 
+def test_one_tap_filters_over_many_unpadded_pixels_stay_with_the_alignment_2_kernels():
+    """1x1 filters give nothing to the patch in LDS that kernels for unpadded channels copy: above 16000 input pixels and 32 channels."""
+    conv = lambda *a: "b.bolt_check(b.OP_CONV2D, b.conv_desc%r)" % (a,)
+    picks = _picks([conv(80, 30, 28, 98, 40, 1, 1, 2), conv(88, 36, 18, 34, 64, 1, 1, 2), conv(2, 59, 27, 82, 16, 1, 1, 2), conv(46, 28, 10, 114, 32, 1, 1),
+                    conv(128, 14, 19, 46, 32, 5, 7)])
+    assert [p.startswith("even_") for p in picks] == [False, False, True, True, True], picks
+
+
 def test_built_in_pick_rule_families():
     """What a call without a config runs (no GPU needed: bolt_check resolves the pick, BOLT_TUNE_LOG=1 names it): the
     halo kernel for a 3x3 stride-1 layer, the ping-pong kernels for a GEMM that fills the chip in either weight layout,
