@@ -667,10 +667,11 @@ static int b2b_heuristic(const std::vector<B2bInstance>& tab, const B2bProblem& 
   }
   // More 128-row tiles than two per compute unit: the tiled kernels go round again, the streaming one overlaps the rounds.  Of
   // the widths that hold the pair the least work takes the rows, then the fewest columns to activate.
-  // A 32-wide op1 gains at any number of rows.  The others gain where the last round is three quarters full, or nothing but
+  // A 32-wide op1, and whatever the tiled kernels have tiles of 64 rows for (15 problems, five activations: 0.45 to 0.76 of their
+  // time), gains at any number of rows.  The others gain where the last round is three quarters full, or nothing but
   // cheap activations stands against tiles of the same widths; (32, 128), whose tiles are three to a compute unit, in two rounds
   // only.  GELU and softplus outweigh the rest: never over more padded columns than the tiled kernel's.  Over 150 problems with
-  // five activations each (20000 to 400000 rows, K0 8 to 128), time against the tiled kernels' pick: mean 0.86, 6 of 750 more
+  // five activations each (20000 to 400000 rows, K0 8 to 128), time against the tiled kernels' pick: mean 0.858, 6 of 750 more
   // than 3 % slower, none more than 10; streamed from 65537 rows on whatever the rest, 115 and 92 (78392 x 32 -> 24 -> 48 with
   // GELU 13.2 -> 25.2 us).
   if (best >= 0 && ceil_div(pr.p.M, 128) > 2 * kNumCU) {
@@ -685,7 +686,7 @@ static int b2b_heuristic(const std::vector<B2bInstance>& tab, const B2bProblem& 
       const StreamRounds r = stream_rounds(pr.p.M, st.waves_m * st.waves_n, st.dyn_lds_bytes(pr.p));
       bool gains = heavy_columns(st) <= heavy_columns(ti);
       if (st.n1t > 64 && st.n0t <= 32) gains &= !heavy0 && !heavy1 && r.rounds == 2 && r.full >= 0.75;
-      else if (st.n1t > 32) gains &= r.full >= 0.75 || (!heavy0 && !heavy1 && st.n0t == ti.n0t && st.n1t == ti.n1t);
+      else if (st.n1t > 32 && ti.bm > 64) gains &= r.full >= 0.75 || (!heavy0 && !heavy1 && st.n0t == ti.n0t && st.n1t == ti.n1t);
       if (gains) best = stream;
     }
   }

@@ -398,7 +398,8 @@ def test_pairs_stream_where_their_rounds_are_full_or_activations_cheap():
              pair(152820, 48, 8, 104, "relu", "relu"), pair(109942, 48, 8, 104, "gelu", "gelu"), pair(68365, 80, 16, 16, "gelu", "none"),
              pair(78816, 40, 64, 64, "gelu", "gelu"), pair(65536, 96, 64, 32, "relu", "relu")]
     streamed = [pair(131072, 96, 64, 32, "relu", "relu"), pair(74538, 96, 64, 32, "gelu", "gelu"), pair(78816, 40, 64, 64, "relu", "hardswish"),
-                pair(109000, 40, 64, 64, "gelu", "gelu"), pair(109942, 48, 8, 104, "relu", "relu"), pair(120995, 40, 128, 64, "softplus", "softplus")]
+                pair(109000, 40, 64, 64, "gelu", "gelu"), pair(109942, 48, 8, 104, "relu", "relu"), pair(120995, 40, 128, 64, "softplus", "softplus"),
+                pair(67914, 24, 56, 120, "gelu", "gelu")]
     picks = _picks(tiled + streamed)
     assert [p.startswith("pairstream") for p in picks] == [False] * len(tiled) + [True] * len(streamed), picks
     assert picks[len(tiled)].endswith("n64_32") and picks[len(tiled) + 3].endswith("n64_64")
