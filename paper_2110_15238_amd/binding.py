@@ -9,6 +9,8 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import sys
+import warnings
 from dataclasses import dataclass
 from typing import Optional, Sequence, Tuple
 
@@ -64,11 +66,6 @@ class BoltError(RuntimeError):
 if not os.path.exists(LIB_PATH):
     raise ImportError("libbolt.so is not built: run `python -c 'import __graft_entry__ as g; g.build()'` "
                       "(or `make -C paper_2110_15238_amd/csrc`) first; there is no fallback path")
-
-FASTCALL_PATH = os.path.join(_HERE, "_fastcall.so")
-if not os.path.exists(FASTCALL_PATH):
-    raise ImportError("_fastcall.so is not built: run `python -c 'import __graft_entry__ as g; g.build()'` "
-                      "(or `make -C paper_2110_15238_amd/csrc`) first")
 
 _lib = C.CDLL(LIB_PATH)
 _vp, _i32, _sz = C.c_void_p, C.c_int32, C.c_size_t
@@ -174,14 +171,26 @@ def _load_torch():
 _fast = None
 
 
+class _NoFast:
+    """In the place of an extension that this interpreter or torch cannot load: every call takes the general path."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
 def _load_fast():
     """The extension needs torch in the process, which this module loads with the first tensor."""
     global _fast
     _load_torch()
-    from . import _fastcall
-    _fastcall.types(GemmDesc, ConvDesc, BoltConfig)
-    _fast = _fastcall
-    return _fastcall
+    try:
+        from . import _fastcall
+        _fastcall.types(GemmDesc, ConvDesc, BoltConfig)
+        _fast = _fastcall
+    except ImportError as e:
+        warnings.warn("calls are marshalled through ctypes, a microsecond slower: %s (make -C paper_2110_15238_amd/csrc "
+                      "PYTHON=%s builds the extension)" % (e, sys.executable), RuntimeWarning, stacklevel=3)
+        _fast = _NoFast()
+    return _fast
 
 
 def _stream() -> int:

@@ -375,6 +375,50 @@ for m, n, k in ((16384, 8, 8192), (16384, 16, 8192), (16384, 32, 8192), (8192, 6
     assert costs and min(costs) >= 2 * 16384 * 8192 / 6.5e6, costs  # the activations at 6.5 TB/s
 
 
+def test_calls_without_the_extension_take_the_general_path():
+    """An interpreter or torch that cannot load _fastcall: the package imports, the first call says so once, and every launch call
+    is marshalled (here: refused, the tensors are on the CPU) through ctypes."""
+    import os
+    import subprocess
+    import sys
+    code = """
+import sys, warnings
+sys.path.insert(0, %r)
+sys.modules["paper_2110_15238_amd._fastcall"] = None  # as if it could not be loaded
+import torch
+import paper_2110_15238_amd as b
+t = torch.zeros(64, 64, dtype=torch.float16)
+d, c = b.gemm_desc(64, 64, 64), b.conv_desc(1, 8, 8, 64, 64, 1, 1)
+calls = [lambda: b.bolt_gemm_epilogue(d, t, t, None, t), lambda: b.bolt_gemm_epilogue_residual(d, t, t, None, t, t),
+         lambda: b.bolt_conv2d_fprop_nhwc(c, t, t, None, t), lambda: b.bolt_conv2d_fprop_nhwc_residual(c, t, t, None, t, t),
+         lambda: b.bolt_b2b_gemm(d, d, t, t, None, t, None, t), lambda: b.bolt_b2b_conv(c, c, t, t, None, t, None, t),
+         lambda: b.bolt_b2b_gemm_chain([d] * 3, t, [t] * 3, [None] * 3, t), lambda: b.bolt_b2b_conv_chain([c] * 3, t, [t] * 3, [None] * 3, t)]
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    refused = 0
+    for call in calls:
+        try:
+            call()
+        except AssertionError as e:
+            refused += "CUDA float16" in str(e)
+assert refused == len(calls), refused
+assert [w.category for w in seen] == [RuntimeWarning], seen
+""" % os.path.abspath(ROOT)
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+
+
+def test_the_c_library_builds_without_torch():
+    """`make lib`, and `make` where the Python has no torch, ask for nothing but hipcc (dry run: nothing is compiled)."""
+    import os
+    import subprocess
+    csrc = os.path.join(os.path.abspath(ROOT), "paper_2110_15238_amd", "csrc")
+    run = lambda *a: subprocess.run(["make", "-C", csrc, "-n", "-B", *a], capture_output=True, text=True, check=True).stdout
+    assert "fastcall" not in run("lib") and "libbolt.so" in run("lib")
+    assert "fastcall.cpp" not in run("PYTHON=false") and "libbolt.so" in run("PYTHON=false")
+    assert "fastcall.cpp" in run()
+
+
 def _picks(calls):
     """The kernels that the built-in rule picks for a list of expressions over `b`, the package (BOLT_TUNE_LOG=1 names them)."""
     import os
