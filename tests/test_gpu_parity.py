@@ -376,6 +376,7 @@ def test_conv_even_channels_infinities_stay_where_they_belong(bolt):
     w = torch.ones((16, 2, 2, 10), dtype=torch.float16, device="cuda")
     w[3, 0, 1, 0] = w[5, 1, 1, 9] = float("inf")
     d = bolt.conv_desc(1, 4, 5, 10, 16, 2, 2, 1, 0)
+    assert sum(bolt.bolt_instance_supports(bolt.OP_CONV2D, k, d) for k in _pingpong_ids(bolt, bolt.OP_CONV2D)) == 16  # all that pad on the way to LDS
     for kid in _pingpong_ids(bolt, bolt.OP_CONV2D):
         if bolt.bolt_instance_supports(bolt.OP_CONV2D, kid, d):
             y = torch.empty((1, 3, 4, 16), dtype=torch.float16, device="cuda")
@@ -392,9 +393,10 @@ def test_conv_even_channels_infinities_stay_where_they_belong(bolt):
 
 
 def _wave_split_ids(bolt, op, *descs):
-    """Instances that split the reduction over their waves: tile K of one matrix instruction, nothing else to split."""
+    """Instances that split the reduction over their waves (8 for every operand mode): 16 x 16 x 32 matrix instructions, tile K of one
+    of them, and of those that accept a channel count divisible by 8 the only ones with operands in flight (two stages)."""
     cfg = lambda k: bolt.bolt_instance_config(op, k)
-    return [k for k in _pingpong_ids(bolt, op) if cfg(k).tile_k == 32 and bolt.bolt_instance_supports(op, k, *descs)]
+    return [k for k in _pingpong_ids(bolt, op) if cfg(k).tile_k == 32 and cfg(k).stages == 2 and bolt.bolt_instance_supports(op, k, *descs)]
 
 
 @pytest.mark.parametrize("layout", ["nk", "kn"])
@@ -416,7 +418,7 @@ def test_gemm_wave_split_integer_bit_exact_with_gaps_and_residual(bolt, layout, 
     d = bolt.gemm_desc(M, N, K, lda=K + 16, ldb=W.shape[1] + 16, ldd=N + 16,
                        b_layout=bolt.LAYOUT_NK if layout == "nk" else bolt.LAYOUT_KN)
     ids = _wave_split_ids(bolt, bolt.OP_GEMM, d)
-    assert len(ids) >= 8
+    assert len(ids) == 8
     tA, tW, tb, tC = gap(A), gap(W), dev(bias), dev(C)
     D = torch.empty((M, N + 16), dtype=torch.float16, device="cuda")
     for kid in ids + [-1]:  # and the built-in pick
@@ -450,7 +452,7 @@ def test_conv_wave_split_integer_bit_exact(bolt, case):
     want_res = ref.conv2d_nhwc_residual(x, w, bias, res, stride=stride, pad=pad)
     d = bolt.conv_desc(N, H, W, Cc, K, R, S, stride, pad)
     ids = _wave_split_ids(bolt, bolt.OP_CONV2D, d)
-    assert len(ids) >= 8
+    assert len(ids) == 8
     y = torch.empty(want.shape, dtype=torch.float16, device="cuda")
     tx, tw, tb, tr = dev(x), dev(w), dev(bias), dev(res)
     for kid in ids + [-1]:
@@ -1426,14 +1428,16 @@ def test_b2b_gemm_rows_streamed_in_rounds(bolt, shape, layout):
     Wd = [dev(np.ascontiguousarray(W.T)) if layout == "nk" else dev(W) for W in (W0, W1)]
     Ad, bd = dev(A), [dev(b0), dev(b1)]
     kids = [k for k in range(bolt.bolt_num_instances(bolt.OP_B2B_GEMM)) if bolt.bolt_instance_supports(bolt.OP_B2B_GEMM, k, g0, g1)]
+    streaming = [k for k in kids if bolt.bolt_instance_config(bolt.OP_B2B_GEMM, k).stages == 1]
+    assert len(streaming) == 1  # of each layout's five widths (the others are too narrow or more than half padding)
     for kid in kids + [-1]:  # -1: the built-in pick rule
         _say("b2b gemm %s weights %s instance %d" % (shape, layout, kid))
         D, R = torch.full((M, N1), float("nan"), dtype=torch.float16, device="cuda"), dev(C)
         bolt.bolt_b2b_gemm(g0, g1, Ad, Wd[0], bd[0], Wd[1], bd[1], D, {"kernel_id": kid})
-        bolt.bolt_b2b_gemm_residual(g0, g1, Ad, Wd[0], bd[0], Wd[1], bd[1], R, R, 0.5)
+        bolt.bolt_b2b_gemm_residual(g0, g1, Ad, Wd[0], bd[0], Wd[1], bd[1], R, R, 0.5, {"kernel_id": kid})
         torch.cuda.synchronize()
         assert_close(host(D), want, "b2b gemm %s instance %d" % (shape, kid))
-    assert_close(host(R), want_res, "b2b gemm %s residual in place" % (shape,))
+        assert_close(host(R), want_res, "b2b gemm %s residual in place, instance %d" % (shape, kid))
 
 
 CONV_CHAINS = [  # (N, H, W, C, K0, R, S, stride, pad, K1, K2)
