@@ -594,8 +594,8 @@ def main():
     out["epilogue_fusion"] = epi
 
     # ------------------------------------------------------------------ channel padding (context)
-    # Table 3 (Section 4.1.3): input channels not divisible by 8.  "unpadded" runs the tuned alignment-2
-    # kernel on the tensor as it is; "padded" pads the activation to the next multiple of 8 (weights are
+    # Table 3 (Section 4.1.3): input channels not divisible by 8.  "unpadded" runs the tuned kernel for
+    # unpadded channels on the tensor as it is; "padded" pads the activation to the next multiple of 8 (weights are
     # padded once, offline) and runs the tuned alignment-8 kernel.  speedup = unpadded conv / padded conv;
     # pad_cost = padding time / (padding + padded conv), as in the table.
     t3 = []
@@ -835,17 +835,18 @@ def main():
                                "cores": ref.num_threads(), "kind": "oracle",
                                "sample": "%s in full (3x3 convolutions at batch 32, %.1f GFLOP), %.1f s" % (
                                    ", ".join(n for n, _, _ in sample), flops / 1e9, dt)}
-    # the long per-shape table first, the fused-vs-unfused numbers and the target rows last (a reader of the tail of
-    # the line finds them there)
-    last = ("epilogue_fusion", "paper_table3_padding", "chains_of_three", "residual_epilogue", "bottleneck_block",
-            "layout_transformation", "probes", "cpu_baseline", "paper_tables_b2b", "b2b", "large_shapes")
-    head = {k: v for k, v in out.items() if k not in last and k != "shapes"}
-    ordered = dict(head)
-    ordered["shapes"] = out["shapes"]
-    for k in last:
-        if k in out:
-            ordered[k] = out[k]
-    print(json.dumps(ordered))
+    # Every table in full goes to stderr, as one line.  The line on stdout stays under 8000 characters, so that whoever keeps only
+    # the end of a log still has all of it: the contract's fields, roofline and baseline, and of the tables the times.
+    print(json.dumps({"tables": out}), file=sys.stderr)
+    context = ("epilogue_fusion", "paper_table3_padding", "chains_of_three", "residual_epilogue", "bottleneck_block",
+               "layout_transformation", "paper_tables_b2b")
+    brief = {k: v for k, v in out.items() if k not in context}
+    for table in ("shapes", "large_shapes"):
+        keys = ("name", "ms", "tflops", "pct_mfma_peak", "error")
+        brief[table] = [{k: row[k] for k in keys if k in row} for row in out[table]]
+    brief["speedups"] = {k: [row.get("speedup", row.get("speedup_vs_three")) for row in out[k]]
+                         for k in ("epilogue_fusion", "paper_table3_padding", "chains_of_three", "paper_tables_b2b")}
+    print(json.dumps(brief))
 
 
 if __name__ == "__main__":
