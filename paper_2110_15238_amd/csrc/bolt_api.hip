@@ -293,7 +293,7 @@ static bolt_status check_conv_desc(const bolt_conv_desc* d, ConvDims* out) {
   if (d->H + 2 * d->pad_h < d->R || d->W + 2 * d->pad_w < d->S) return BOLT_ERR_INVALID_ARG;
   if (d->x_layout != BOLT_TENSOR_NHWC && d->x_layout != BOLT_TENSOR_NCHW) return BOLT_ERR_INVALID_ARG;
   if (d->y_layout != BOLT_TENSOR_NHWC && d->y_layout != BOLT_TENSOR_NCHW) return BOLT_ERR_INVALID_ARG;
-  // C % 8 == 0 is the fast path (128-bit accesses); an even C runs on the alignment-2 instances; C <= 4 (any
+  // C % 8 == 0 is the fast path (128-bit accesses); an even C runs on the instances for unpadded channels; C <= 4 (any
   // parity, either input layout) on the first-layer instances
   if ((d->K & 7) || ((d->C & 1) && d->C > 4)) return BOLT_ERR_ALIGNMENT;
   if (d->x_layout == BOLT_TENSOR_NCHW && d->C > 4) return BOLT_ERR_UNSUPPORTED;
@@ -419,7 +419,7 @@ static int fprop_heuristic(const std::vector<FpropInstance>& tab, const FpropPro
     if (!fprop_supports(in, pr) || (in.worth_trying && !in.worth_trying(pr.p))) continue;
     if (need_split_k && !fprop_can_split_k(in)) continue;
     const FpropParams& p = pr.p;
-    if (in.estimate) {  // a family with a cost model of its own, in the same microseconds
+    if (in.estimate) {  // a family with a cost model of its own, in the same microseconds (the first-layer strips: always the lowest)
       const double cost = in.estimate(p);
       if (tune_log_enabled()) std::fprintf(stderr, "[bolt_pick] candidate %d %s cost %.4g\n", i, in.name, cost);
       if (best < 0 || cost < best_cost) { best = i; best_cost = cost; }

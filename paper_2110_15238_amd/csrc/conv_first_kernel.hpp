@@ -15,8 +15,9 @@
 //   * each wave keeps all 64 channels' weights in registers (T k-steps x 4 fragments, 112 registers for 7 x 7) and walks over
 //     its share of the strip's 16-pixel blocks.
 // TP is chosen so that the strips fill the chip's 512 workgroup slots in whole rounds (plan()).
-// What bounds it: the output's way to memory.  Measured, 32 images of 224 x 224 x 3, 7 x 7 / 2, 64 channels, NCHW (51 of 61 MB
-// are output), conv_smallc_kernel -> this one: 29 -> 21.5 us (NHWC 24.3 -> 19.7), 3 x 3 / 2 24.5 -> 14.5; 32 of 96 x 96, 7 x 7 / 2,
+// What bounds it: instruction issue.  Vector instructions take 54 % of the SIMD-cycles, matrix ones 26 %, two waves share a SIMD;
+// the output leaves at 2.3 TB/s; 39 % of the LDS-active cycles are bank conflicts, with the LDS active in 28 % of all (counters
+// of the first of these).  Measured, 32 images of 224 x 224 x 3, 7 x 7 / 2, 64 channels, NCHW, conv_smallc_kernel -> this one: 29 -> 21.5 us (NHWC 24.3 -> 19.7), 3 x 3 / 2 24.5 -> 14.5; 32 of 96 x 96, 7 x 7 / 2,
 // 32 channels 15.0 -> 8.7; 1 of 224 x 224 7.5 -> 6.2.
 #pragma once
 #include "conv_smallc_kernel.hpp"

@@ -1,5 +1,6 @@
 // Alignment-2 convolution instances: input channel counts that are even but not multiples of 8.
-// These are what an unpadded layer has to run on; Table 3 measures channel padding against them.
+// What the kernels that pad on the way to LDS (inst_conv_even.hip) do not take, or not as fast, runs here: fewer than 10
+// channels, patches beyond LDS, one-tap filters over many pixels.
 #include "instances.hpp"
 namespace bolt {
 #define A2(BM, BN, BK, WM, WN) BOLT_FPROP_INSTANCE(BM, BN, BK, WM, WN, 2, 2)
