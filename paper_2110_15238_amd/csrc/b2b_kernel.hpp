@@ -464,6 +464,7 @@ struct B2bInstance {
   // Relative time per unit of tile work of this kernel family on the convolution pairs of Section 4.1.2, as measured
   // (0 = 1.0: the weights-resident kernels); read by the built-in pick rule only, bolt_tune measures.
   float prior;
+  bool any_n1;  // the second width costs what the problem has, not what was compiled: never too wide
 };
 
 template <typename KernT>

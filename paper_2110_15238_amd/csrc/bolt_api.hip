@@ -247,6 +247,7 @@ struct Tables {
     register_gemm_ws_instances(gemm);  // small problems (appended, as above)
     register_conv_ws_instances(conv);
     register_conv_first_instances(conv);  // first layers of 3 or 4 channels
+    register_conv_patch_instances(conv);  // 3x3 into at most 64 channels (appended, as above)
     register_b2b_gemm_instances(b2b_gemm);
     register_b2b_gemm_dma_instances(b2b_gemm);
     register_b2b_gemm_dma_kn_instances(b2b_gemm);
@@ -254,6 +255,7 @@ struct Tables {
     register_b2b_conv_instances(b2b_conv);
     register_b2b_conv_dma_instances(b2b_conv);
     register_b2b_conv_halo_instances(b2b_conv);
+    register_b2b_conv_patch_instances(b2b_conv);  // (appended, as above)
   }
 };
 static const Tables& tables() {
@@ -367,7 +369,7 @@ static bool fprop_supports(const FpropInstance& in, const FpropProblem& pr) {
   }
   // an NCHW output: only the instances with that store, and they have no other; no residual form
   if ((pr.p.y_nchw != 0) != in.nchw_out) return false;
-  if (in.nchw_out && pr.residual) return false;
+  if ((in.nchw_out || in.no_residual) && pr.residual) return false;
   if (in.wmode != pr.wmode) return false;
   if (in.xmode != pr.xmode) return false;
   if (in.kn_dma && (int64_t)pr.p.K * pr.p.ldw * 2 >= (1ll << 31)) return false;
@@ -467,7 +469,7 @@ static int fprop_pick(const std::vector<FpropInstance>& tab, const FpropProblem&
   };
   static_assert(sizeof(Key) == sizeof(void*) + (7 + 11) * sizeof(int), "compared as bytes: no padding");
   const FpropParams& p = pr.p;
-  const Key key{&tab, pr.xmode | pr.wmode << 4 | (pr.residual ? 256 : 0) | (p.x_nchw ? 512 : 0) | (p.y_nchw ? 1024 : 0) | (need_split_k ? 2048 : 0),
+  const Key key{&tab, pr.xmode | pr.wmode << 4 | (pr.residual ? 256 : 0) | (p.x_nchw ? 512 : 0) | (p.y_nchw ? 1024 : 0) | (need_split_k ? 2048 : 0) | p.act << 12,
                 p.M, p.N, p.K, p.ldx, p.ldw, p.ldy, p.cg};
   struct Entry {
     Key key;
@@ -606,15 +608,17 @@ static bool b2b_can_run(const B2bInstance& in, const B2bProblem& pr) {
 // Threadblock residence with the tightest compiled bound: an instance that would carry more than 2x padding in a
 // width is left out ...
 static bool b2b_is_tight(const B2bInstance& in, const B2bProblem& pr) {
+  if (in.any_n1) return true;
   return !((in.n0t > 32 && in.n0t / 2 >= pr.p.N0) || (in.n1t > 32 && in.n1t / 2 >= pr.p.N1));
 }
 // ... unless that leaves the problem without a kernel (e.g. N0 = 128 with N1 = 16: no compiled pair of widths is tight
 // in both).
+// (Instances that are tight by design leave the others' legality as it was.)
 static bool b2b_supports(const std::vector<B2bInstance>& tab, int id, const B2bProblem& pr) {
   if (!b2b_can_run(tab[id], pr)) return false;
   if (b2b_is_tight(tab[id], pr)) return true;
   for (const B2bInstance& other : tab)
-    if (b2b_can_run(other, pr) && b2b_is_tight(other, pr)) return false;
+    if (!other.any_n1 && b2b_can_run(other, pr) && b2b_is_tight(other, pr)) return false;
   return true;
 }
 
@@ -648,7 +652,7 @@ static int b2b_heuristic(const std::vector<B2bInstance>& tab, const B2bProblem& 
   int best = -1;
   double best_cost = 0;
   for (int i = 0; i < (int)tab.size(); ++i) {
-    if (b2b_streams(tab[i]) || !b2b_supports(tab, i, pr)) continue;
+    if (tab[i].any_n1 || b2b_streams(tab[i]) || !b2b_supports(tab, i, pr)) continue;
     const B2bInstance& in = tab[i];
     const double tiles = ceil_div(pr.p.M, in.bm);
     const int lds = in.dyn_lds_bytes ? in.dyn_lds_bytes(pr.p) : in.lds_bytes(pr.p.K0);
@@ -690,6 +694,14 @@ static int b2b_heuristic(const std::vector<B2bInstance>& tab, const B2bProblem& 
       if (gains) best = stream;
     }
   }
+  // The convolution pairs with the first op's weights in registers (conv_patch_kernel), the tightest widths of those that can run
+  // it: of 98 pairs (batch 1 to 61, 14 x 14 to 112 x 112, 16 to 128 channels, with and without a residual) 0.41 to 0.95 of the
+  // time of the tiled kernels' pick, 1.0 twice.
+  int patch = -1;
+  auto widths = [](const B2bInstance& in) { return (in.bk << 10) + in.n0t; };
+  for (int i = 0; i < (int)tab.size(); ++i)
+    if (tab[i].any_n1 && b2b_supports(tab, i, pr) && (patch < 0 || widths(tab[i]) < widths(tab[patch]))) patch = i;
+  if (patch >= 0) best = patch;
   if (tune_log_enabled() && best >= 0) std::fprintf(stderr, "[bolt_pick] -> %d %s\n", best, tab[best].name);
   return best;
 }

@@ -219,6 +219,7 @@ struct FpropInstance {
   // Where the pick rule and bolt_tune consider this instance (null: wherever it is legal).  Not a matter of legality: a
   // configuration that was tuned for one number of rows keeps working at any other.
   bool (*worth_trying)(const FpropParams&);
+  bool no_residual;  // the kernel has no form with a residual matrix
 };
 
 template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int XMODE, int WMODE>

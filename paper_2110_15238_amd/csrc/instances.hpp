@@ -14,6 +14,7 @@
 #include "conv_even_kernel.hpp"
 #include "conv_first_kernel.hpp"
 #include "conv_halo_kernel.hpp"
+#include "conv_patch_kernel.hpp"
 #include "conv_smallc_kernel.hpp"
 #include "b2b_chain_kernel.hpp"
 #include "chain_stream_kernel.hpp"
@@ -128,6 +129,8 @@ void register_conv_even_instances(std::vector<FpropInstance>& v);
 void register_gemm_ws_instances(std::vector<FpropInstance>& v);
 void register_conv_ws_instances(std::vector<FpropInstance>& v);
 void register_conv_first_instances(std::vector<FpropInstance>& v);
+void register_b2b_conv_patch_instances(std::vector<B2bInstance>& v);
+void register_conv_patch_instances(std::vector<FpropInstance>& v);
 void register_conv_smallc_instances(std::vector<FpropInstance>& v);
 void register_conv_nchw_out_instances(std::vector<FpropInstance>& v);
 void register_b2b_gemm_instances(std::vector<B2bInstance>& v);

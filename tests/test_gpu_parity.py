@@ -783,6 +783,55 @@ def test_b2b_conv_shapes_every_instance(bolt, shape):
     assert ran >= 1, "no instance for %s" % (shape,)
 
 
+PATCH_EDGES = [  # N H W C K0 R stride pad K1: units of 4 x 8 pixels and less, chunks of 64 columns, padded channels
+    (1, 1, 1, 8, 8, 3, 1, 1, 8), (2, 9, 9, 64, 64, 3, 1, 1, 256), (1, 4, 8, 64, 40, 3, 1, 1, 72), (3, 5, 17, 48, 64, 3, 1, 1, 136), (1, 13, 33, 40, 56, 3, 1, 0, 64),
+    (2, 7, 15, 32, 64, 3, 1, 2, 200), (5, 6, 23, 16, 32, 3, 1, 1, 192), (1, 11, 16, 56, 24, 3, 1, 1, 256), (2, 17, 19, 64, 64, 3, 2, 1, 256), (1, 15, 34, 24, 48, 3, 2, 1, 88),
+    (4, 9, 9, 64, 24, 3, 2, 0, 64), (1, 5, 9, 128, 64, 1, 1, 0, 256), (2, 8, 31, 72, 40, 1, 1, 0, 104), (3, 9, 14, 16, 32, 1, 1, 0, 8), (1, 13, 21, 104, 32, 1, 2, 0, 160), (2, 10, 7, 64, 64, 1, 2, 1, 128),
+    (9, 56, 56, 64, 64, 3, 1, 1, 64), (40, 30, 29, 32, 32, 3, 1, 1, 72), (36, 45, 50, 24, 32, 1, 1, 0, 40)]  # (the last three: several units per wave)
+
+
+@pytest.mark.parametrize("case", PATCH_EDGES)
+def test_conv_patch_pairs_and_single_op_integer_bit_exact(bolt, case):
+    """The kernels with the first op's weights in registers, at the edges of their units, columns and channel counts; every
+    partial sum is exact (|sum| <= 2 C R S + 2, and 2 K0 times that), so results are equal bit for bit; the residual in place."""
+    N, H, W, Cc, K0, R, stride, pad, K1 = case
+    x, w0 = wl.integer_fp16(511, 0, (N, H, W, Cc), 0, 1), wl.integer_fp16(511, 1, (K0, R, R, Cc), -1, 1)
+    b0, w1, b1 = wl.integer_fp16(511, 2, (K0,), -2, 2), wl.integer_fp16(511, 3, (K1, 1, 1, K0), -1, 1), wl.integer_fp16(511, 4, (K1,), -2, 2)
+    c0 = bolt.conv_desc(N, H, W, Cc, K0, R, R, stride, pad)
+    P, Q = bolt.conv_out_hw(c0)
+    res = wl.integer_fp16(511, 5, (N, P, Q, K1), -3, 3)
+    xd, w0d, b0d, w1d, b1d = (dev(t) for t in (x, w0, b0, w1, b1))
+    ran = 0
+    for act0, act1, beta1, bias in (("relu", "relu", 1.0, True), ("none", "none", 2.0, True), ("none", "relu", 1.0, False)):
+        c0 = bolt.conv_desc(N, H, W, Cc, K0, R, R, stride, pad, act=act0)
+        c1 = bolt.conv_desc(N, P, Q, K0, K1, 1, 1, act=act1, beta=beta1)
+        b1_eff = (b1 * np.float16(beta1)) if bias else None
+        want = ref.b2b_conv(x, w0, b0 if bias else None, w1, b1_eff, stride=stride, pad=pad, act0=act0, act1=act1)
+        want_res = ref.b2b_conv_residual(x, w0, b0 if bias else None, w1, b1_eff, res, gamma=2.0, stride=stride, pad=pad, act0=act0, act1=act1)
+        for kid in range(bolt.bolt_num_instances(bolt.OP_B2B_CONV)):
+            cfg = bolt.bolt_instance_config(bolt.OP_B2B_CONV, kid)
+            if cfg.tile_n != 256 or cfg.tile_m != 128 or cfg.stages != 1 or not bolt.bolt_instance_supports(bolt.OP_B2B_CONV, kid, c0, c1):
+                continue
+            _say("conv patch pair %s instance %d" % (case, kid))
+            y, r = torch.full((N, P, Q, K1), float("nan"), dtype=torch.float16, device="cuda"), dev(res)
+            bolt.bolt_b2b_conv(c0, c1, xd, w0d, b0d if bias else None, w1d, b1d if bias else None, y, {"kernel_id": kid})
+            bolt.bolt_b2b_conv_residual(c0, c1, xd, w0d, b0d if bias else None, w1d, b1d if bias else None, r, r, 2.0, {"kernel_id": kid})
+            torch.cuda.synchronize()
+            assert_bit_equal(host(y), want, "conv patch pair %s instance %d" % (case, kid))
+            assert_bit_equal(host(r), want_res, "conv patch pair %s residual, instance %d" % (case, kid))
+            ran += 1
+    assert ran >= 3
+    if R == 3 and stride == 1:
+        want, n = ref.conv2d_nhwc(x, w0, b0, stride=1, pad=pad), bolt.bolt_num_instances(bolt.OP_CONV2D)
+        c0 = bolt.conv_desc(N, H, W, Cc, K0, 3, 3, 1, pad)
+        for kid in (n - 2, n - 1):
+            if bolt.bolt_instance_supports(bolt.OP_CONV2D, kid, c0):
+                y = torch.full((N, P, Q, K0), float("nan"), dtype=torch.float16, device="cuda")
+                bolt.bolt_conv2d_fprop_nhwc(c0, xd, w0d, b0d, y, {"kernel_id": kid})
+                torch.cuda.synchronize()
+                assert_bit_equal(host(y), want, "conv patch %s instance %d" % (case, kid))
+
+
 # ---------------------------------------------------------------------------------------------
 # config 5: every distinct ResNet-50 layer shape at full size, tuned, sampled outputs
 # ---------------------------------------------------------------------------------------------
