@@ -47,6 +47,15 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* partial
   }
 }
 
+// Reads `n` 16-byte items on every XCD (workgroup ids are dealt round-robin over 8): bolt_tune evicts the L2 caches with it.
+// `never` is 0: it keeps the loads alive.
+__global__ __launch_bounds__(256) void tune_evict_kernel(const uintx4* src, int n, int never, unsigned* sink) {
+  uintx4 v = {0, 0, 0, 0};
+  const int wgs = gridDim.x >> 3;
+  for (int i = (blockIdx.x >> 3) * blockDim.x + threadIdx.x; i < n; i += wgs * blockDim.x) v ^= src[i];
+  if (never) *sink = v[0] ^ v[1] ^ v[2] ^ v[3];
+}
+
 // Kernel padding (Section 3.2.3): one thread writes one 16-byte chunk of the padded tensor.  An even
 // channel count is read as 32-bit pairs (a pair never straddles the end of a pixel), an odd one half
 // by half.  The host guarantees pixels * C8 / 8 < 2^31.
@@ -952,39 +961,93 @@ static bolt_status time_launches(F&& fn, int warm, int reps, hipStream_t stream,
 }
 
 
+// What the timing of a candidate is made of.  A program runs a layer once and then others: its weights, and mostly its input, are no
+// longer in the L2 caches, which back-to-back launches on the same buffers leave warm.  Ranked that way, the ResNet-50 layers
+// picked kernels that took 879 us (batch 32; batch 1: 397) in a network whose best ones take 764 (273), also because kernels
+// shorter than the host's launches all looked alike.  So a repetition is: read twice the caches' size, launch twice.  The
+// first launch finds cold caches, the second warm ones; the mean of the two is within 1 % of the best on either side.  The reads
+// also keep the GPU behind the host, so that short kernels are told apart.
+struct TuneEvict {
+  // the scratch array of bolt_gemm_epilogue_noalloc: 4 times the 4 MB of L2 that an XCD has, half of it read (nothing is written)
+  static constexpr int kBytes = BOLT_NOALLOC_SCRATCH_BYTES / 2;
+  void* const buf = scratch_of_current_device();
+  bolt_status launch(hipStream_t stream) const {
+    hipLaunchKernelGGL(tune_evict_kernel, dim3(kNumCU * 8), dim3(256), 0, stream, (const uintx4*)buf, kBytes / 16, 0, (unsigned*)buf);
+    return hipGetLastError() == hipSuccess ? BOLT_OK : BOLT_ERR_LAUNCH;
+  }
+};
+
 template <typename RunF>
 static bolt_status tune_candidates(std::vector<Candidate>& cands, RunF&& run, hipStream_t stream, Candidate* best,
                                    int* tried) {
   hipEvent_t e0, e1;
   if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) return BOLT_ERR_LAUNCH;
-  bolt_status status = BOLT_OK;
+  const TuneEvict evict;
+  bolt_status status = evict.buf ? BOLT_OK : BOLT_ERR_LAUNCH;
   int n_ok = 0;
-  // pass 1: a short timing of every candidate
-  for (auto& c : cands) {
-    bolt_status s = time_launches([&] { return run(c); }, 2, 8, stream, e0, e1, &c.ms);
-    if (s == BOLT_ERR_LAUNCH) { status = s; break; }
-    if (s != BOLT_OK) { c.ms = -1.f; continue; }
-    if (tune_log_enabled())
-      std::fprintf(stderr, "[bolt_tune] pass1 id %d swizzle %d split_k %d: %.4f ms\n", c.id, c.swizzle, c.split_k, c.ms);
-    ++n_ok;
-  }
-  if (status == BOLT_OK && n_ok == 0) status = BOLT_ERR_UNSUPPORTED;
-  if (status == BOLT_OK) {
-    std::vector<Candidate*> order;
-    for (auto& c : cands) if (c.ms >= 0.f) order.push_back(&c);
-    // Near-ties go to the XCD-aware tile order: the same time with fewer operand bytes crossing the fabric.
-    auto score = [](const Candidate* c) { return c->ms * (c->swizzle > 0 ? 0.985f : 1.f); };
-    std::sort(order.begin(), order.end(), [&](Candidate* a, Candidate* b) { return score(a) < score(b); });
-    // pass 2: the few fastest again, longer
-    const int finalists = std::min<int>(6, (int)order.size());
-    Candidate* win = nullptr;
-    for (int i = 0; i < finalists && status == BOLT_OK; ++i) {
-      Candidate* c = order[i];
-      bolt_status s = time_launches([&] { return run(*c); }, 3, 60, stream, e0, e1, &c->ms);
-      if (s != BOLT_OK) { status = s; break; }
-      if (!win || score(c) < score(win)) win = c;
+  {
+    // milliseconds of one repetition without its launches
+    float base = 0.f;
+    auto time_evict = [&] {
+      float ms = 0.f;
+      bolt_status s = time_launches([&] { return evict.launch(stream); }, 1, 8, stream, e0, e1, &ms);
+      if (s == BOLT_OK) base = base == 0.f ? ms : std::min(base, ms);
+      return s;
+    };
+    auto time_one = [&](const Candidate& c, int warm, int reps, float* ms) {
+      for (int i = 0; i < warm; ++i)
+        if (bolt_status s = run(c); s != BOLT_OK) return s;
+      bolt_status s = time_launches([&] {
+        bolt_status r = evict.launch(stream);
+        if (r == BOLT_OK) r = run(c);
+        return r == BOLT_OK ? run(c) : r;
+      }, 0, reps, stream, e0, e1, ms);
+      *ms = std::max(*ms - base, 0.f) / 2;
+      return s;
+    };
+    for (int i = 0; i < 4 && status == BOLT_OK; ++i) status = time_evict();
+    // pass 1: a short timing of every candidate, and once more of those within 30 % of the first
+    float first = 0.f;
+    for (auto& c : cands) {
+      if (status != BOLT_OK) break;
+      bolt_status s = time_one(c, 1, 3, &c.ms);
+      if (s == BOLT_ERR_LAUNCH) { status = s; break; }
+      if (s != BOLT_OK) { c.ms = -1.f; continue; }
+      if (tune_log_enabled())
+        std::fprintf(stderr, "[bolt_tune] pass1 id %d swizzle %d split_k %d: %.4f ms\n", c.id, c.swizzle, c.split_k, c.ms);
+      first = n_ok++ ? std::min(first, c.ms) : c.ms;
     }
-    if (status == BOLT_OK) { *best = *win; *tried = n_ok; }
+    if (status == BOLT_OK && n_ok == 0) status = BOLT_ERR_UNSUPPORTED;
+    std::vector<Candidate*> order;
+    for (auto& c : cands)
+      if (status == BOLT_OK && c.ms >= 0.f && c.ms <= 1.3f * first) {
+        float ms = 0.f;
+        status = time_one(c, 0, 3, &ms);
+        c.ms = std::min(c.ms, ms);
+        order.push_back(&c);
+      }
+    if (status == BOLT_OK) {
+      // Near-ties go to the XCD-aware tile order: the same time with fewer operand bytes crossing the fabric.
+      auto score = [](const Candidate* c) { return c->ms * (c->swizzle > 0 ? 0.985f : 1.f); };
+      std::sort(order.begin(), order.end(), [&](Candidate* a, Candidate* b) { return score(a) < score(b); });
+      // pass 2: the few fastest in turns, the median of the turns
+      constexpr int kTurns = 3;
+      order.resize(std::min<size_t>(6, order.size()));
+      std::vector<float> t(order.size() * kTurns);
+      for (int turn = 0; turn < kTurns; ++turn)
+        for (size_t i = 0; i < order.size() && status == BOLT_OK; ++i) status = time_one(*order[i], 0, 4, &t[i * kTurns + turn]);
+      Candidate* win = nullptr;
+      for (size_t i = 0; i < order.size(); ++i) {
+        std::nth_element(&t[i * kTurns], &t[i * kTurns] + kTurns / 2, &t[i * kTurns] + kTurns);
+        order[i]->ms = t[i * kTurns + kTurns / 2];
+        if (tune_log_enabled())
+          std::fprintf(stderr, "[bolt_tune] pass2 id %d swizzle %d split_k %d: %.4f ms\n", order[i]->id, order[i]->swizzle, order[i]->split_k, order[i]->ms);
+        if (!win || score(order[i]) < score(win)) win = order[i];
+      }
+      // the time that is reported: launches back to back
+      if (status == BOLT_OK) status = time_launches([&] { return run(*win); }, 1, 20, stream, e0, e1, &win->ms);
+      if (status == BOLT_OK) { *best = *win; *tried = n_ok; }
+    }
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
