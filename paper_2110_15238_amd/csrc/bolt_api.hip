@@ -256,6 +256,7 @@ struct Tables {
     register_gemm_ws_instances(gemm);  // small problems (appended, as above)
     register_conv_ws_instances(conv);
     register_conv_first_instances(conv);  // first layers of 3 or 4 channels
+    register_conv_slice_instances(conv);  // 3x3 of 128 to 512 channels (appended, as above)
     register_conv_patch_instances(conv);  // 3x3 into at most 64 channels (appended, as above)
     register_b2b_gemm_instances(b2b_gemm);
     register_b2b_gemm_dma_instances(b2b_gemm);

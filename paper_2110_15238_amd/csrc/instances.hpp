@@ -15,6 +15,7 @@
 #include "conv_first_kernel.hpp"
 #include "conv_halo_kernel.hpp"
 #include "conv_patch_kernel.hpp"
+#include "conv_slice_kernel.hpp"
 #include "conv_smallc_kernel.hpp"
 #include "b2b_chain_kernel.hpp"
 #include "chain_stream_kernel.hpp"
@@ -131,6 +132,7 @@ void register_conv_ws_instances(std::vector<FpropInstance>& v);
 void register_conv_first_instances(std::vector<FpropInstance>& v);
 void register_b2b_conv_patch_instances(std::vector<B2bInstance>& v);
 void register_conv_patch_instances(std::vector<FpropInstance>& v);
+void register_conv_slice_instances(std::vector<FpropInstance>& v);
 void register_conv_smallc_instances(std::vector<FpropInstance>& v);
 void register_conv_nchw_out_instances(std::vector<FpropInstance>& v);
 void register_b2b_gemm_instances(std::vector<B2bInstance>& v);

@@ -832,6 +832,35 @@ def test_conv_patch_pairs_and_single_op_integer_bit_exact(bolt, case):
                 assert_bit_equal(host(y), want, "conv patch %s instance %d" % (case, kid))
 
 
+SLICE_EDGES = [  # N H W K: tiles of 64 and 128 pixels and of 64 and 128 columns with remainders, images of one row or column, several images per tile
+    (1, 1, 1, 8), (1, 7, 9, 64), (1, 8, 8, 72), (13, 5, 1, 136), (3, 1, 43, 128), (2, 3, 2, 200), (9, 7, 7, 64), (1, 2, 32, 120), (3, 14, 14, 256), (20, 9, 8, 136)]
+
+
+@pytest.mark.parametrize("channels", (128, 256, 512))
+@pytest.mark.parametrize("shape", SLICE_EDGES)
+def test_conv_slice_integer_bit_exact(bolt, shape, channels):
+    """The 3x3 kernels split by input channels: every partial sum is exact (|sum| <= 9 C + 4 < 2^24), so results are equal bit for
+    bit.  Without a bias, with beta = 2 and without an activation too."""
+    N, H, W, K = shape
+    x, w, b = wl.integer_fp16(523, 0, (N, H, W, channels), 0, 1), wl.integer_fp16(523, 1, (K, 3, 3, channels), -1, 1), wl.integer_fp16(523, 2, (K,), -2, 2)
+    xd, wd, bd = dev(x), dev(w), dev(b)
+    ran = 0
+    for act, beta, bias in (("relu", 1.0, True), ("none", 2.0, True), ("relu", 1.0, False)):
+        d = bolt.conv_desc(N, H, W, channels, K, 3, 3, 1, 1, act=act, beta=beta)
+        want = ref.conv2d_nhwc(x, w, b * np.float16(beta) if bias else None, stride=1, pad=1, act=act)
+        for kid in range(bolt.bolt_num_instances(bolt.OP_CONV2D)):
+            cfg = bolt.bolt_instance_config(bolt.OP_CONV2D, kid)
+            if cfg.tile_k != 32 or cfg.waves_m != 1 or cfg.mfma_shape != 16 or cfg.stages != 2 or not bolt.bolt_instance_supports(bolt.OP_CONV2D, kid, d):
+                continue
+            _say("conv slice %s x %d instance %d" % (shape, channels, kid))
+            y = torch.full((N, H, W, K), float("nan"), dtype=torch.float16, device="cuda")
+            bolt.bolt_conv2d_fprop_nhwc(d, xd, wd, bd if bias else None, y, {"kernel_id": kid})
+            torch.cuda.synchronize()
+            assert_bit_equal(host(y), want, "conv slice %s x %d instance %d" % (shape, channels, kid))
+            ran += 1
+    assert ran >= 3 or (channels == 512 and W > 12)  # (three rows of 512 channels have to fit LDS beside the tile)
+
+
 # ---------------------------------------------------------------------------------------------
 # config 5: every distinct ResNet-50 layer shape at full size, tuned, sampled outputs
 # ---------------------------------------------------------------------------------------------
