@@ -298,9 +298,7 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const ConvPatchParam
   };
   auto op0_step = [&](const half_t* xs, int k) {
 #pragma unroll
-    for (int a = 0; a < FN0; ++a) {
-      acc0[a] = mfma_32x32x16(wf[k][a], xq[k % D], acc0[a]);
-    }
+    for (int a = 0; a < FN0; ++a) acc0[a] = mfma_32x32x16(wf[k][a], xq[k % D], acc0[a]);
     if (k + D < KS) read_x(xs, k + D);
   };
   const unsigned lo0 = p.act0 == ACT_RELU ? 0u : 0x7e007e00u, lo1 = p.act1 == ACT_RELU ? 0u : 0x7e007e00u;
@@ -418,12 +416,12 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const ConvPatchParam
     }
   };
   auto wait_patch = [&]() {
-      // the next patch has landed: it is older than the stores of all columns
-      if (nch == 1) __builtin_amdgcn_s_waitcnt(0x0F70 | 4);
-      else if (nch == 2) __builtin_amdgcn_s_waitcnt(0x0F70 | 8);
-      else if (nch == 3) __builtin_amdgcn_s_waitcnt(0x0F70 | 12);
-      else __builtin_amdgcn_s_waitcnt(0x0F70 | 1 << 14);
-      asm volatile("" ::: "memory");
+    // the next patch has landed: it is older than the stores of all columns
+    if (nch == 1) __builtin_amdgcn_s_waitcnt(0x0F70 | 4);
+    else if (nch == 2) __builtin_amdgcn_s_waitcnt(0x0F70 | 8);
+    else if (nch == 3) __builtin_amdgcn_s_waitcnt(0x0F70 | 12);
+    else __builtin_amdgcn_s_waitcnt(0x0F70 | 1 << 14);
+    asm volatile("" ::: "memory");
   };
 
   if constexpr (T::OVERLAP) {
@@ -445,7 +443,7 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const ConvPatchParam
     int un = u + step;
     Unit nxt = unit_at(un);
     issue_patch(patch_of(nxt, un < u_end), patch0 + NW * T::PATCH / 2);
-      make_d();
+    make_d();
     __builtin_amdgcn_s_waitcnt(0x0F70);
     asm volatile("" ::: "memory");
     while (un < u_end) {
@@ -493,7 +491,7 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const ConvPatchParam
         if (s == 0 || s < nch) segment(std::true_type{});
         else segment(std::false_type{});
       }
-          make_d();
+      make_d();
       wait_patch();
       cur = nxt;
       un = un2;
@@ -564,7 +562,7 @@ hipError_t launch_conv_patch_single(const FpropParams& f, hipStream_t stream) {
     "patch_c" #CP "_r" #RS "_st" #ST, 128, 64, 64, 4, 1, 1, 0, 2, 0, &bolt::launch_conv_patch_single<CP, RS, ST>, \
         &bolt::ConvPatchTraits<CP, 64, RS, ST, false>::supports_single,                                          \
         &bolt::ConvPatchTraits<CP, 64, RS, ST, false>::lds_bytes_single, 0, 0, true, false, false,               \
-        &bolt::ConvPatchTraits<CP, 64, RS, ST, false>::estimate, nullptr, true                                                                                         \
+        &bolt::ConvPatchTraits<CP, 64, RS, ST, false>::estimate, nullptr, true                              \
   }
 
 #define BOLT_CONV_PATCH_PAIR_INSTANCE(CP, N0T, RS, ST)                                                          \

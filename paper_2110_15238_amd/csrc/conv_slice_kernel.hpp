@@ -330,7 +330,7 @@ hipError_t launch_conv_slice(const FpropParams& p, hipStream_t stream) {
   {                                                                                                            \
     "slice_" #BM "x" #BN "_c" #CWS, BM, BN, 32, 4, 1, 1, 0, 2, 0, &bolt::launch_conv_slice<BM, BN, CWS>,          \
         &bolt::ConvSliceTraits<BM, BN, CWS>::supports, &bolt::ConvSliceTraits<BM, BN, CWS>::lds_bytes, 0, 16,    \
-        true, false, false, &bolt::ConvSliceTraits<BM, BN, CWS>::estimate, nullptr, true                                                            \
+        true, false, false, &bolt::ConvSliceTraits<BM, BN, CWS>::estimate, nullptr, true                   \
   }
 
 }  // namespace bolt
