@@ -59,19 +59,21 @@ __device__ __forceinline__ int lds_chunk_offset(int row, int chunk) {
 // erfc(z) = t * Q(t) * exp(-z^2), where Q is a degree-7 polynomial fitted (Chebyshev nodes on t in
 // (0, 1], float64 scaled-erfc as the target) to 4.6e-6 relative error.  This form has no cancellation in
 // the negative tail, where 1 + erf(v / sqrt 2) would lose every digit.
+// v * Phi(v) = max(v, 0) - |v| * erfc(z) / 2 on either side of zero, without a select; the polynomial is Q / 2.  |v| is bounded so
+// that infinity meets no product with the zero that erfc has become by then.
 __device__ __forceinline__ float gelu_fast(float v) {
-  const float z = fabsf(v) * 0.70710678118654752440f;
-  const float t = __builtin_amdgcn_rcpf(1.f + 0.5f * z);
-  float q = 4.458448196e-02f;
-  q = q * t + -8.891160022e-02f;
-  q = q * t + -6.914768965e-02f;
-  q = q * t + 1.436112067e-01f;
-  q = q * t + 1.560333553e-01f;
-  q = q * t + 2.497963131e-01f;
-  q = q * t + 2.819394284e-01f;
-  q = q * t + 2.820960852e-01f;
-  const float h = 0.5f * t * q * __builtin_amdgcn_exp2f(z * z * -1.44269504088896340736f);  // erfc(z) / 2
-  return v * (v < 0.f ? h : 1.f - h);
+  const float a = __builtin_elementwise_minimum(fabsf(v), 1e18f);  // (NaN stays NaN)
+  const float t = __builtin_amdgcn_rcpf(1.f + 0.35355339059327376220f * a);
+  float q = 2.229224098e-02f;
+  q = q * t + -4.445580011e-02f;
+  q = q * t + -3.457384482e-02f;
+  q = q * t + 7.180560335e-02f;
+  q = q * t + 7.801667765e-02f;
+  q = q * t + 1.248981566e-01f;
+  q = q * t + 1.409697142e-01f;
+  q = q * t + 1.410480426e-01f;
+  const float h = t * q * __builtin_amdgcn_exp2f(a * a * -0.72134752044448170368f);  // erfc(z) / 2
+  return __builtin_elementwise_maximum(v, 0.f) - a * h;
 }
 
 // softplus = max(v, 0) + log1p(e), e = exp(-|v|) in (0, 1]: three series terms while e is small (the
