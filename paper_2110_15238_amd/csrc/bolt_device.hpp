@@ -122,6 +122,19 @@ __device__ __forceinline__ float apply_act(float v, int act) {
   }
 }
 
+// ReLU or nothing in one instruction, max(v, lo) with lo = 0 or NaN: of a number and a NaN the hardware's maximum is the number, so
+// v > 0 ? v : 0 for every v, NaN included, and v itself otherwise.  (In C++ the compiler turns it back into two selects.)
+__device__ __forceinline__ float relu_bound(int act) { return act == ACT_RELU ? 0.f : __builtin_nanf(""); }
+__device__ __forceinline__ float at_least(float v, float lo) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  float r;
+  asm("v_max_f32 %0, %1, %2" : "=v"(r) : "s"(lo), "v"(v));
+  return r;
+#else
+  return v > lo || !(lo == lo) ? v : lo;
+#endif
+}
+
 // Fused epilogue arithmetic (Section 3.1, patterns (i)-(iii)) for one quad of an accumulator
 // fragment: 4 consecutive columns n .. n+3 of one output row, registers 4q .. 4q+3.
 //   out = act(alpha * acc + beta * bias[n + e]),  converted to FP16 with round-to-nearest-even.
@@ -151,11 +164,9 @@ __device__ __forceinline__ half4 epilogue_quad4_values(floatx4 a4, half4 hb, con
   if constexpr (SLOW) {
     v = apply_act_slow4(v, ep.act);
   } else {
+    const float lo = relu_bound(ep.act);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float r = v[e] > 0.f ? v[e] : 0.f;
-      v[e] = ep.act == ACT_RELU ? r : v[e];
-    }
+    for (int e = 0; e < 4; ++e) v[e] = at_least(v[e], lo);
   }
 #pragma unroll
   for (int e = 0; e < 4; ++e) o[e] = (half_t)v[e];

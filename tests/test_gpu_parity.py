@@ -832,6 +832,25 @@ def test_conv_patch_pairs_and_single_op_integer_bit_exact(bolt, case):
                 assert_bit_equal(host(y), want, "conv patch %s instance %d" % (case, kid))
 
 
+@pytest.mark.parametrize("layout", ("kn", "nk"))
+def test_epilogue_of_nan_and_infinity_every_instance(bolt, layout):
+    """ReLU is v > 0 ? v : 0 (NaN gives 0), no activation passes NaN on, GELU keeps NaN and infinity."""
+    a = np.zeros((64, 64), np.float16)
+    a[:4, 0] = np.nan, np.inf, -np.inf, -1
+    d = lambda act: bolt.gemm_desc(64, 64, 64, act=act, b_layout=bolt.LAYOUT_KN if layout == "kn" else bolt.LAYOUT_NK)
+    ad, bd = dev(a), dev(np.ones((64, 64), np.float16))
+    want = {"none": (np.nan, np.inf, -np.inf, -1, 0), "relu": (0, np.inf, 0, 0, 0), "gelu": (np.nan, np.inf)}
+    for kid in range(bolt.bolt_num_instances(bolt.OP_GEMM)):
+        for act, rows in want.items():
+            if not bolt.bolt_instance_supports(bolt.OP_GEMM, kid, d(act)):
+                continue
+            y = torch.full((64, 64), 7.0, dtype=torch.float16, device="cuda")
+            bolt.bolt_gemm_epilogue(d(act), ad, bd, None, y, {"kernel_id": kid})
+            torch.cuda.synchronize()
+            got = host(y)[:len(rows)]
+            assert np.array_equal(got, np.repeat(np.array(rows, np.float16)[:, None], 64, 1), equal_nan=True), (kid, act, got[:, 0])
+
+
 SLICE_EDGES = [  # N H W K: tiles of 64 and 128 pixels and of 64 and 128 columns with remainders, images of one row or column, several images per tile
     (1, 1, 1, 8), (1, 7, 9, 64), (1, 8, 8, 72), (13, 5, 1, 136), (3, 1, 43, 128), (2, 3, 2, 200), (9, 7, 7, 64), (1, 2, 32, 120), (3, 14, 14, 256), (20, 9, 8, 136)]
 
