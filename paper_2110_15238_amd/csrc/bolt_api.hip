@@ -991,7 +991,7 @@ static bolt_status tune_candidates(std::vector<Candidate>& cands, RunF&& run, hi
     float base = 0.f;
     auto time_evict = [&] {
       float ms = 0.f;
-      bolt_status s = time_launches([&] { return evict.launch(stream); }, 1, 8, stream, e0, e1, &ms);
+      bolt_status s = time_launches([&] { return evict.launch(stream); }, 1, 4, stream, e0, e1, &ms);
       if (s == BOLT_OK) base = base == 0.f ? ms : std::min(base, ms);
       return s;
     };
@@ -1006,7 +1006,7 @@ static bolt_status tune_candidates(std::vector<Candidate>& cands, RunF&& run, hi
       *ms = std::max(*ms - base, 0.f) / 2;
       return s;
     };
-    for (int i = 0; i < 4 && status == BOLT_OK; ++i) status = time_evict();
+    for (int i = 0; i < 2 && status == BOLT_OK; ++i) status = time_evict();
     // pass 1: a short timing of every candidate, and once more of those within 30 % of the first
     float first = 0.f;
     for (auto& c : cands) {
