@@ -469,7 +469,8 @@ static int fprop_heuristic(const std::vector<FpropInstance>& tab, const FpropPro
 
 // The rule's answer for a problem, remembered per thread in a small direct-mapped table: estimating every instance costs
 // 0.8 us of host time per call, as much as a quarter of the smallest launch.  The key is every number that the rule and
-// the instances' legality tests read (sizes, leading dimensions, geometry, modes), no address; a collision replaces.
+// the instances' legality tests read (sizes, leading dimensions, geometry, modes, the activation, whether alpha is 1), no
+// address; a collision replaces.
 static int fprop_pick(const std::vector<FpropInstance>& tab, const FpropProblem& pr, bool need_split_k) {
   if (tune_log_enabled()) return fprop_heuristic(tab, pr, need_split_k);
   struct Key {
@@ -479,7 +480,8 @@ static int fprop_pick(const std::vector<FpropInstance>& tab, const FpropProblem&
   };
   static_assert(sizeof(Key) == sizeof(void*) + (7 + 11) * sizeof(int), "compared as bytes: no padding");
   const FpropParams& p = pr.p;
-  const Key key{&tab, pr.xmode | pr.wmode << 4 | (pr.residual ? 256 : 0) | (p.x_nchw ? 512 : 0) | (p.y_nchw ? 1024 : 0) | (need_split_k ? 2048 : 0) | p.act << 12,
+  const Key key{&tab, pr.xmode | pr.wmode << 4 | (pr.residual ? 256 : 0) | (p.x_nchw ? 512 : 0) | (p.y_nchw ? 1024 : 0) | (need_split_k ? 2048 : 0) |
+                          p.act << 12 | (p.alpha == 1.f ? 1 << 16 : 0),
                 p.M, p.N, p.K, p.ldx, p.ldw, p.ldy, p.cg};
   struct Entry {
     Key key;

@@ -832,6 +832,19 @@ def test_conv_patch_pairs_and_single_op_integer_bit_exact(bolt, case):
                 assert_bit_equal(host(y), want, "conv patch %s instance %d" % (case, kid))
 
 
+@pytest.mark.parametrize("channels", (24, 64))
+def test_one_convolution_with_changing_alpha_and_activation(bolt, channels):
+    """Calls without a config on one thread that differ in alpha and the activation only: a remembered pick is not for all of them."""
+    x, w, b = wl.uniform_fp16(557, 0, (2, 28, 30, channels), -1, 1), wl.normal_fp16(557, 1, (64, 3, 3, channels), 0.1), wl.uniform_fp16(557, 2, (64,), -1, 1)
+    xd, wd, bd = dev(x), dev(w), dev(b)
+    y = torch.empty((2, 28, 30, 64), dtype=torch.float16, device="cuda")
+    for alpha, act in ((1.0, "relu"), (0.5, "relu"), (1.0, "relu"), (1.0, "gelu"), (0.5, "gelu"), (1.0, "none"), (-2.0, "none"), (1.0, "relu")):
+        y.fill_(float("nan"))
+        bolt.bolt_conv2d_fprop_nhwc(bolt.conv_desc(2, 28, 30, channels, 64, 3, 3, 1, 1, alpha=alpha, act=act), xd, wd, bd, y)
+        torch.cuda.synchronize()
+        assert_close(host(y), ref.conv2d_nhwc(x, w, b, stride=1, pad=1, alpha=alpha, act=act), "alpha %g %s" % (alpha, act))
+
+
 @pytest.mark.parametrize("layout", ("kn", "nk"))
 def test_epilogue_of_nan_and_infinity_every_instance(bolt, layout):
     """ReLU is v > 0 ? v : 0 (NaN gives 0), no activation passes NaN on, GELU keeps NaN and infinity."""

@@ -1,0 +1,57 @@
+"""Which kernels the library launches, without a GPU: in a process of its own whose HIP runtime is tests/hip_recorder.c."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+pytestmark = pytest.mark.skipif(not os.path.exists(os.path.join(ROOT, "paper_2110_15238_amd", "libbolt.so")),
+                                reason="libbolt.so not built (run __graft_entry__.build())")
+
+PRELUDE = """
+import ctypes as C, sys
+sys.path.insert(0, %r)
+import paper_2110_15238_amd as b
+lib, rec = b.binding.raw(), C.CDLL(%r)
+rec.recorder_launches.restype = C.c_char_p
+P = 0x10000  # stands for every device pointer
+
+def cost(name, ms, repeated=None):
+    rec.recorder_cost(name.encode(), C.c_float(ms), C.c_float(ms if repeated is None else repeated))
+
+def conv(d, cfg=None, res=False):  # status and kernels of one call
+    c = None if cfg is None else C.byref(b.BoltConfig.from_dict(cfg))
+    if res: s = lib.bolt_conv2d_fprop_nhwc_residual(C.byref(d), P, P, P, P, 1.0, P, c, None, 0, None)
+    else: s = lib.bolt_conv2d_fprop_nhwc(C.byref(d), P, P, P, P, c, None, 0, None)
+    return s, rec.recorder_launches().decode().split()
+"""
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("recorder") / "hip_recorder.so")
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", so, os.path.join(HERE, "hip_recorder.c")], check=True)
+
+    def go(code):
+        env = dict(os.environ, LD_PRELOAD=":".join([so] + os.environ.get("LD_PRELOAD", "").split(":")).rstrip(":"))
+        r = subprocess.run([sys.executable, "-c", PRELUDE % (ROOT, so) + code], env=env, capture_output=True, text=True)
+        assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
+        return r.stdout
+
+    return go
+
+
+def test_a_remembered_pick_is_for_its_alpha_and_activation(run):
+    """conv_patch_kernel has no alpha and no GELU: after a call that it serves, the same sizes with another alpha or activation run on
+    another kernel, as they do alone, and the first call runs on it again."""
+    run("""
+d = lambda alpha, act: b.conv_desc(8, 56, 56, 64, 64, 3, 3, 1, 1, alpha=alpha, act=act)
+for turn in range(2):
+    for alpha, act, patch in ((1.0, "relu", True), (0.5, "relu", False), (1.0, "relu", True), (1.0, "gelu", False), (0.5, "none", False), (1.0, "none", True)):
+        s, kernels = conv(d(alpha, act))
+        assert s == 0 and len(kernels) == 1, (s, kernels)
+        assert ("conv_patch_kernel" in kernels[0]) == patch, (turn, alpha, act, kernels)
+""")
