@@ -464,7 +464,10 @@ struct B2bInstance {
   // Relative time per unit of tile work of this kernel family on the convolution pairs of Section 4.1.2, as measured
   // (0 = 1.0: the weights-resident kernels); read by the built-in pick rule only, bolt_tune measures.
   float prior;
-  bool any_n1;  // the second width costs what the problem has, not what was compiled: never too wide
+  // A family with a rule of its own for where the built-in pick takes it (null: the common cost model, which the prior above is
+  // for).  Its two widths are never too wide: it is tight wherever it can run, and the other instances' legality does not
+  // depend on it.
+  bool (*gains)(const B2bParams&, bool residual);
 };
 
 template <typename KernT>

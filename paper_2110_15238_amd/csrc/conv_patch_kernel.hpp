@@ -120,6 +120,26 @@ struct ConvPatchTraits {
   }
   static bool supports_single(const FpropParams& f) { return supports(from_single(f)); }
   static int lds_bytes_single(const FpropParams&) { return lds_bytes_n(0); }
+  // Where the pick rule takes a pair: where the pixels fill the rounds of units that they take.  A unit that an image does not
+  // fill costs as much as a full one: images of one column fill an eighth of every unit, of one pixel a 32nd, and without this
+  // rule took up to 14 times the tiled kernels' time (1x1 images, 100000 of them, 3x3 64 -> 64 -> 256: 23.7 -> 330 us).  Up to
+  // two rounds the fill of the tiled kernels' own tiles outweighs it (1601 problems: 0.56 to 1.13 of their time, mean 0.8).  Beyond,
+  // a round takes 0.9 to 6.4 us, and the tiled kernels 0.9 to 12 for the 32768 pixels of a full one: the bounds below are
+  // where the two meet, by what weighs in them (8 to 64 columns: one chunk; a residual of more than 128; 72 products of
+  // 32 x 32 x 16 in op0).  Over 5132 problems (images of 1 x 1 to 11 x 24, 1500 to 130000 pixels, with and without a residual)
+  // the choice takes 1.01 times the faster of the two.
+  static bool gains(const B2bParams& p, bool residual) {
+    const ConvPatchParams q = plan(p);
+    const int rounds = (q.units + MOST_WGS * NW - 1) / (MOST_WGS * NW);
+    if (rounds <= 2) return true;
+    const bool window = RS == 3 && ST == 1;
+    const double least = p.N1 <= 64            ? (window && p.N0 <= 32 ? 0.48 : 0.70)
+                         : window && p.cg.C > 48 ? 0.60
+                         : p.N1 <= 128         ? 0.35
+                         : residual            ? 0.70
+                                               : 0.40;
+    return p.M >= least * (rounds == 3 ? 0.8 : 1.0) * rounds * (MOST_WGS * NW * TP * TQ);
+  }
   // Pick rule, us: the fill with the first unit, then a round per unit and wave (from 28 problems, 1 to 7 rounds)
   static double estimate(const FpropParams& f) {
     const int rounds = (plan(from_single(f)).units + MOST_WGS * NW - 1) / (MOST_WGS * NW);
@@ -569,7 +589,7 @@ hipError_t launch_conv_patch_single(const FpropParams& f, hipStream_t stream) {
   {                                                                                                            \
     "b2bpatch_c" #CP "_n" #N0T "_r" #RS "_st" #ST, 0, 128, CP, 4, 1, N0T, 256, 1, 0, 256, 1, nullptr,            \
         &bolt::launch_conv_patch<CP, N0T, RS, ST, true>, &bolt::ConvPatchTraits<CP, N0T, RS, ST, true>::supports,            \
-        &bolt::ConvPatchTraits<CP, N0T, RS, ST, true>::lds_bytes, true, 0.25f, true                                    \
+        &bolt::ConvPatchTraits<CP, N0T, RS, ST, true>::lds_bytes, true, 0.f, &bolt::ConvPatchTraits<CP, N0T, RS, ST, true>::gains  \
   }
 
 }  // namespace bolt
