@@ -379,7 +379,7 @@ static bool fprop_supports(const FpropInstance& in, const FpropProblem& pr) {
   }
   // an NCHW output: only the instances with that store, and they have no other; no residual form
   if ((pr.p.y_nchw != 0) != in.nchw_out) return false;
-  if ((in.nchw_out || in.no_residual) && pr.residual) return false;
+  if (in.nchw_out && pr.residual) return false;
   if (in.wmode != pr.wmode) return false;
   if (in.xmode != pr.xmode) return false;
   if (in.kn_dma && (int64_t)pr.p.K * pr.p.ldw * 2 >= (1ll << 31)) return false;
@@ -429,7 +429,7 @@ static int fprop_heuristic(const std::vector<FpropInstance>& tab, const FpropPro
   for (int i = 0; i < (int)tab.size(); ++i) {
     const FpropInstance& in = tab[i];
     if (!fprop_supports(in, pr) || (in.worth_trying && !in.worth_trying(pr.p))) continue;
-    if (need_split_k && !fprop_can_split_k(in)) continue;
+    if ((need_split_k && !fprop_can_split_k(in)) || (pr.residual && in.plain_pick)) continue;
     const FpropParams& p = pr.p;
     if (in.estimate) {  // a family with a cost model of its own, in the same microseconds (the first-layer strips: always the lowest)
       const double cost = in.estimate(p);

@@ -110,10 +110,10 @@ struct ConvPatchTraits {
     return g.C <= CP && p.N0 <= N0T && p.N1 <= 256 && lds_bytes_n(p.N1) <= 160 * 1024;
   }
   static int lds_bytes(const B2bParams& p) { return lds_bytes_n(p.N1); }
-  // the single op: its epilogue is op0's
+  // the single op: its epilogue is op0's, and so is its residual
   static B2bParams from_single(const FpropParams& f) {
     B2bParams p{};
-    p.X = f.X; p.W0 = f.W; p.b0 = f.bias; p.b0_on = f.bias_on; p.Y = f.Y;
+    p.X = f.X; p.W0 = f.W; p.b0 = f.bias; p.b0_on = f.bias_on; p.Y = f.Y; p.res = f.res; p.ldr = f.ldr; p.gamma = f.gamma;
     p.M = f.M; p.N0 = p.N1 = f.N; p.K0 = f.K; p.ldw0 = f.ldw; p.ldy = f.ldy;
     p.alpha0 = f.alpha; p.beta0 = f.beta; p.act0 = f.act; p.alpha1 = 1.f; p.cg = f.cg;
     return p;
@@ -322,48 +322,57 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const ConvPatchParam
     if (k + D < KS) read_x(xs, k + D);
   };
   const unsigned lo0 = p.act0 == ACT_RELU ? 0u : 0x7e007e00u, lo1 = p.act1 == ACT_RELU ? 0u : 0x7e007e00u;
+  constexpr bool RES1 = RES && PAIR, RES0 = RES && !PAIR;  // the op that the residual goes to
+  auto stage_at = [&](int row, int chunk) { return out + row * NC + ((chunk ^ ((row >> 1) & 7)) << 3); };
   half8 d[FN0 * 2];
   auto make_d = [&]() {  // the hand-over: op0's output as op1's operand
 #pragma unroll
     for (int a = 0; a < FN0; ++a)
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
+      for (int t = 0; t < 2; ++t) {
+        half8 rs = {0, 0, 0, 0, 0, 0, 0, 0};
+        if constexpr (RES0) rs = *(const half8*)stage_at(l32, a * 4 + t * 2 + g);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const half2v v = pk_max(half2v{(half_t)acc0[a][t * 8 + 2 * e], (half_t)acc0[a][t * 8 + 2 * e + 1]}, lo0);
+          float v0 = acc0[a][t * 8 + 2 * e], v1 = acc0[a][t * 8 + 2 * e + 1];
+          if constexpr (RES0) {
+            v0 += p.gamma * (float)rs[2 * e];
+            v1 += p.gamma * (float)rs[2 * e + 1];
+          }
+          const half2v v = pk_max(half2v{(half_t)v0, (half_t)v1}, lo0);
           d[a * 2 + t][2 * e] = v[0];
           d[a * 2 + t][2 * e + 1] = v[1];
         }
+      }
   };
 
   // ---- 64 columns of op1 out, through this wave's piece of LDS (one wave's LDS accesses are served in order) ------------------------
   __amdgpu_buffer_rsrc_t yr, rr;
   unsigned y_at, r_at;     // this lane's 16 bytes of the unit's first output row: lanes 8j .. 8j + 7 take pixel j
-  int rows_out;            // output rows of the unit
-  auto set_out = [&](const Unit& t) {
+  int rows_out, rows_res;  // output rows of the unit
+  // 16 bytes per lane of an [M][ld] matrix at a unit: its descriptor, and this lane's offset in the first row
+  auto set_rows = [&](const Unit& t, const half_t* base, int ld, __amdgpu_buffer_rsrc_t& desc, unsigned& at, int& rows) {
     const int64_t m_at = ((int64_t)t.img * cg.P + t.p0) * cg.Q + t.q0;
-    const int64_t rem = ((int64_t)(p.M - m_at - 1) * p.ldy + p.N1) * 2;
-    yr = make_rsrc(p.Y + m_at * p.ldy, (unsigned)(rem < 0x7fffffff ? rem : 0x7fffffff));
-    rows_out = cg.P - t.p0;
+    const int64_t rem = ((int64_t)(p.M - m_at - 1) * ld + p.N1) * 2;
+    desc = make_rsrc(base + m_at * ld, (unsigned)(rem < 0x7fffffff ? rem : 0x7fffffff));
+    rows = cg.P - t.p0;
     const int j = lane >> 3;
-    const bool ok = (t.q0 + j < cg.Q) & (j < p.tq);
-    y_at = ok ? (unsigned)(j * p.ldy + (lane & 7) * 8) * 2u : kInvalidOffset;
-    if constexpr (RES) {
-      const int64_t remr = ((int64_t)(p.M - m_at - 1) * p.ldr + p.N1) * 2;
-      rr = make_rsrc(p.res + m_at * p.ldr, (unsigned)(remr < 0x7fffffff ? remr : 0x7fffffff));
-      r_at = ok ? (unsigned)(j * p.ldr + (lane & 7) * 8) * 2u : kInvalidOffset;
-    }
+    at = ((t.q0 + j < cg.Q) & (j < p.tq)) ? (unsigned)(j * ld + (lane & 7) * 8) * 2u : kInvalidOffset;
   };
-  auto row_offset = [&](int i, int c, unsigned at, int ld) {
-    const bool ok = (i < rows_out) & (c * NC + (lane & 7) * 8 < p.N1);
+  auto set_res = [&](const Unit& t) { set_rows(t, p.res, p.ldr, rr, r_at, rows_res); };
+  auto set_out = [&](const Unit& t) {
+    set_rows(t, p.Y, p.ldy, yr, y_at, rows_out);
+    if constexpr (RES1) set_res(t);
+  };
+  auto row_offset = [&](int i, int c, unsigned at, int ld, int rows) {
+    const bool ok = (i < rows) & (c * NC + (lane & 7) * 8 < p.N1);
     return ok ? at + (unsigned)(i * cg.Q * ld + c * NC) * 2u : kInvalidOffset;
   };
-  auto stage_at = [&](int row, int chunk) { return out + row * NC + ((chunk ^ ((row >> 1) & 7)) << 3); };
   uintx4 rv[RES ? 4 : 1];
   auto fetch_res = [&](int c) {
     if constexpr (RES) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) rv[i] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(rr, row_offset(i, c, r_at, p.ldr), 0, 0));
+      for (int i = 0; i < 4; ++i) rv[i] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(rr, row_offset(i, c, r_at, p.ldr, rows_res), 0, 0));
     }
   };
   auto stage_res = [&]() {
@@ -382,11 +391,11 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const ConvPatchParam
       return;
     }
     half8 rs = {0, 0, 0, 0, 0, 0, 0, 0}, o;
-    if constexpr (RES) rs = *slot;
+    if constexpr (RES1) rs = *slot;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       float v0 = acc1[a][t * 8 + 2 * e], v1 = acc1[a][t * 8 + 2 * e + 1];
-      if constexpr (RES) {
+      if constexpr (RES1) {
         v0 += p.gamma * (float)rs[2 * e];
         v1 += p.gamma * (float)rs[2 * e + 1];
       }
@@ -403,8 +412,8 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const ConvPatchParam
     for (int i = 0; i < 4; ++i) {
       const uintx4 v = *(const uintx4*)stage_at(i * 8 + (lane >> 3), lane & 7);
       // non-temporal, except where a cache line is shared by columns that are stored at different times
-      if (whole_lines) __builtin_amdgcn_raw_buffer_store_b128(v, yr, row_offset(i, c, y_at, p.ldy), 0, 2);
-      else __builtin_amdgcn_raw_buffer_store_b128(v, yr, row_offset(i, c, y_at, p.ldy), 0, 0);
+      if (whole_lines) __builtin_amdgcn_raw_buffer_store_b128(v, yr, row_offset(i, c, y_at, p.ldy, rows_out), 0, 2);
+      else __builtin_amdgcn_raw_buffer_store_b128(v, yr, row_offset(i, c, y_at, p.ldy, rows_out), 0, 0);
     }
     asm volatile("" ::: "memory");
   };
@@ -425,14 +434,15 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const ConvPatchParam
   };
 
   auto all_out = [&]() {  // op1 and output of the unit in d
-    fetch_res(0);
+    if constexpr (RES1) fetch_res(0);
     for (int c = 0; c < nch; ++c) {
-      stage_res();
+      if constexpr (RES1) stage_res();
       op1(c);
 #pragma unroll
       for (int q = 0; q < 4; ++q) octet_out(q);
       store_out(c);
-      if (c + 1 < nch) fetch_res(c + 1);
+      if constexpr (RES1)
+        if (c + 1 < nch) fetch_res(c + 1);
     }
   };
   auto wait_patch = [&]() {
@@ -462,7 +472,12 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const ConvPatchParam
     Unit cur = first;
     int un = u + step;
     Unit nxt = unit_at(un);
+    if constexpr (RES0) {
+      set_res(cur);
+      fetch_res(0);
+    }
     issue_patch(patch_of(nxt, un < u_end), patch0 + NW * T::PATCH / 2);
+    if constexpr (RES0) stage_res();
     make_d();
     __builtin_amdgcn_s_waitcnt(0x0F70);
     asm volatile("" ::: "memory");
@@ -475,7 +490,8 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const ConvPatchParam
       buf ^= 1;
       const half_t* const xs = patch0 + buf * (NW * T::PATCH / 2) + x_at;
       set_out(cur);
-      fetch_res(0);
+      if constexpr (RES0) set_res(nxt);  // (one unit ahead of the output: it goes to op0's results)
+      if constexpr (RES) fetch_res(0);
       op0_start(xs);
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
@@ -483,7 +499,7 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const ConvPatchParam
         auto segment = [&](auto with_out) {
           constexpr bool OUT_TOO = decltype(with_out)::value;
           if constexpr (OUT_TOO) {
-            stage_res();
+            if constexpr (RES1) stage_res();
             op1(s);
           }
           int q = 0, r = 0;
@@ -505,12 +521,14 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const ConvPatchParam
           __builtin_amdgcn_sched_barrier(0);
           if constexpr (OUT_TOO) {
             store_out(s);
-            if (s + 1 < nch) fetch_res(s + 1);
+            if constexpr (RES1)
+              if (s + 1 < nch) fetch_res(s + 1);
           }
         };
         if (s == 0 || s < nch) segment(std::true_type{});
         else segment(std::false_type{});
       }
+      if constexpr (RES0) stage_res();  // (the stored unit has left the place)
       make_d();
       wait_patch();
       cur = nxt;
@@ -560,8 +578,7 @@ hipError_t launch_conv_patch(const B2bParams& p, int /*grid*/, int lds_bytes, hi
   using T = ConvPatchTraits<CP, N0T, RS, ST, PAIR>;
   static LdsOptIn opt_in[2];
   auto kern = conv_patch_kernel<CP, N0T, RS, ST, PAIR, false>;
-  if constexpr (PAIR)
-    if (p.res) kern = conv_patch_kernel<CP, N0T, RS, ST, true, true>;
+  if (p.res) kern = conv_patch_kernel<CP, N0T, RS, ST, PAIR, true>;
   if (hipError_t e = opt_in[p.res ? 1 : 0].ensure((const void*)kern, 160 * 1024); e != hipSuccess) return e;
   const ConvPatchParams q = T::plan(p);
   // (every XCD, ids are dealt round-robin over 8, has the same number of waves for its eighth of the units)

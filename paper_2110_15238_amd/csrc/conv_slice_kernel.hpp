@@ -79,7 +79,7 @@ struct ConvSliceTraits {
   }
 };
 
-template <int BM, int BN, int CWS>
+template <int BM, int BN, int CWS, bool RES>
 __global__ __launch_bounds__(256, 1) void conv_slice_kernel(const ConvSliceParams p) {
 #if defined(__HIP_DEVICE_COMPILE__)
   using T = ConvSliceTraits<BM, BN, CWS>;
@@ -125,7 +125,7 @@ __global__ __launch_bounds__(256, 1) void conv_slice_kernel(const ConvSliceParam
   }
 
   // what the epilogue needs, now: a scalar load that misses takes as long as the whole of its arithmetic
-  EpilogueArgs ep{p.bias, p.bias_on, p.N, p.alpha, p.beta, p.act};
+  EpilogueArgs ep{p.bias, p.bias_on, p.N, p.alpha, p.beta, p.act, RES ? p.gamma : 0.f};
   half_t* y = p.Y;
   int ldy = p.ldy;
   asm volatile("" : "+s"(ep.alpha), "+s"(ep.beta), "+s"(ep.act), "+s"(ep.N), "+s"(y), "+s"(ldy));
@@ -259,6 +259,18 @@ __global__ __launch_bounds__(256, 1) void conv_slice_kernel(const ConvSliceParam
 #pragma unroll
   for (int ph = 0; ph < PH; ++ph) {
     floatx4 own[AP][FQ];
+    constexpr int BP = AP * 16, CPR = BP / 8, PASSES = FQ * 16 * CPR / 64;  // columns of a half, their chunks, instructions for a wave's rows
+    const int n_half = n0 + ph * BP;
+    // the residual's rows as the stores write them, on their way while the sums go round
+    half8 rv[RES ? PASSES : 1];
+    if constexpr (RES) {
+#pragma unroll
+      for (int i = 0; i < PASSES; ++i) {
+        const int m = m0 + wave * FQ * 16 + (i * 64 + lane) / CPR, n = n_half + (i * 64 + lane) % CPR * 8;
+        rv[i] = half8{0, 0, 0, 0, 0, 0, 0, 0};
+        if ((m < p.M) & (n < ep.N)) rv[i] = *(const half8*)(p.res + (int64_t)m * p.ldr + n);
+      }
+    }
     barrier_after_lds_writes();  // all waves are done with what the sums overwrite
 #pragma unroll
     for (int q = 0; q < NW; ++q) {
@@ -286,23 +298,29 @@ __global__ __launch_bounds__(256, 1) void conv_slice_kernel(const ConvSliceParam
     asm volatile("" ::: "memory");
     // ---- epilogue; the halves pass through this wave's part of the sums, so that stores write whole rows ----------------------------
     half_t* const out = reinterpret_cast<half_t*>(mine);
-    constexpr int BP = AP * 16, CPR = BP / 8;  // columns of a half, their chunks
-    const int n_half = n0 + ph * BP;
+    if constexpr (RES) {
+#pragma unroll
+      for (int i = 0; i < PASSES; ++i) {
+        const int row = (i * 64 + lane) / CPR, chunk = (i * 64 + lane) % CPR;
+        *(half8*)(out + row * BP + ((chunk ^ ctile_swizzle<CPR>(row)) << 3)) = rv[i];
+      }
+      asm volatile("" ::: "memory");
+    }
     auto finish = [&](auto slow) {
 #pragma unroll
       for (int a = 0; a < AP; ++a)
 #pragma unroll
         for (int b = 0; b < FQ; ++b) {
           const int n = a * 16 + g * 4, row = b * 16 + l16;
-          *(half4*)(out + row * BP + (((n >> 3) ^ ctile_swizzle<CPR>(row)) << 3) + (n & 4)) =
-              epilogue_quad4_values<decltype(slow)::value, false>(own[a][b], bias[ph * AP + a], ep, half4{0, 0, 0, 0});
+          half4* const slot = (half4*)(out + row * BP + (((n >> 3) ^ ctile_swizzle<CPR>(row)) << 3) + (n & 4));
+          *slot = epilogue_quad4_values<decltype(slow)::value, RES>(own[a][b], bias[ph * AP + a], ep, RES ? *slot : half4{0, 0, 0, 0});
         }
     };
     if (ep.act > ACT_RELU) finish(std::true_type{});
     else finish(std::false_type{});
     asm volatile("" ::: "memory");
 #pragma unroll
-    for (int i = 0; i < FQ * 16 * CPR / 64; ++i) {
+    for (int i = 0; i < PASSES; ++i) {
       const int row = (i * 64 + lane) / CPR, chunk = (i * 64 + lane) % CPR;
       const int m = m0 + wave * FQ * 16 + row, n = n_half + chunk * 8;
       if ((m < p.M) & (n < ep.N))
@@ -315,9 +333,9 @@ __global__ __launch_bounds__(256, 1) void conv_slice_kernel(const ConvSliceParam
 template <int BM, int BN, int CWS>
 hipError_t launch_conv_slice(const FpropParams& p, hipStream_t stream) {
   using T = ConvSliceTraits<BM, BN, CWS>;
-  static LdsOptIn opt_in;
-  auto kern = conv_slice_kernel<BM, BN, CWS>;
-  if (hipError_t e = opt_in.ensure((const void*)kern, 160 * 1024); e != hipSuccess) return e;
+  static LdsOptIn opt_in[2];
+  auto kern = p.res ? conv_slice_kernel<BM, BN, CWS, true> : conv_slice_kernel<BM, BN, CWS, false>;
+  if (hipError_t e = opt_in[p.res ? 1 : 0].ensure((const void*)kern, 160 * 1024); e != hipSuccess) return e;
   ConvSliceParams q{p};
   q.rcp_hw = 0xffffffffu / (unsigned)(p.cg.H * p.cg.Wi);
   q.rcp_w = 0xffffffffu / (unsigned)p.cg.Wi;

@@ -219,7 +219,7 @@ struct FpropInstance {
   // Where the pick rule and bolt_tune consider this instance (null: wherever it is legal).  Not a matter of legality: a
   // configuration that was tuned for one number of rows keeps working at any other.
   bool (*worth_trying)(const FpropParams&);
-  bool no_residual;  // the kernel has no form with a residual matrix
+  bool plain_pick;  // the pick rule's cost was measured without a residual: a call with one runs this kernel if its config says so
 };
 
 template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int XMODE, int WMODE>

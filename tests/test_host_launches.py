@@ -55,3 +55,21 @@ for turn in range(2):
         assert s == 0 and len(kernels) == 1, (s, kernels)
         assert ("conv_patch_kernel" in kernels[0]) == patch, (turn, alpha, act, kernels)
 """)
+
+
+@pytest.mark.parametrize("shape", [(2, 56, 56, 64, 64), (2, 28, 28, 32, 40), (2, 28, 28, 128, 128), (2, 14, 14, 256, 256), (2, 7, 7, 512, 512)])
+def test_every_instance_of_a_plain_3x3_takes_a_residual(run, shape):
+    """A config that bolt_tune found for the plain op (any legal instance) is valid with a residual, on that instance; without a config
+    the call keeps to the kernels whose cost with a residual the pick rule knows."""
+    run("""
+d, ids = b.conv_desc(%d, %d, %d, %d, %d, 3, 3, 1, 1), []
+for kid in range(b.bolt_num_instances(b.OP_CONV2D)):
+    if not b.bolt_instance_supports(b.OP_CONV2D, kid, d): continue
+    plain, res = conv(d, dict(kernel_id=kid)), conv(d, dict(kernel_id=kid), True)
+    assert plain[0] == 0 and res[0] == 0 and len(res[1]) == 1, (kid, plain, res)
+    assert plain[1][0].split("Li")[0] == res[1][0].split("Li")[0], (plain, res)
+    ids += [kid] * ("conv_slice" in plain[1][0] or "conv_patch" in plain[1][0])
+assert ids
+s, kernels = conv(d, res=True)
+assert s == 0 and not any(k in kernels[0] for k in ("conv_slice", "conv_patch")), kernels
+""" % shape)
