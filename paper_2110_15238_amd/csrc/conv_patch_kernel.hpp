@@ -140,9 +140,12 @@ struct ConvPatchTraits {
                                                : 0.40;
     return p.M >= least * (rounds == 3 ? 0.8 : 1.0) * rounds * (MOST_WGS * NW * TP * TQ);
   }
-  // Pick rule, us: the fill with the first unit, then a round per unit and wave (from 28 problems, 1 to 7 rounds)
+  // Pick rule, us: the fill with the first unit, then a round per unit and wave (from 28 problems, 1 to 7 rounds).  A single round
+  // takes 3.7 or 4.9 too, but stands against the kernels for small problems, whose estimates are up to 1.1 us too high here: of 83
+  // problems that the two numbers took from them, 32 ran 1.02 to 1.14 times as long (550 pixels, 8 -> 32: 3.6 -> 4.1 us).
   static double estimate(const FpropParams& f) {
     const int rounds = (plan(from_single(f)).units + MOST_WGS * NW - 1) / (MOST_WGS * NW);
+    if (rounds == 1) return CP > 32 ? 5.2 : 4.6;
     return CP > 32 ? 4.9 + 2.3 * (rounds - 1) : 3.7 + 1.5 * (rounds - 1);
   }
 };

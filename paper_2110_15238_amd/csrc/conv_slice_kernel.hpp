@@ -72,10 +72,12 @@ struct ConvSliceTraits {
     return g.C == C && g.R == 3 && g.S == 3 && g.stride_h == 1 && g.stride_w == 1 && g.pad_h == 1 && g.pad_w == 1 &&
            lds_bytes(p) <= 160 * 1024;
   }
-  // Pick rule, us: a round of tiles is fill, sum and launch of 2.7, then 1.9 per 64 x 64 outputs and 128 channels (hot, from 18 problems)
+  // Pick rule, us: a round of tiles is fill, sum and launch of 2.7, then 1.9 per 64 x 64 outputs and 128 channels (hot, from 18 problems).
+  // (One round: 0.4 more, what the kernels for small problems, against which it stands, are estimated too high; 480 pixels,
+  // 128 -> 152: 5.5 us there, 5.9 here.)
   static double estimate(const FpropParams& p) {
-    const int tiles = (p.M + BM - 1) / BM * ((p.N + BN - 1) / BN);
-    return 0.6 + (tiles + 255) / 256 * (2.7 + 1.9 * (BM / 64 * (BN / 64) * CWS) + 2.0 * (PH - 1));
+    const int rounds = ((p.M + BM - 1) / BM * ((p.N + BN - 1) / BN) + 255) / 256;
+    return (rounds == 1 ? 1.0 : 0.6) + rounds * (2.7 + 1.9 * (BM / 64 * (BN / 64) * CWS) + 2.0 * (PH - 1));
   }
 };
 
