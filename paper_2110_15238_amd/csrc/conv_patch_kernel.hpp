@@ -102,9 +102,12 @@ struct ConvPatchTraits {
     }
     return best;
   }
+  // What the overlapped loop computes: ReLU or nothing, the products as they are.  Everything else runs on the general form of the
+  // kernel if a config says so; the pick rule's costs are those of the plain one.
+  static bool plain(const B2bParams& p) { return p.act0 <= ACT_RELU && p.act1 <= ACT_RELU && p.alpha0 == 1.f && p.alpha1 == 1.f; }
+  static bool plain_single(const FpropParams& f) { return plain(from_single(f)); }
   static bool supports(const B2bParams& p) {
     const ConvGeom& g = p.cg;
-    if (p.act0 > ACT_RELU || p.act1 > ACT_RELU || p.alpha0 != 1.f || p.alpha1 != 1.f) return false;
     if (g.R != RS || g.S != RS || g.stride_h != g.stride_w || g.pad_h > 2 || g.pad_w > 2 || g.C % 8 != 0) return false;
     if (RS == 3 ? g.stride_h != ST : g.stride_h > 2) return false;
     return g.C <= CP && p.N0 <= N0T && p.N1 <= 256 && lds_bytes_n(p.N1) <= 160 * 1024;
@@ -129,6 +132,7 @@ struct ConvPatchTraits {
   // 32 x 32 x 16 in op0).  Over 5132 problems (images of 1 x 1 to 11 x 24, 1500 to 130000 pixels, with and without a residual)
   // the choice takes 1.01 times the faster of the two.
   static bool gains(const B2bParams& p, bool residual) {
+    if (!plain(p)) return false;
     const ConvPatchParams q = plan(p);
     const int rounds = (q.units + MOST_WGS * NW - 1) / (MOST_WGS * NW);
     if (rounds <= 2) return true;
@@ -159,7 +163,8 @@ __device__ __forceinline__ half2v pk_max(half2v v, unsigned lo) {
 }
 #endif
 
-template <int CP, int N0T, int RS, int ST, bool PAIR, bool RES>
+// GEN: any activation and any alpha, the epilogues in single precision and one unit after the other.
+template <int CP, int N0T, int RS, int ST, bool PAIR, bool RES, bool GEN>
 __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const ConvPatchParams p) {
 #if defined(__HIP_DEVICE_COMPILE__)
   using T = ConvPatchTraits<CP, N0T, RS, ST, PAIR>;
@@ -300,6 +305,11 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const ConvPatchParam
   floatx16 acc0[FN0];
   half8 xq[D];
   auto set_bias = [&](floatx16& acc, const float* bias) {  // 32 columns: the accumulators start from the bias
+    if constexpr (GEN) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+      return;
+    }
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -327,6 +337,27 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const ConvPatchParam
   const unsigned lo0 = p.act0 == ACT_RELU ? 0u : 0x7e007e00u, lo1 = p.act1 == ACT_RELU ? 0u : 0x7e007e00u;
   constexpr bool RES1 = RES && PAIR, RES0 = RES && !PAIR;  // the op that the residual goes to
   auto stage_at = [&](int row, int chunk) { return out + row * NC + ((chunk ^ ((row >> 1) & 7)) << 3); };
+  // act(alpha acc + beta bias + gamma res) of accumulators 8t .. 8t + 7
+  auto general = [&](const floatx16& acc, int t, const float* bias, half8 rs, float gamma, float alpha, int act) {
+    half8 o;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const floatx4 b = *(const floatx4*)(bias + t * 16 + g * 8 + h * 4);
+      floatx4 v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = alpha * acc[t * 8 + h * 4 + e] + b[e] + gamma * (float)rs[h * 4 + e];
+      if (act > ACT_RELU) {
+        v = apply_act_slow4_inline(v, act);
+      } else {
+        const float lo = relu_bound(act);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = at_least(v[e], lo);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[h * 4 + e] = (half_t)v[e];
+    }
+    return o;
+  };
   half8 d[FN0 * 2];
   auto make_d = [&]() {  // the hand-over: op0's output as op1's operand
 #pragma unroll
@@ -335,6 +366,10 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const ConvPatchParam
       for (int t = 0; t < 2; ++t) {
         half8 rs = {0, 0, 0, 0, 0, 0, 0, 0};
         if constexpr (RES0) rs = *(const half8*)stage_at(l32, a * 4 + t * 2 + g);
+        if constexpr (GEN) {
+          d[a * 2 + t] = general(acc0[a], t, bias0 + a * 32, rs, RES0 ? p.gamma : 0.f, p.alpha0, p.act0);
+          continue;
+        }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           float v0 = acc0[a][t * 8 + 2 * e], v1 = acc0[a][t * 8 + 2 * e + 1];
@@ -386,7 +421,7 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const ConvPatchParam
     }
   };
   floatx16 acc1[2];
-  auto octet_out = [&](int i) {  // octet i = 0 .. 3 of this lane's 32 values of the 64 columns
+  auto octet_out = [&](int i, int c) {  // octet i = 0 .. 3 of this lane's 32 values of the 64 columns
     const int a = i >> 1, t = i & 1;
     half8* const slot = (half8*)stage_at(l32, a * 4 + t * 2 + g);
     if constexpr (!PAIR) {
@@ -395,6 +430,10 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const ConvPatchParam
     }
     half8 rs = {0, 0, 0, 0, 0, 0, 0, 0}, o;
     if constexpr (RES1) rs = *slot;
+    if constexpr (GEN) {
+      *slot = general(acc1[a], t, bias1 + c * NC + a * 32, rs, RES1 ? p.gamma : 0.f, p.alpha1, p.act1);
+      return;
+    }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       float v0 = acc1[a][t * 8 + 2 * e], v1 = acc1[a][t * 8 + 2 * e + 1];
@@ -442,7 +481,7 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const ConvPatchParam
       if constexpr (RES1) stage_res();
       op1(c);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) octet_out(q);
+      for (int q = 0; q < 4; ++q) octet_out(q, c);
       store_out(c);
       if constexpr (RES1)
         if (c + 1 < nch) fetch_res(c + 1);
@@ -457,7 +496,7 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const ConvPatchParam
     asm volatile("" ::: "memory");
   };
 
-  if constexpr (T::OVERLAP) {
+  if constexpr (T::OVERLAP && !GEN) {
     // ---- first unit: the weights go to registers on the way
 #pragma unroll
     for (int k = 0; k < D; ++k) read_wf(k);
@@ -517,7 +556,7 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const ConvPatchParam
             if constexpr (OUT_TOO) {  // (two products of op0 and more stand between those of op1 and the use of their results)
               if (k > k0) {
 #pragma unroll
-                for (; q < ((k - k0) * 4) / (k1 - k0 - 1); ++q) octet_out(q);
+                for (; q < ((k - k0) * 4) / (k1 - k0 - 1); ++q) octet_out(q, s);
               }
             }
           }
@@ -564,6 +603,11 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const ConvPatchParam
       const int un = u + step;
       const Unit nxt = unit_at(un);
       issue_patch(patch_of(nxt, un < u_end), patch0);
+      if constexpr (RES0) {
+        set_res(cur);
+        fetch_res(0);
+        stage_res();
+      }
       make_d();
       set_out(cur);
       all_out();
@@ -579,10 +623,11 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const ConvPatchParam
 template <int CP, int N0T, int RS, int ST, bool PAIR>
 hipError_t launch_conv_patch(const B2bParams& p, int /*grid*/, int lds_bytes, hipStream_t stream) {
   using T = ConvPatchTraits<CP, N0T, RS, ST, PAIR>;
-  static LdsOptIn opt_in[2];
-  auto kern = conv_patch_kernel<CP, N0T, RS, ST, PAIR, false>;
-  if (p.res) kern = conv_patch_kernel<CP, N0T, RS, ST, PAIR, true>;
-  if (hipError_t e = opt_in[p.res ? 1 : 0].ensure((const void*)kern, 160 * 1024); e != hipSuccess) return e;
+  static LdsOptIn opt_in[4];
+  const bool res = p.res != nullptr, gen = !T::plain(p);
+  auto kern = gen ? (res ? conv_patch_kernel<CP, N0T, RS, ST, PAIR, true, true> : conv_patch_kernel<CP, N0T, RS, ST, PAIR, false, true>)
+                  : (res ? conv_patch_kernel<CP, N0T, RS, ST, PAIR, true, false> : conv_patch_kernel<CP, N0T, RS, ST, PAIR, false, false>);
+  if (hipError_t e = opt_in[gen * 2 + res].ensure((const void*)kern, 160 * 1024); e != hipSuccess) return e;
   const ConvPatchParams q = T::plan(p);
   // (every XCD, ids are dealt round-robin over 8, has the same number of waves for its eighth of the units)
   int grid = std::min((q.units + T::NW - 1) / T::NW, T::MOST_WGS);
@@ -602,7 +647,7 @@ hipError_t launch_conv_patch_single(const FpropParams& f, hipStream_t stream) {
     "patch_c" #CP "_r" #RS "_st" #ST, 128, 64, 64, 4, 1, 1, 0, 2, 0, &bolt::launch_conv_patch_single<CP, RS, ST>, \
         &bolt::ConvPatchTraits<CP, 64, RS, ST, false>::supports_single,                                          \
         &bolt::ConvPatchTraits<CP, 64, RS, ST, false>::lds_bytes_single, 0, 0, true, false, false,               \
-        &bolt::ConvPatchTraits<CP, 64, RS, ST, false>::estimate, nullptr, true                              \
+        &bolt::ConvPatchTraits<CP, 64, RS, ST, false>::estimate, &bolt::ConvPatchTraits<CP, 64, RS, ST, false>::plain_single, true \
   }
 
 #define BOLT_CONV_PATCH_PAIR_INSTANCE(CP, N0T, RS, ST)                                                          \

@@ -842,6 +842,53 @@ def test_conv_patch_pairs_and_single_op_integer_bit_exact(bolt, case):
         assert ran >= 3
 
 
+@pytest.mark.parametrize("case", [c for c in PATCH_EDGES if c[0] * c[1] * c[2] > 5000 or c[0] in (3, 5)] + [(2, 17, 19, 64, 64, 3, 2, 1, 256), (1, 5, 9, 128, 64, 1, 1, 0, 256)])
+def test_conv_patch_other_activations_and_alpha(bolt, case):
+    """What conv_patch_kernel's overlapped loop does not compute runs on its general form: a config that was tuned with ReLU is valid
+    with any activation and alpha, alone, as a pair and with a residual."""
+    N, H, W, Cc, K0, R, stride, pad, K1 = case
+    x, w0 = wl.uniform_fp16(513, 0, (N, H, W, Cc), -1, 1), wl.normal_fp16(513, 1, (K0, R, R, Cc), (2.0 / (R * R * Cc)) ** 0.5)
+    b0, w1, b1 = wl.uniform_fp16(513, 2, (K0,), -1, 1), wl.normal_fp16(513, 3, (K1, 1, 1, K0), (2.0 / K0) ** 0.5), wl.uniform_fp16(513, 4, (K1,), -1, 1)
+    P, Q = bolt.conv_out_hw(bolt.conv_desc(N, H, W, Cc, K0, R, R, stride, pad))
+    res0, res1 = wl.uniform_fp16(513, 5, (N, P, Q, K0), -2, 2), wl.uniform_fp16(513, 6, (N, P, Q, K1), -2, 2)
+    xd, w0d, b0d, w1d, b1d = (dev(t) for t in (x, w0, b0, w1, b1))
+    pairs = singles = 0
+    for act0, alpha0, act1, alpha1 in (("gelu", 1.0, "relu", 1.0), ("relu", 1.0, "softplus", 1.0), ("none", 0.5, "hardswish", -2.0), ("relu", -0.75, "none", 1.0)):
+        c0 = bolt.conv_desc(N, H, W, Cc, K0, R, R, stride, pad, act=act0, alpha=alpha0)
+        c1 = bolt.conv_desc(N, P, Q, K0, K1, 1, 1, act=act1, alpha=alpha1, beta=0.5)
+        plain0, plain1 = bolt.conv_desc(N, H, W, Cc, K0, R, R, stride, pad), bolt.conv_desc(N, P, Q, K0, K1, 1, 1)
+        d0 = ref.conv2d_nhwc(x, w0, b0, stride=stride, pad=pad, alpha=alpha0, act=act0)
+        want = ref.conv2d_nhwc(d0, w1, b1, alpha=alpha1, beta=0.5, act=act1)
+        want_res = ref.conv2d_nhwc_residual(d0, w1, b1, res1, alpha=alpha1, beta=0.5, gamma=-0.5, act=act1)
+        for kid in range(bolt.bolt_num_instances(bolt.OP_B2B_CONV)):
+            cfg = bolt.bolt_instance_config(bolt.OP_B2B_CONV, kid)
+            if cfg.tile_n != 256 or cfg.tile_m != 128 or cfg.stages != 1 or not bolt.bolt_instance_supports(bolt.OP_B2B_CONV, kid, plain0, plain1):
+                continue
+            _say("conv patch pair %s instance %d %s %g %s %g" % (case, kid, act0, alpha0, act1, alpha1))
+            y, r = torch.full((N, P, Q, K1), float("nan"), dtype=torch.float16, device="cuda"), dev(res1)
+            bolt.bolt_b2b_conv(c0, c1, xd, w0d, b0d, w1d, b1d, y, {"kernel_id": kid})
+            bolt.bolt_b2b_conv_residual(c0, c1, xd, w0d, b0d, w1d, b1d, r, r, -0.5, {"kernel_id": kid})
+            torch.cuda.synchronize()
+            assert_close(host(y), want, "conv patch pair %s instance %d %s %s" % (case, kid, act0, act1))
+            assert_close(host(r), want_res, "conv patch pair %s residual, instance %d %s %s" % (case, kid, act0, act1))
+            pairs += 1
+        if (act0, alpha0) == ("relu", 1.0) or R == 1 or stride == 2:
+            continue
+        want = ref.conv2d_nhwc_residual(x, w0, b0, res0, stride=stride, pad=pad, alpha=alpha0, gamma=-0.5, act=act0)
+        for kid in range(bolt.bolt_num_instances(bolt.OP_CONV2D)):
+            if not bolt.bolt_instance_supports(bolt.OP_CONV2D, kid, plain0) or bolt.bolt_instance_supports(bolt.OP_CONV2D, kid, bolt.conv_desc(N, H, W, Cc, 72, 3, 3, 1, pad)):
+                continue  # (the family that has a limit of 64 output channels)
+            _say("conv patch %s instance %d %s %g" % (case, kid, act0, alpha0))
+            y, r = torch.full((N, P, Q, K0), float("nan"), dtype=torch.float16, device="cuda"), dev(res0)
+            bolt.bolt_conv2d_fprop_nhwc(c0, xd, w0d, b0d, y, {"kernel_id": kid})
+            bolt.bolt_conv2d_fprop_nhwc_residual(c0, xd, w0d, b0d, r, r, -0.5, {"kernel_id": kid})
+            torch.cuda.synchronize()
+            assert_close(host(y), d0, "conv patch %s instance %d %s" % (case, kid, act0))
+            assert_close(host(r), want, "conv patch %s residual, instance %d %s" % (case, kid, act0))
+            singles += 1
+    assert pairs >= 4 and (singles >= 3 or R == 1 or stride == 2)
+
+
 @pytest.mark.parametrize("channels", (24, 64))
 def test_one_convolution_with_changing_alpha_and_activation(bolt, channels):
     """Calls without a config on one thread that differ in alpha and the activation only: a remembered pick is not for all of them."""

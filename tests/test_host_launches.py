@@ -73,3 +73,32 @@ assert ids
 s, kernels = conv(d, res=True)
 assert s == 0 and not any(k in kernels[0] for k in ("conv_slice", "conv_patch")), kernels
 """ % shape)
+
+
+def test_a_pair_or_3x3_tuned_with_relu_takes_any_activation_and_alpha(run):
+    """Legality is a matter of sizes: every instance that runs a problem with ReLU and alpha = 1 runs it with the others, by its config;
+    without one such a call stays off conv_patch_kernel, whose costs the pick rule knows for the plain form."""
+    run("""
+def pair(c0, c1, cfg=None):
+    c = None if cfg is None else C.byref(b.BoltConfig.from_dict(cfg))
+    return lib.bolt_b2b_conv(C.byref(c0), C.byref(c1), P, P, P, P, P, P, c, None, 0, None), rec.recorder_launches().decode().split()
+others = (("gelu", 1.0), ("relu", 0.5), ("softplus", -1.0), ("hardswish", 1.0), ("none", 2.0))
+d = lambda act="relu", alpha=1.0: b.conv_desc(8, 56, 56, 64, 64, 3, 3, 1, 1, alpha=alpha, act=act)
+e = lambda act="relu", alpha=1.0: b.conv_desc(8, 56, 56, 64, 256, 1, 1, alpha=alpha, act=act)
+ran = 0
+for kid in range(b.bolt_num_instances(b.OP_CONV2D)):
+    if b.bolt_instance_supports(b.OP_CONV2D, kid, d()):
+        for o in others:
+            assert conv(d(*o), dict(kernel_id=kid))[0] == 0, (kid, o)
+            ran += 1
+for kid in range(b.bolt_num_instances(b.OP_B2B_CONV)):
+    if b.bolt_instance_supports(b.OP_B2B_CONV, kid, d(), e()):
+        for o in others:
+            assert pair(d(*o), e(), dict(kernel_id=kid))[0] == 0 and pair(d(), e(*o), dict(kernel_id=kid))[0] == 0, (kid, o)
+            ran += 1
+assert ran >= 30
+for o in others:
+    for s, kernels in (conv(d(*o)), pair(d(*o), e()), pair(d(), e(*o))):
+        assert s == 0 and "conv_patch" not in kernels[0], (o, kernels)
+assert "conv_patch" in conv(d())[1][0] and "conv_patch" in pair(d(), e())[1][0]
+""")
