@@ -989,8 +989,11 @@ static bolt_status tune_candidates(std::vector<Candidate>& cands, RunF&& run, hi
   bolt_status status = evict.buf ? BOLT_OK : BOLT_ERR_LAUNCH;
   int n_ok = 0;
   {
-    // milliseconds of one repetition without its launches
+    // Candidates are compared by the milliseconds of a whole repetition.  What of it is the launches' is needed where a share of
+    // their time counts, and then roughly: the reads by themselves do not take what they take between launches, so two launches
+    // are never taken for less than the 4 us that the shortest need.
     float base = 0.f;
+    auto own = [&](float ms) { return std::max(ms - base, 0.004f); };
     auto time_evict = [&] {
       float ms = 0.f;
       bolt_status s = time_launches([&] { return evict.launch(stream); }, 1, 4, stream, e0, e1, &ms);
@@ -1005,8 +1008,11 @@ static bolt_status tune_candidates(std::vector<Candidate>& cands, RunF&& run, hi
         if (r == BOLT_OK) r = run(c);
         return r == BOLT_OK ? run(c) : r;
       }, 0, reps, stream, e0, e1, ms);
-      *ms = std::max(*ms - base, 0.f) / 2;
       return s;
+    };
+    auto log_candidate = [&](int pass, const Candidate& c) {
+      if (tune_log_enabled())
+        std::fprintf(stderr, "[bolt_tune] pass%d id %d swizzle %d split_k %d: %.4f ms\n", pass, c.id, c.swizzle, c.split_k, (c.ms - base) / 2);
     };
     for (int i = 0; i < 2 && status == BOLT_OK; ++i) status = time_evict();
     // pass 1: a short timing of every candidate, and once more of those within 30 % of the first
@@ -1016,14 +1022,13 @@ static bolt_status tune_candidates(std::vector<Candidate>& cands, RunF&& run, hi
       bolt_status s = time_one(c, 1, 3, &c.ms);
       if (s == BOLT_ERR_LAUNCH) { status = s; break; }
       if (s != BOLT_OK) { c.ms = -1.f; continue; }
-      if (tune_log_enabled())
-        std::fprintf(stderr, "[bolt_tune] pass1 id %d swizzle %d split_k %d: %.4f ms\n", c.id, c.swizzle, c.split_k, c.ms);
+      log_candidate(1, c);
       first = n_ok++ ? std::min(first, c.ms) : c.ms;
     }
     if (status == BOLT_OK && n_ok == 0) status = BOLT_ERR_UNSUPPORTED;
     std::vector<Candidate*> order;
     for (auto& c : cands)
-      if (status == BOLT_OK && c.ms >= 0.f && c.ms <= 1.3f * first) {
+      if (status == BOLT_OK && c.ms >= 0.f && c.ms <= first + 0.3f * own(first)) {
         float ms = 0.f;
         status = time_one(c, 0, 3, &ms);
         c.ms = std::min(c.ms, ms);
@@ -1031,7 +1036,7 @@ static bolt_status tune_candidates(std::vector<Candidate>& cands, RunF&& run, hi
       }
     if (status == BOLT_OK) {
       // Near-ties go to the XCD-aware tile order: the same time with fewer operand bytes crossing the fabric.
-      auto score = [](const Candidate* c) { return c->ms * (c->swizzle > 0 ? 0.985f : 1.f); };
+      auto score = [&](const Candidate* c) { return c->ms - (c->swizzle > 0 ? 0.015f * own(c->ms) : 0.f); };
       std::sort(order.begin(), order.end(), [&](Candidate* a, Candidate* b) { return score(a) < score(b); });
       // pass 2: the few fastest in turns, the median of the turns
       constexpr int kTurns = 3;
@@ -1043,8 +1048,7 @@ static bolt_status tune_candidates(std::vector<Candidate>& cands, RunF&& run, hi
       for (size_t i = 0; i < order.size(); ++i) {
         std::nth_element(&t[i * kTurns], &t[i * kTurns] + kTurns / 2, &t[i * kTurns] + kTurns);
         order[i]->ms = t[i * kTurns + kTurns / 2];
-        if (tune_log_enabled())
-          std::fprintf(stderr, "[bolt_tune] pass2 id %d swizzle %d split_k %d: %.4f ms\n", order[i]->id, order[i]->swizzle, order[i]->split_k, order[i]->ms);
+        log_candidate(2, *order[i]);
         if (!win || score(order[i]) < score(win)) win = order[i];
       }
       // the time that is reported: launches back to back

@@ -102,3 +102,18 @@ for o in others:
         assert s == 0 and "conv_patch" not in kernels[0], (o, kernels)
 assert "conv_patch" in conv(d())[1][0] and "conv_patch" in pair(d(), e())[1][0]
 """)
+
+
+@pytest.mark.parametrize("after_itself", (0.014, 0.020, 0.026, 0.040))
+def test_tuner_ranks_short_kernels_whatever_the_eviction_took(run, after_itself):
+    """bolt_tune times a candidate together with a kernel that evicts the caches.  What that kernel takes by itself, back to back, is not what
+    it takes between launches: if it takes longer, candidates of a few microseconds are still told apart."""
+    run("""
+cost("tune_evict", 0.020, %g); cost("conv_slice", 0.0030); cost("conv_halo", 0.0031); cost("", 0.0035)
+d, best = b.conv_desc(8, 14, 14, 256, 256, 3, 3, 1, 1), b.BoltConfig()
+ptrs = (C.c_void_p * 4)(P, P, P, P)
+assert lib.bolt_tune(b.OP_CONV2D, C.byref(d), None, ptrs, None, 0, None, C.byref(best), None, None) == 0
+rec.recorder_launches()
+s, kernels = conv(d, dict(kernel_id=best.kernel_id))
+assert s == 0 and "conv_slice" in kernels[0], kernels
+""" % after_itself)
