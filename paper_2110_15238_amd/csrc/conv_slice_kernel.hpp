@@ -113,11 +113,13 @@ __global__ __launch_bounds__(256, 1) void conv_slice_kernel(const ConvSliceParam
   const int m0 = tm * BM, n0 = tn * BN;
 
   char* const lds0 = reinterpret_cast<char*>(lds);
+  // this tile's rows of the weights; the whole matrix may be larger than a descriptor's 4 GiB
+  const int w_rows = p.N - n0 < BN ? p.N - n0 : BN;
+  const __amdgpu_buffer_rsrc_t wr = make_rsrc(p.W + (int64_t)n0 * p.ldw, (unsigned)(((w_rows - 1) * p.ldw + p.K) * 2));
   // ---- the weights of this column band into the L2, each workgroup of the XCD a share: in a network they come from memory, and
   // the ring below looks ahead for less than that takes.  One load touches 64 lines of 128 bytes; its data goes nowhere. ----------
   {
-    const unsigned bytes = (unsigned)((p.N - n0 < BN ? p.N - n0 : BN) * p.ldw * 2);
-    const __amdgpu_buffer_rsrc_t wr = make_rsrc(p.W + (int64_t)n0 * p.ldw, bytes);
+    const unsigned bytes = (unsigned)(w_rows * p.ldw * 2);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const unsigned at = (unsigned)(((i * cnt + pos) * T::NT + (int)threadIdx.x) * 128);
@@ -153,13 +155,11 @@ __global__ __launch_bounds__(256, 1) void conv_slice_kernel(const ConvSliceParam
 
   // ---- weights: a step is [output channel][32 input channels], XOR-swizzled; 16 rows per load instruction ------------------------
   half_t* const ws = reinterpret_cast<half_t*>(lds0 + xs + T::input_bytes(cg));
-  const unsigned w_bytes = (unsigned)(((p.N - n0 - 1) * p.ldw + p.K) * 2);
-  const __amdgpu_buffer_rsrc_t wr = make_rsrc(p.W + (int64_t)n0 * p.ldw, w_bytes);
   unsigned w_at[FN];
 #pragma unroll
   for (int a = 0; a < FN; ++a) {
     const int n = a * 16 + (lane >> 2), ch = (lane & 3) ^ dma_swizzle<32>(n);
-    w_at[a] = n0 + n < p.N ? (unsigned)(n * p.ldw + wave * T::CW + ch * 8) * 2u : kInvalidOffset;
+    w_at[a] = n < w_rows ? (unsigned)(n * p.ldw + wave * T::CW + ch * 8) * 2u : kInvalidOffset;
   }
   auto load_w = [&](int a, int t) {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, BOLT_LDS_PTR(ws + t % D * (T::W_BYTES / 2) + a * 512), 16, w_at[a],

@@ -953,6 +953,27 @@ def test_conv_slice_integer_bit_exact(bolt, shape, channels):
     assert ran >= 3 or (channels == 512 and W > 12)  # (three rows of 512 channels have to fit LDS beside the tile)
 
 
+@pytest.mark.parametrize("channels,K", [(128, 1864152), (512, 466056)])
+def test_conv_slice_weights_beyond_a_descriptor(bolt, channels, K):
+    """More than 4 GiB of weights: a tile's descriptor covers its own rows.  One pixel, of which only the centre tap is inside; sums of at most
+    512 products of integers are exact in single precision."""
+    x = torch.randint(-1, 2, (1, 1, 1, channels), device="cuda").half()
+    w = torch.empty((K, 3, 3, channels), dtype=torch.float16, device="cuda").random_(-2, 3)
+    want = (w[:, 1, 1].float() @ x.view(-1).float()).clamp(min=0).half()
+    d = bolt.conv_desc(1, 1, 1, channels, K, 3, 3, 1, 1)
+    ran = 0
+    for kid in range(bolt.bolt_num_instances(bolt.OP_CONV2D)):
+        cfg = bolt.bolt_instance_config(bolt.OP_CONV2D, kid)
+        if cfg.tile_k != 32 or cfg.tile_m < 64 or cfg.mfma_shape != 16 or not bolt.bolt_instance_supports(bolt.OP_CONV2D, kid, d):
+            continue
+        _say("conv slice %d -> %d instance %d" % (channels, K, kid))
+        y = torch.full((K,), float("nan"), dtype=torch.float16, device="cuda")
+        bolt.bolt_conv2d_fprop_nhwc(d, x, w, None, y, {"kernel_id": kid})
+        assert torch.equal(y, want), "conv slice %d -> %d instance %d" % (channels, K, kid)
+        ran += 1
+    assert ran >= 1
+
+
 # ---------------------------------------------------------------------------------------------
 # config 5: every distinct ResNet-50 layer shape at full size, tuned, sampled outputs
 # ---------------------------------------------------------------------------------------------
