@@ -73,11 +73,11 @@ struct ConvSliceTraits {
            lds_bytes(p) <= 160 * 1024;
   }
   // Pick rule, us: a round of tiles is fill, sum and launch of 2.7, then 1.9 per 64 x 64 outputs and 128 channels (hot, from 18 problems).
-  // (One round: 0.4 more, what the kernels for small problems, against which it stands, are estimated too high; 480 pixels,
-  // 128 -> 152: 5.5 us there, 5.9 here.)
+  // (One round of more than one column of tiles: 0.4 more, what the kernels for small problems, against which it stands, are estimated
+  // too high there; 480 pixels, 128 -> 152: 5.5 us there, 5.9 here; 1500 pixels, 128 -> 64: 5.6 and 5.4.)
   static double estimate(const FpropParams& p) {
     const int rounds = ((p.M + BM - 1) / BM * ((p.N + BN - 1) / BN) + 255) / 256;
-    return (rounds == 1 ? 1.0 : 0.6) + rounds * (2.7 + 1.9 * (BM / 64 * (BN / 64) * CWS) + 2.0 * (PH - 1));
+    return (rounds == 1 && p.N > BN ? 1.0 : 0.6) + rounds * (2.7 + 1.9 * (BM / 64 * (BN / 64) * CWS) + 2.0 * (PH - 1));
   }
 };
 

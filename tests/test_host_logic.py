@@ -500,9 +500,9 @@ def test_small_3x3s_stay_with_the_kernels_for_small_problems():
     """The streamed and the sliced 3x3 kernels, one round of units or tiles: not where the wave-split kernels are faster."""
     conv = lambda n, h, w, c, k: "b.bolt_check(b.OP_CONV2D, b.conv_desc(%d, %d, %d, %d, %d, 3, 3, 1, 1))" % (n, h, w, c, k)
     small = [conv(550, 1, 1, 8, 32), conv(4, 3, 3, 16, 16), conv(30, 22, 4, 24, 16), conv(172, 1, 26, 40, 32), conv(27, 48, 1, 64, 64), conv(20, 8, 3, 128, 152)]
-    new = [conv(22, 25, 8, 32, 64), conv(7, 57, 36, 8, 16), conv(119, 25, 12, 8, 48), conv(8, 56, 56, 64, 64), conv(8, 28, 28, 128, 128)]
+    new = [conv(22, 25, 8, 32, 64), conv(7, 57, 36, 8, 16), conv(119, 25, 12, 8, 48), conv(8, 56, 56, 64, 64), conv(8, 28, 28, 128, 128), conv(6, 10, 25, 128, 64)]
     picks = _picks(small + new)
-    assert [p.split("_")[0] for p in picks] == ["ws"] * len(small) + ["patch"] * 4 + ["slice"], picks
+    assert [p.split("_")[0] for p in picks] == ["ws"] * len(small) + ["patch"] * 4 + ["slice"] * 2, picks
 
 
 def test_built_in_pick_rule_families():
