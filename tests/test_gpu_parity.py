@@ -787,7 +787,8 @@ PATCH_EDGES = [  # N H W C K0 R stride pad K1: units of 4 x 8 pixels and less, c
     (1, 1, 1, 8, 8, 3, 1, 1, 8), (2, 9, 9, 64, 64, 3, 1, 1, 256), (1, 4, 8, 64, 40, 3, 1, 1, 72), (3, 5, 17, 48, 64, 3, 1, 1, 136), (1, 13, 33, 40, 56, 3, 1, 0, 64),
     (2, 7, 15, 32, 64, 3, 1, 2, 200), (5, 6, 23, 16, 32, 3, 1, 1, 192), (1, 11, 16, 56, 24, 3, 1, 1, 256), (2, 17, 19, 64, 64, 3, 2, 1, 256), (1, 15, 34, 24, 48, 3, 2, 1, 88),
     (4, 9, 9, 64, 24, 3, 2, 0, 64), (1, 5, 9, 128, 64, 1, 1, 0, 256), (2, 8, 31, 72, 40, 1, 1, 0, 104), (3, 9, 14, 16, 32, 1, 1, 0, 8), (1, 13, 21, 104, 32, 1, 2, 0, 160), (2, 10, 7, 64, 64, 1, 2, 1, 128),
-    (9, 56, 56, 64, 64, 3, 1, 1, 64), (40, 30, 29, 32, 32, 3, 1, 1, 72), (36, 45, 50, 24, 32, 1, 1, 0, 40)]  # (the last three: several units per wave)
+    (9, 56, 56, 64, 64, 3, 1, 1, 64), (40, 30, 29, 32, 32, 3, 1, 1, 72), (36, 45, 50, 24, 32, 1, 1, 0, 40),  # (from here on: several units per wave)
+    (24, 57, 57, 64, 64, 3, 2, 1, 136), (21, 61, 55, 24, 40, 3, 2, 1, 40), (17, 46, 50, 128, 64, 1, 1, 0, 72), (35, 61, 59, 120, 32, 1, 2, 0, 40)]
 
 
 @pytest.mark.parametrize("case", PATCH_EDGES)
@@ -904,12 +905,13 @@ def test_one_convolution_with_changing_alpha_and_activation(bolt, channels):
 
 @pytest.mark.parametrize("layout", ("kn", "nk"))
 def test_epilogue_of_nan_and_infinity_every_instance(bolt, layout):
-    """ReLU is v > 0 ? v : 0 (NaN gives 0), no activation passes NaN on, GELU keeps NaN and infinity."""
+    """ReLU is v > 0 ? v : 0 (NaN gives 0), no activation passes NaN on, GELU keeps NaN and infinity and is 0, its
+    limit, at minus infinity."""
     a = np.zeros((64, 64), np.float16)
     a[:4, 0] = np.nan, np.inf, -np.inf, -1
     d = lambda act: bolt.gemm_desc(64, 64, 64, act=act, b_layout=bolt.LAYOUT_KN if layout == "kn" else bolt.LAYOUT_NK)
     ad, bd = dev(a), dev(np.ones((64, 64), np.float16))
-    want = {"none": (np.nan, np.inf, -np.inf, -1, 0), "relu": (0, np.inf, 0, 0, 0), "gelu": (np.nan, np.inf)}
+    want = {"none": (np.nan, np.inf, -np.inf, -1, 0), "relu": (0, np.inf, 0, 0, 0), "gelu": (np.nan, np.inf, 0)}
     for kid in range(bolt.bolt_num_instances(bolt.OP_GEMM)):
         for act, rows in want.items():
             if not bolt.bolt_instance_supports(bolt.OP_GEMM, kid, d(act)):
@@ -919,6 +921,69 @@ def test_epilogue_of_nan_and_infinity_every_instance(bolt, layout):
             torch.cuda.synchronize()
             got = host(y)[:len(rows)]
             assert np.array_equal(got, np.repeat(np.array(rows, np.float16)[:, None], 64, 1), equal_nan=True), (kid, act, got[:, 0])
+
+
+def test_epilogue_of_nan_and_infinity_every_convolution_instance(bolt):
+    """The same for 3x3 convolutions and pairs, among them the maximum of packed halves that conv_patch_kernel has.  Single ops: images of
+    one pixel, of the filter the centre tap is inside, one output channel passes the pixel's first channel on.  Pairs, whose first
+    op spreads what it gets over a pixel's channels: the first op's bias in one channel that the second passes on, then the second's bias."""
+    special = {"none": (np.nan, np.inf, -np.inf, -1, 0), "relu": (0, np.inf, 0, 0, 0), "gelu": (np.nan, np.inf, 0)}
+    values = np.array((np.nan, np.inf, -np.inf, -1, 0), np.float16)
+    equal = lambda got, want: np.array_equal(got, np.array(want, np.float16), equal_nan=True)
+    for channels in (64, 128):
+        x, w0, w1 = np.zeros((5, 1, 1, channels), np.float16), np.zeros((64, 3, 3, channels), np.float16), np.zeros((64, 1, 1, 64), np.float16)
+        x[:, 0, 0, 0] = values
+        w0[0, 1, 1, 0] = w1[0, 0, 0, 0] = 1
+        xd, zd, w0d, w1d = dev(x), dev(np.zeros_like(x)), dev(w0), dev(w1)
+        biases = torch.zeros((6, 64), dtype=torch.float16, device="cuda")  # one value in the first channel each, and all of them in five channels
+        biases[:5, 0] = biases[5, :5] = dev(values)
+        for act, want in special.items():
+            c0, c1 = bolt.conv_desc(5, 1, 1, channels, 64, 3, 3, 1, 1, act=act), bolt.conv_desc(5, 1, 1, 64, 64, 1, 1, act=act)
+            singles = [k for k in range(bolt.bolt_num_instances(bolt.OP_CONV2D)) if bolt.bolt_instance_supports(bolt.OP_CONV2D, k, c0)]
+            pairs = [k for k in range(bolt.bolt_num_instances(bolt.OP_B2B_CONV)) if bolt.bolt_instance_supports(bolt.OP_B2B_CONV, k, c0, c1)]
+            assert len(singles) >= 3 and len(pairs) >= 3
+            for kid in singles:
+                _say("nan and infinity, %s, single instance %d, %d channels" % (act, kid, channels))
+                y = torch.full((5, 64), 7.0, dtype=torch.float16, device="cuda")
+                bolt.bolt_conv2d_fprop_nhwc(c0, xd, w0d, None, y, {"kernel_id": kid})
+                torch.cuda.synchronize()
+                assert equal(host(y)[:len(want), 0], want), (kid, act, host(y)[:, 0])
+            for kid in pairs:
+                _say("nan and infinity, %s, pair instance %d, %d channels" % (act, kid, channels))
+                for i in range(6):
+                    y = torch.full((5, 64), 7.0, dtype=torch.float16, device="cuda")
+                    bolt.bolt_b2b_conv(c0, c1, zd, w0d, biases[i] if i < 5 else None, w1d, biases[5] if i == 5 else None, y, {"kernel_id": kid})
+                    torch.cuda.synchronize()
+                    got = host(y)
+                    if i == 5:
+                        assert equal(got[:, :len(want)], np.repeat(np.array(want, np.float16)[None], 5, 0)), (kid, act, got[0, :5])
+                    elif i < len(want):
+                        assert equal(got[:, 0], [want[i]] * 5), (kid, act, i, got[:, 0])
+
+
+@pytest.mark.parametrize("channels", (128, 256, 512))
+def test_conv_slice_other_activations_and_alpha(bolt, channels):
+    """The transcendental branch of the sliced 3x3 kernels' epilogue and alpha != 1, with and without a residual."""
+    N, H, W, K = 3, 9, 7, 136
+    x, w = wl.uniform_fp16(529, 0, (N, H, W, channels), -1, 1), wl.normal_fp16(529, 1, (K, 3, 3, channels), (2.0 / (9 * channels)) ** 0.5)
+    b, res = wl.uniform_fp16(529, 2, (K,), -1, 1), wl.uniform_fp16(529, 3, (N, H, W, K), -2, 2)
+    xd, wd, bd = dev(x), dev(w), dev(b)
+    for act, alpha in (("gelu", 1.0), ("softplus", -0.5), ("hardswish", 2.0), ("none", 0.5)):
+        d, ran = bolt.conv_desc(N, H, W, channels, K, 3, 3, 1, 1, act=act, alpha=alpha), 0
+        want, want_res = (ref.conv2d_nhwc(x, w, b, stride=1, pad=1, alpha=alpha, act=act),
+                          ref.conv2d_nhwc_residual(x, w, b, res, stride=1, pad=1, alpha=alpha, gamma=-0.5, act=act))
+        for kid in range(bolt.bolt_num_instances(bolt.OP_CONV2D)):
+            cfg = bolt.bolt_instance_config(bolt.OP_CONV2D, kid)
+            if cfg.tile_k != 32 or cfg.tile_m < 64 or cfg.mfma_shape != 16 or not bolt.bolt_instance_supports(bolt.OP_CONV2D, kid, d):
+                continue
+            y, r = torch.full((N, H, W, K), float("nan"), dtype=torch.float16, device="cuda"), dev(res)
+            bolt.bolt_conv2d_fprop_nhwc(d, xd, wd, bd, y, {"kernel_id": kid})
+            bolt.bolt_conv2d_fprop_nhwc_residual(d, xd, wd, bd, r, r, -0.5, {"kernel_id": kid})
+            torch.cuda.synchronize()
+            assert_close(host(y), want, "conv slice %d %s %g instance %d" % (channels, act, alpha, kid))
+            assert_close(host(r), want_res, "conv slice %d %s %g residual, instance %d" % (channels, act, alpha, kid))
+            ran += 1
+        assert ran >= 1
 
 
 SLICE_EDGES = [  # N H W K: tiles of 64 and 128 pixels and of 64 and 128 columns with remainders, images of one row or column, several images per tile
