@@ -15,12 +15,16 @@
 //   * bias in the accumulators from the start, ReLU on packed halves: one vector instruction per output value.  One wave per SIMD
 //     issues one instruction every 4 cycles, so instructions are what the loop is short of (a first form with 1740 per unit
 //     took 13400 cycles for it; 700 are left).
-// What bounds it: pairs from 8 images of 56 x 56 on memory (64 -> 64 -> 256 at batch 32: 64 MB in 19.8 us, rounds of 3.4 units per
-// wave); below, the fill: weights, first patch and a unit's chain of products take 5 us (64 channels) beside the launch.
+// What bounds it: the chain of one wave per SIMD, neither memory nor a pipe.  64 -> 64 -> 256 at 56 x 56, batch 32, moves its 64 MB at 3.3 TB/s
+// (a large copy: 4.9; the 1x1 pairs here: 4.5), the matrix cores are busy for 30 % of the SIMDs' cycles, vector instructions for 15 % and
+// LDS for 30 %; a wave waits for loads, LDS and the places of its stores for 43 % of its life, and 3136 units are 3.4 rounds.  Below 8
+// images, the fill: weights, first patch and a unit's chain of products take 5 us (64 channels) beside the launch.
+// Its residual: single ops fetch it one unit ahead of the output.  Other activations than ReLU and alpha != 1 run without the overlap (GEN).
 // Measured under a HIP graph, best tiled instance -> this one, us: 3x3 -> 1x1 at 56 x 56, 64 -> 64 -> 256, batch 32 24.4 -> 19.8, with a
 // residual 35.0 -> 28.9, batch 8 12.9 -> 7.7; 32 -> 32 -> 128 with a residual 30.5 -> 14.3; 112 x 112, 32 -> 32 -> 128 93 -> 23.4;
 // stride 2, 64 -> 64 -> 256 13.6 -> 9.2; 1x1 -> 1x1 at 56 x 56, 64 -> 64 -> 256 26.1 -> 14.4 (4.5 TB/s).  The single 3x3 at 56 x 56,
-// 64 -> 64: batch 32 12.8 -> 12.0, 16 9.3 -> 7.1, 8 7.9 -> 5.2.
+// 64 -> 64: batch 32 12.8 -> 12.0, 16 9.3 -> 7.1, 8 7.9 -> 5.2; with a residual, 15.4 -> 12.7 and 9.0 -> 5.9 at batch 32 and 8.
+// Widths end at 64: the weights of 96 -> 96 would take 648 of a SIMD's 512 registers.
 #pragma once
 #include <algorithm>
 

@@ -17,7 +17,10 @@
 // over the waves and the store behind them, 20 %.
 // Measured with cold / warm caches, best other instance -> this one, us, batch 32: 28 x 28 x 128 -> 128 15.4 / 14.2 -> 13.9 / 13.0; 14 x 14 x 256
 // -> 256 17.7 / 15.2 -> 13.2 / 11.4; 7 x 7 x 512 -> 512 22.8 / 17.0 -> 13.2 / 10.9; batch 8: 12.7 / 10.9 -> 6.2 / 5.7, 11.8 / 10.8 -> 9.5 / 7.1,
-// 16.2 / 13.8 -> 12.8 / 10.0.
+// 16.2 / 13.8 -> 12.8 / 10.0.  A residual, whose rows are on their way while the sums go round, costs 0.3 to 0.7 us (batch 32, warm: 14.8 -> 13.3,
+// 15.7 -> 12.0, 17.7 -> 12.2 against the other kernels).
+// Channels are 128, 256 and 512 because a wave's quarter is unrolled in whole steps of 32 and its pixels lie in LDS at a power of two of chunks:
+// 96, 192 and 320 do not split so, 384 would need a bank order of its own; each count costs up to three kernels of 13 to 22 KB.
 #pragma once
 #include <utility>
 
