@@ -450,6 +450,14 @@ __global__ __launch_bounds__(64 * WM0 * WN0) void b2b_lds_kernel(const B2bParams
   }
 }
 
+// Megabytes that a convolution pair reads and writes: the activations (of a strided 1x1, the pixels that it samples), the output
+// and the residual.
+inline double b2b_conv_mbytes(const B2bParams& p, bool residual) {
+  const ConvGeom& g = p.cg;
+  const double pixels = g.R == 1 && g.S == 1 ? p.M : (double)(p.M / (g.P * g.Q)) * g.H * g.Wi;
+  return 2e-6 * (pixels * g.C + (double)p.M * p.N1 * (residual ? 2 : 1));
+}
+
 struct B2bInstance {
   const char* name;
   int mode;  // 0 RF-resident, 1 LDS-resident
@@ -464,10 +472,9 @@ struct B2bInstance {
   // Relative time per unit of tile work of this kernel family on the convolution pairs of Section 4.1.2, as measured
   // (0 = 1.0: the weights-resident kernels); read by the built-in pick rule only, bolt_tune measures.
   float prior;
-  // A family with a rule of its own for where the built-in pick takes it (null: the common cost model, which the prior above is
-  // for).  Its two widths are never too wide: it is tight wherever it can run, and the other instances' legality does not
-  // depend on it.
-  bool (*gains)(const B2bParams&, bool residual);
+  // A family with an estimate of its own for the built-in pick, in us (null: the common cost model, which the prior above is for).
+  // Its two widths are never too wide: it is tight wherever it can run, and the other instances' legality does not depend on it.
+  double (*estimate)(const B2bParams&, bool residual);
 };
 
 template <typename KernT>

@@ -620,7 +620,7 @@ static bool b2b_can_run(const B2bInstance& in, const B2bProblem& pr) {
 // Threadblock residence with the tightest compiled bound: an instance that would carry more than 2x padding in a
 // width is left out ...
 static bool b2b_is_tight(const B2bInstance& in, const B2bProblem& pr) {
-  if (in.gains) return true;
+  if (in.estimate) return true;
   return !((in.n0t > 32 && in.n0t / 2 >= pr.p.N0) || (in.n1t > 32 && in.n1t / 2 >= pr.p.N1));
 }
 // ... unless that leaves the problem without a kernel (e.g. N0 = 128 with N1 = 16: no compiled pair of widths is tight
@@ -629,7 +629,7 @@ static bool b2b_supports(const std::vector<B2bInstance>& tab, int id, const B2bP
   if (!b2b_can_run(tab[id], pr)) return false;
   if (b2b_is_tight(tab[id], pr)) return true;
   for (const B2bInstance& other : tab)
-    if (!other.gains && b2b_can_run(other, pr) && b2b_is_tight(other, pr)) return false;
+    if (!other.estimate && b2b_can_run(other, pr) && b2b_is_tight(other, pr)) return false;
   return true;
 }
 
@@ -663,7 +663,7 @@ static int b2b_heuristic(const std::vector<B2bInstance>& tab, const B2bProblem& 
   int best = -1;
   double best_cost = 0;
   for (int i = 0; i < (int)tab.size(); ++i) {
-    if (tab[i].gains || b2b_streams(tab[i]) || !b2b_supports(tab, i, pr)) continue;
+    if (tab[i].estimate || b2b_streams(tab[i]) || !b2b_supports(tab, i, pr)) continue;
     const B2bInstance& in = tab[i];
     const double tiles = ceil_div(pr.p.M, in.bm);
     const int lds = in.dyn_lds_bytes ? in.dyn_lds_bytes(pr.p) : in.lds_bytes(pr.p.K0);
@@ -706,14 +706,15 @@ static int b2b_heuristic(const std::vector<B2bInstance>& tab, const B2bProblem& 
     }
   }
   // The convolution pairs with the first op's weights in registers (conv_patch_kernel), the tightest widths of those that can run
-  // it, where they gain (ConvPatchTraits::gains).
+  // it, where their estimate is below that of the tiled kernels' pick: its cost in us, two-wave workgroups of 64 rows apart, and what
+  // memory moves (16 % off).  Over the pairs of ConvPatchTraits::estimate_pair the choice takes 1.011 times the faster of the two, 1.5 at most;
+  // the tiled kernels 1.27 and 3.4, conv_patch_kernel wherever it can run 1.38 and 7.
+  auto tiled_us = [&] { return 5.0 + best_cost * 1e-6 * (tab[best].bm == 64 ? 1.25 : 0.8) + 0.14 * b2b_conv_mbytes(pr.p, pr.residual); };
   int patch = -1;
   auto widths = [](const B2bInstance& in) { return (in.bk << 10) + in.n0t; };
   for (int i = 0; i < (int)tab.size(); ++i)
-    if (tab[i].gains && b2b_supports(tab, i, pr) && (best < 0 || tab[i].gains(pr.p, pr.residual)) &&
-        (patch < 0 || widths(tab[i]) < widths(tab[patch])))
-      patch = i;
-  if (patch >= 0) best = patch;
+    if (tab[i].estimate && b2b_supports(tab, i, pr) && (patch < 0 || widths(tab[i]) < widths(tab[patch]))) patch = i;
+  if (patch >= 0 && (best < 0 || tab[patch].estimate(pr.p, pr.residual) < tiled_us())) best = patch;
   if (tune_log_enabled() && best >= 0) std::fprintf(stderr, "[bolt_pick] -> %d %s\n", best, tab[best].name);
   return best;
 }

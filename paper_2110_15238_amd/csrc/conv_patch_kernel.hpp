@@ -27,6 +27,7 @@
 // Widths end at 64: the weights of 96 -> 96 would take 648 of a SIMD's 512 registers.
 #pragma once
 #include <algorithm>
+#include <cmath>
 
 #include "b2b_dma_kernel.hpp"
 
@@ -127,26 +128,15 @@ struct ConvPatchTraits {
   }
   static bool supports_single(const FpropParams& f) { return supports(from_single(f)); }
   static int lds_bytes_single(const FpropParams&) { return lds_bytes_n(0); }
-  // Where the pick rule takes a pair: where the pixels fill the rounds of units that they take.  A unit that an image does not
-  // fill costs as much as a full one: images of one column fill an eighth of every unit, of one pixel a 32nd, and without this
-  // rule took up to 14 times the tiled kernels' time (1x1 images, 100000 of them, 3x3 64 -> 64 -> 256: 23.7 -> 330 us).  Up to
-  // two rounds the fill of the tiled kernels' own tiles outweighs it (1601 problems: 0.56 to 1.13 of their time, mean 0.8).  Beyond,
-  // a round takes 0.9 to 6.4 us, and the tiled kernels 0.9 to 12 for the 32768 pixels of a full one: the bounds below are
-  // where the two meet, by what weighs in them (8 to 64 columns: one chunk; a residual of more than 128; 72 products of
-  // 32 x 32 x 16 in op0).  Over 5132 problems (images of 1 x 1 to 11 x 24, 1500 to 130000 pixels, with and without a residual)
-  // the choice takes 1.01 times the faster of the two.
-  static bool gains(const B2bParams& p, bool residual) {
-    if (!plain(p)) return false;
-    const ConvPatchParams q = plan(p);
-    const int rounds = (q.units + MOST_WGS * NW - 1) / (MOST_WGS * NW);
-    if (rounds <= 2) return true;
-    const bool window = RS == 3 && ST == 1;
-    const double least = p.N1 <= 64            ? (window && p.N0 <= 32 ? 0.48 : 0.70)
-                         : window && p.cg.C > 48 ? 0.60
-                         : p.N1 <= 128         ? 0.35
-                         : residual            ? 0.70
-                                               : 0.40;
-    return p.M >= least * (rounds == 3 ? 0.8 : 1.0) * rounds * (MOST_WGS * NW * TP * TQ);
+  // Pick rule, us of a pair: the fill, then rounds of units, each with its products of 32 x 32 x 16, the load instructions of a patch, and
+  // per 64 columns of op1 the store, the residual and the products; and what memory moves.  A unit that an image does not fill costs
+  // as much as a full one.  (3998 pairs, images of 1 x 1 to 112 x 112, 1000 to 300000 pixels, with and without a residual: 6 % off, nine of
+  // ten within 9 %.)
+  static double estimate_pair(const B2bParams& p, bool residual) {
+    if (!plain(p)) return HUGE_VAL;
+    const int rounds = (plan(p).units + MOST_WGS * NW - 1) / (MOST_WGS * NW), chunks = (p.N1 + NC - 1) / NC;
+    const double round = 0.07 + 0.018 * (KS * FN0) + 0.033 * (ROWS * RI) + chunks * (0.38 + 0.075 * FN0 + (residual ? 0.42 : 0.0));
+    return 3.2 + rounds * round + 0.049 * b2b_conv_mbytes(p, residual);
   }
   // Pick rule, us: the fill with the first unit, then a round per unit and wave (from 28 problems, 1 to 7 rounds).  A single round
   // takes 3.7 or 4.9 too, but stands against the kernels for small problems, whose estimates are up to 1.1 us too high here: of 83
@@ -658,7 +648,8 @@ hipError_t launch_conv_patch_single(const FpropParams& f, hipStream_t stream) {
   {                                                                                                            \
     "b2bpatch_c" #CP "_n" #N0T "_r" #RS "_st" #ST, 0, 128, CP, 4, 1, N0T, 256, 1, 0, 256, 1, nullptr,            \
         &bolt::launch_conv_patch<CP, N0T, RS, ST, true>, &bolt::ConvPatchTraits<CP, N0T, RS, ST, true>::supports,            \
-        &bolt::ConvPatchTraits<CP, N0T, RS, ST, true>::lds_bytes, true, 0.f, &bolt::ConvPatchTraits<CP, N0T, RS, ST, true>::gains  \
+        &bolt::ConvPatchTraits<CP, N0T, RS, ST, true>::lds_bytes, true, 0.f,         \
+        &bolt::ConvPatchTraits<CP, N0T, RS, ST, true>::estimate_pair                                              \
   }
 
 }  // namespace bolt

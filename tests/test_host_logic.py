@@ -483,7 +483,7 @@ def test_one_tap_filters_over_many_unpadded_pixels_stay_with_the_alignment_2_ker
 
 def test_pairs_keep_to_the_tiled_kernels_where_images_do_not_fill_units():
     """conv_patch_kernel works on 4 x 8 output pixels of one image: many images of one column or one pixel took it up to 14 times as
-    long as the tiled kernels.  Up to two units per wave it gains whatever their fill."""
+    long as the tiled kernels.  Elsewhere it gains, also with units that are half full where the tiled kernels' widths do not fit."""
     def pair(n, h, w, c, k0, r, stride, k1):
         p, q = (h - 1) // stride + 1, (w - 1) // stride + 1
         return ("b.bolt_check(b.OP_B2B_CONV, b.conv_desc(%d, %d, %d, %d, %d, %d, %d, %d, %d), b.conv_desc(%d, %d, %d, %d, %d, 1, 1))" %
@@ -491,7 +491,8 @@ def test_pairs_keep_to_the_tiled_kernels_where_images_do_not_fill_units():
     tiled = [pair(100000, 1, 1, 64, 64, 3, 1, 256), pair(12000, 1, 1, 64, 64, 1, 1, 256), pair(1785, 56, 1, 32, 32, 3, 1, 64), pair(166, 300, 2, 64, 64, 3, 2, 128),
              pair(25000, 2, 2, 128, 64, 1, 1, 64), pair(1785, 1, 56, 64, 64, 3, 1, 256)]
     patch = [pair(1000, 1, 1, 64, 64, 3, 1, 256), pair(32, 56, 56, 64, 64, 3, 1, 256), pair(214, 7, 56, 32, 32, 3, 1, 128), pair(32, 112, 112, 32, 32, 3, 1, 64),
-             pair(2040, 7, 7, 64, 64, 1, 1, 256), pair(4, 14, 14, 64, 64, 3, 1, 256), pair(32, 56, 56, 64, 64, 3, 2, 32)]
+             pair(2040, 7, 7, 64, 64, 1, 1, 256), pair(4, 14, 14, 64, 64, 3, 1, 256), pair(32, 56, 56, 64, 64, 3, 2, 32),
+             pair(72, 85, 11, 56, 16, 3, 1, 72), pair(179, 19, 86, 64, 56, 1, 2, 8)]  # (half-filled units, but tiled kernels of twice to four times the width)
     picks = _picks(tiled + patch)
     assert [p.startswith("b2bpatch_") for p in picks] == [False] * len(tiled) + [True] * len(patch), picks
 
