@@ -45,8 +45,8 @@ def run(tmp_path_factory):
 
 
 def test_a_remembered_pick_is_for_its_alpha_and_activation(run):
-    """conv_patch_kernel has no alpha and no GELU: after a call that it serves, the same sizes with another alpha or activation run on
-    another kernel, as they do alone, and the first call runs on it again."""
+    """The pick rule takes conv_patch_kernel for alpha = 1 with ReLU or nothing: after such a call the same sizes with another alpha or
+    activation run on another kernel, as they do alone, and the first call runs on it again."""
     run("""
 d = lambda alpha, act: b.conv_desc(8, 56, 56, 64, 64, 3, 3, 1, 1, alpha=alpha, act=act)
 for turn in range(2):
