@@ -8,6 +8,7 @@
 #include <stdint.h>
 
 #include <mutex>
+#include <utility>
 
 namespace bolt {
 
@@ -18,6 +19,16 @@ typedef half_t half8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+
+// f(integral_constant<int, 0>) .. f(integral_constant<int, N - 1>): a loop that is unrolled whatever its length
+template <int... I, typename F>
+__device__ __forceinline__ void for_constants_impl(std::integer_sequence<int, I...>, F&& f) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void for_constants(F&& f) {
+  for_constants_impl(std::make_integer_sequence<int, N>{}, f);
+}
 
 enum { ACT_NONE = 0, ACT_RELU = 1, ACT_GELU = 2, ACT_HARDSWISH = 3, ACT_SOFTPLUS = 4 };
 

@@ -22,21 +22,9 @@
 // Channels are 128, 256 and 512 because a wave's quarter is unrolled in whole steps of 32 and its pixels lie in LDS at a power of two of chunks:
 // 96, 192 and 320 do not split so, 384 would need a bank order of its own; each count costs up to three kernels of 13 to 22 KB.
 #pragma once
-#include <utility>
-
 #include "fprop_dma_kernel.hpp"
 
 namespace bolt {
-
-// f(integral_constant<int, 0>) .. f(integral_constant<int, N - 1>): a loop that is unrolled whatever its length
-template <int... I, typename F>
-__device__ __forceinline__ void for_constants_impl(std::integer_sequence<int, I...>, F&& f) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void for_constants(F&& f) {
-  for_constants_impl(std::make_integer_sequence<int, N>{}, f);
-}
 
 struct ConvSliceParams : FpropParams {
   unsigned rcp_hw, rcp_w, rcp_tiles;  // (2^32 - 1) / (H W), / W and / tiles_m: quotients from them are exact or one too small

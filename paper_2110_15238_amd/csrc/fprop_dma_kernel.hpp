@@ -20,9 +20,6 @@ namespace bolt {
 
 #define BOLT_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
 
-#ifndef BOLT_INTERLEAVE_READS
-#define BOLT_INTERLEAVE_READS 1
-#endif
 #ifndef BOLT_FRAG_DEPTH
 #define BOLT_FRAG_DEPTH 4  // MFMAs a register set of fragments should feed
 #endif
@@ -145,7 +142,7 @@ struct DmaTileLoader {
       for (int j = J0; j < J1; ++j) {
         const int rb = (j * NW + wave) * RPI;
         const int row = rb + lrow;
-        const unsigned off = (row < rows_valid && k < K) ? (unsigned)(row * ld + k) * 2u : kInvalidOffset;
+        const unsigned off = ((row < rows_valid) & (k < K)) ? (unsigned)(row * ld + k) * 2u : kInvalidOffset;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, BOLT_LDS_PTR(dst + rb * BK), 16, off, 0, 0, 0);
       }
     } else {
@@ -154,7 +151,7 @@ struct DmaTileLoader {
       for (int j = J0; j < J1; ++j) {
         const int rb = (j * NW + wave) * RPI;
         const int ih = (xhw[j] >> 16) + cr, iw = (int)(short)(xhw[j] & 0xffff) + cs;
-        const bool ok = k < K && (unsigned)ih < (unsigned)cg.H && (unsigned)iw < (unsigned)cg.Wi;
+        const bool ok = (k < K) & ((unsigned)ih < (unsigned)cg.H) & ((unsigned)iw < (unsigned)cg.Wi);
         const unsigned off = ok ? (unsigned)(xbase[j] + delta) * 2u : kInvalidOffset;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, BOLT_LDS_PTR(dst + rb * BK), 16, off, 0, 0, 0);
       }
@@ -219,7 +216,7 @@ struct DmaKnTileLoader {
       const int rb = (j * NW + wave) * RPI;
       const int row = rb + lrow, k = kt * BK + row;
       const int c = lc ^ kn_swizzle<BN>(row);  // the chunk of the row this lane's fixed LDS slot holds
-      const unsigned off = (k < K && c * 8 < cols_valid) ? (unsigned)(k * ld + c * 8) * 2u : kInvalidOffset;
+      const unsigned off = ((k < K) & (c * 8 < cols_valid)) ? (unsigned)(k * ld + c * 8) * 2u : kInvalidOffset;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, BOLT_LDS_PTR(dst + rb * BN), 16, off, 0, 0, 0);
     }
   }
@@ -388,6 +385,22 @@ struct FpropDmaTraits {
   static_assert(NS >= 1 && NS <= 8, "stages (NS == 1: problems of a single k-tile per k-group only)");
   static_assert(KG >= 1 && NT <= 1024, "workgroup size");
   static_assert(STORE_THREADS % CPR == 0 && BM % ROWS_PER_PASS == 0, "C tile store mapping");
+
+  // k-steps of 16 per register set of operand fragments: enough for `depth` MFMAs, as far as the k-tile has them.  Eight MFMAs
+  // cover an LDS round trip under load, four do not (see the main loop), but the sets are registers: eight only where as many
+  // workgroups fit a compute unit as with four, by registers (512 per SIMD lane; accumulators, both sets and about 28 more)
+  // and by LDS.  128 x 64 x 64 on 4 waves, 3 stages: 76 registers -> 132, two workgroups either way; 128 x 128 x 64 on 8 waves with
+  // 2 stages would go from two (102) to one (155).  A single stage has no loads to overlap with and stays with four.
+  static constexpr int KS = BK / 16;
+  static constexpr int group_steps(int depth) {
+    return FM * FN >= depth ? 1 : depth / (FM * FN) < KS ? depth / (FM * FN) : KS;
+  }
+  static constexpr int resident(int depth) {
+    const int regs = (FM * FN * 16 + 2 * group_steps(depth) * (FM + FN) * 4 + 28 + 7) / 8 * 8;
+    const int by_regs = 512 / regs * 4 / NW, by_lds = 160 * 1024 / LDS_BYTES;
+    return by_regs < by_lds ? by_regs : by_lds;
+  }
+  static constexpr int G = group_steps(NS > 1 && resident(2 * BOLT_FRAG_DEPTH) >= resident(BOLT_FRAG_DEPTH) ? 2 * BOLT_FRAG_DEPTH : BOLT_FRAG_DEPTH);
 };
 
 // NCHW: the output tensor is [N][K][P][Q] (convolutions only; see fprop_tile_out_with)
@@ -462,168 +475,131 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG) void fprop_dma_kernel(
   // Fragments are double-buffered in registers in groups of G k-steps: the LDS reads of the next
   // group (or of the first group of the next tile) are in flight while the MFMAs of the current one
   // execute, so the matrix pipe keeps working across the workgroup barrier that separates two
-  // k-tiles.  A wave tile with few accumulators issues few MFMAs per k-step, too few to cover an LDS
-  // round trip, so it prefetches deeper: G k-steps hold about BOLT_FRAG_DEPTH MFMAs.
-  constexpr int KS = BK / 16;
-  constexpr int G = FM * FN >= BOLT_FRAG_DEPTH ? 1 : (BOLT_FRAG_DEPTH / (FM * FN) < KS ? BOLT_FRAG_DEPTH / (FM * FN) : KS);
-  constexpr int NG = KS / G;  // fragment groups per k-tile
-  static_assert(KS % G == 0 && (NG == 1 || NG % 2 == 0), "register sets alternate per group");
+  // k-tiles.
+  constexpr int G = T::G, NG = T::KS / G;  // k-steps per group, groups per k-tile
+  static_assert(T::KS % G == 0 && (NG == 1 || NG == 2 || NG == 4), "fragment groups per k-tile; register sets alternate per group");
   half8 xf[2][G][FM], wf[2][G][FN];
-  auto read_group = [&](int stage, int grp, half8 (&x)[G][FM], half8 (&w)[G][FN]) {
-    const half_t* xs = lds_group + stage * STAGE;
+  // Fragment R (x first) of the reads of group `grp` of the tile in stage `stg`.
+  auto read_one = [&](int stg, int grp, auto rc, half8 (&x)[G][FM], half8 (&w)[G][FN]) {
+    constexpr int R = decltype(rc)::value, k = R / (FM + FN), f = R % (FM + FN);
+    const half_t* xs = lds_group + stg * STAGE;
     const half_t* ws = xs + BM * BK;
-#pragma unroll
-    for (int k = 0; k < G; ++k) {
-      const int chunk = (grp * G + k) * 2 + g;
-#pragma unroll
-      for (int b = 0; b < FM; ++b)
-        x[k][b] = *(const half8*)(xs + dma_chunk_offset<BK>(wm * WTM + b * 32 + l32, chunk));
-#pragma unroll
-      for (int a = 0; a < FN; ++a) {
-        if constexpr (WKN) w[k][a] = kn_frag_read<BN>(ws, wfo[a], (grp * G + k) * 16);
-        else w[k][a] = *(const half8*)(ws + dma_chunk_offset<BK>(wn * WTN + a * 32 + l32, chunk));
-      }
-    }
-  };
-  auto mfma_group = [&](const half8 (&x)[G][FM], const half8 (&w)[G][FN]) {
-#pragma unroll
-    for (int k = 0; k < G; ++k)
-#pragma unroll
-      for (int a = 0; a < FN; ++a)
-#pragma unroll
-        for (int b = 0; b < FM; ++b) acc[a][b] = mfma_32x32x16(w[k][a], x[k][b], acc[a][b]);
+    const int chunk = (grp * G + k) * 2 + g;
+    if constexpr (f < FM) x[k][f] = *(const half8*)(xs + dma_chunk_offset<BK>(wm * WTM + f * 32 + l32, chunk));
+    else if constexpr (WKN) w[k][f - FM] = kn_frag_read<BN>(ws, wfo[f - FM], (grp * G + k) * 16);
+    else w[k][f - FM] = *(const half8*)(ws + dma_chunk_offset<BK>(wn * WTN + (f - FM) * 32 + l32, chunk));
   };
 
   // ---- NS-deep pipeline: one barrier per k-tile ----------------------------------------------
   const int n_tiles = (kt_end - kt_first + KG - 1) / KG;  // pipeline steps, the same for every k-group
   if (n_tiles > 0) {
+    int stage = 0, fill_stage = 0;
+    auto load_one = [&](int kt, auto ic) {  // load instruction I of tile kt: [X instructions | W instructions]
+      constexpr int I = decltype(ic)::value, XN = XL::NI;
+      half_t* s = lds_group + fill_stage * STAGE;
+      if constexpr (I < XN) xl.template issue_part<I, I + 1>(kt, s, p.cg);
+      else wl.template issue_part<I - XN, I - XN + 1>(kt, s + BM * BK, p.cg);
+    };
 #pragma unroll
-    for (int s = 0; s < NS; ++s)
-      if (s < n_tiles) issue(kt_begin + s * KG, s);
+    for (int t = 0; t < NS; ++t)
+      if (t < n_tiles) issue(kt_begin + t * KG, t);
     if (n_tiles >= NS) barrier_after_loads<(NS - 1) * L>();
     else barrier_after_loads<0>();
-    read_group(0, 0, xf[0], wf[0]);
-    int stage = 0;
-    // The L load instructions of a k-tile are issued in SL slices spread over the MFMA groups that
-    // follow the barrier which frees their stage: a burst of direct-to-LDS loads stalls in issue while
-    // the address path digests it, and a wave issues in order, so everything behind the burst would
-    // wait with it.  Slice 0 goes out right after the barrier, the others between the later groups.
-    constexpr int SL = NG > 1 ? NG : KS;
-    auto issue_slice = [&](int kt, int stg, auto sc) {
-      constexpr int S = decltype(sc)::value;
-      constexpr int lo = S * L / SL, hi = (S + 1) * L / SL;  // positions in [X instructions | W instructions]
-      constexpr int XN = XL::NI;
-      constexpr int xlo = lo < XN ? lo : XN, xhi = hi < XN ? hi : XN;
-      constexpr int wlo = (lo > XN ? lo : XN) - XN, whi = (hi > XN ? hi : XN) - XN;
-      half_t* s = lds_group + stg * STAGE;
-      xl.template issue_part<xlo, xhi>(kt, s, p.cg);
-      wl.template issue_part<wlo, whi>(kt, s + BM * BK, p.cg);
-      if (S == SL - 1) {
+    for_constants<G * (FM + FN)>([&](auto rc) { read_one(0, 0, rc, xf[0], wf[0]); });
+    // From tile `it` to the next: this wave's reads of the tile are complete (lgkmcnt 0) and tile it+1 has landed (vmcnt); behind
+    // the barrier that holds for every wave, so the stage just read can be refilled with tile it+NS while the last MFMAs of
+    // tile `it` are still to issue.
+    auto turn = [&](int it) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (n_tiles - 2 - it >= NS - 2) barrier_after_reads_and_loads<(NS >= 2 ? NS - 2 : 0) * L>();
+      else barrier_after_reads_and_loads<0>();
+      fill_stage = stage;
+      stage = stage + 1 == NS ? 0 : stage + 1;
+    };
+    // The MFMAs of fragment group j, out of register set SET; the reads of the next group (READS; the first group of the next tile
+    // behind the last of this one); and slice (j + 1) % NG of the L load instructions of tile kt (LOADS 1; 2: if `more`).
+    // A wave issues in order: a burst of LDS reads or of direct-to-LDS loads is issue time during which this wave feeds
+    // the matrix pipe nothing, and since the barrier keeps the waves in step, the LDS, the address path and the matrix pipes then
+    // work in turns.  So both are laid out between the MFMAs, two reads behind one (and the loads evenly), and the fences
+    // keep it so: left alone, the scheduler sinks each read to just before its use.  Cycles of a k-tile step with operands in the
+    // L2s, bursts -> this (the MFMAs alone need 512 of a 128 x 128 x 64 step, 640 with the barrier): 128 x 128 tiles on 2 x 4 waves
+    // 1030 -> 725 (row-major weights 1060 -> 825), on 2 x 2 1310 -> 990, 128 x 64 on 2 x 2 870 -> 530, 256 x 128 on 4 x 2 1580 -> 1220.
+    // Three reads behind an MFMA, or sets for four MFMAs instead of eight, take 5 to 25 % more; a branch around every load 5 to 8.
+    // Per launch, operands from beyond the L2s, best instance of each: 14 x 14 1024 -> 2048 at stride 2, 32 images, 13.8 -> 12.8 us;
+    // 3 x 3 at stride 2 512 -> 512 20.8 -> 17.9; 2048^3 row-major 23.3 -> 22.3; 2537 x 1176 x 7296 62.3 -> 58.2.  From 19 GFLOP on the
+    // clock takes part of it back (1.94 -> 1.71 GHz at 4096 x 2048 x 1024, 21.0 -> 19.0 us).
+    auto group = [&](auto jc, auto setc, auto readsc, auto loadsc, int kt, bool more) {
+      constexpr int j = decltype(jc)::value, cur = decltype(setc)::value, nxt = cur ^ 1, LOADS = decltype(loadsc)::value;
+      constexpr bool last = j + 1 == NG;
+      constexpr int MF = G * FM * FN, RD = decltype(readsc)::value ? G * (FM + FN) : 0;
+      constexpr int S = (j + 1) % NG, L0 = S * L / NG, LD = LOADS ? (S + 1) * L / NG - L0 : 0;
+      constexpr int PER = (RD + MF - 1) / MF > 2 ? (RD + MF - 1) / MF : 2;
+      __builtin_amdgcn_sched_barrier(0);
+      for_constants<MF>([&](auto mc) {
+        constexpr int I = decltype(mc)::value, k = I / (FM * FN), a = I / FM % FN, b = I % FM;
+        acc[a][b] = mfma_32x32x16(wf[cur][k][a], xf[cur][k][b], acc[a][b]);
+        constexpr int r0 = I * PER < RD ? I * PER : RD, r1 = (I + 1) * PER < RD ? (I + 1) * PER : RD;
+        for_constants<r1 - r0>([&](auto rc) {
+          read_one(stage, last ? 0 : j + 1, std::integral_constant<int, r0 + decltype(rc)::value>{}, xf[nxt], wf[nxt]);
+        });
+        constexpr int l0 = I * LD / MF, l1 = (I + 1) * LD / MF;
+        if constexpr (l1 > l0)
+          if (LOADS == 1 || more) for_constants<l1 - l0>([&](auto lc) { load_one(kt, std::integral_constant<int, L0 + l0 + decltype(lc)::value>{}); });
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    };
+    using C0 = std::integral_constant<int, 0>;
+    using C1 = std::integral_constant<int, 1>;
+    if constexpr (NG > 1) {
+      // All stages are requested when the loop begins, so the first load is due behind the first turn: a step is the last group of
+      // one tile and the other groups of the next, with loads as long as there are tiles to load.
+      constexpr int SET = (NG - 1) & 1;
+      auto others = [&](auto loadsc, int kt) {
+        for_constants<NG - 1>([&](auto jc) { group(jc, std::integral_constant<int, decltype(jc)::value & 1>{}, C1{}, loadsc, kt, true); });
+      };
+      using LastGroup = std::integral_constant<int, NG - 1>;
+      using LastSet = std::integral_constant<int, SET>;
+      others(C0{}, 0);
+      int it = 0;
+      for (; NS > 1 && it + NS < n_tiles; ++it) {
+        const int kt = kt_begin + (it + NS) * KG;
+        turn(it);
+        group(LastGroup{}, LastSet{}, C1{}, C1{}, kt, true);
+        others(C1{}, kt);
         xl.advance(p.cg);
         wl.advance(p.cg);
       }
-    };
-    auto read_step = [&](int stg, int ks, half8 (&x)[FM], half8 (&w)[FN]) {
-      const half_t* xs = lds_group + stg * STAGE;
-      const half_t* ws = xs + BM * BK;
-      const int chunk = ks * 2 + g;
-#pragma unroll
-      for (int b = 0; b < FM; ++b) x[b] = *(const half8*)(xs + dma_chunk_offset<BK>(wm * WTM + b * 32 + l32, chunk));
-#pragma unroll
-      for (int a = 0; a < FN; ++a) {
-        if constexpr (WKN) w[a] = kn_frag_read<BN>(ws, wfo[a], ks * 16);
-        else w[a] = *(const half8*)(ws + dma_chunk_offset<BK>(wn * WTN + a * 32 + l32, chunk));
+      for (; NS > 1 && it + 1 < n_tiles; ++it) {
+        turn(it);
+        group(LastGroup{}, LastSet{}, C1{}, C0{}, 0, false);
+        others(C0{}, 0);
       }
-    };
-    int fill_stage = 0;  // stage that the tile in flight of issue (tile it-1+NS) goes to
-    // One k-tile; `par` = register set that holds its first fragment group.
-    auto tile_body = [&](int it, auto par) {
-      constexpr int P = decltype(par)::value;
-      if constexpr (NG > 1) {
-        // Large wave tiles: one LDS read between consecutive MFMAs instead of a burst of FM + FN reads in front
-        // of them (a burst is FM + FN issue slots during which this wave feeds the matrix pipe nothing).
-        constexpr bool IL = BOLT_INTERLEAVE_READS && G == 1 && FM * FN > FM + FN;
-        auto group = [&](auto jc) {
-          constexpr int j = decltype(jc)::value;
-          constexpr int cur = (P + j) & 1, nxt = cur ^ 1;
-          // Fences keep the order "loads, the next group's reads, this group's MFMAs": left alone, the
-          // scheduler sinks each read to just before its first use and the MFMAs wait on LDS.
-          __builtin_amdgcn_sched_barrier(0);
-          if (j + 1 < NG) {
-            // slice j+1 of the tile whose slice 0 went out at the barrier that ended tile it-1
-            if (it >= 1 && it - 1 + NS < n_tiles)
-              issue_slice(kt_begin + (it - 1 + NS) * KG, fill_stage, std::integral_constant<int, (j + 1 < NG ? j + 1 : 0)>{});
-            if constexpr (IL) __builtin_amdgcn_sched_barrier(0);
-            read_group(stage, j + 1, xf[nxt], wf[nxt]);
-          } else {
-            // end of tile `it`: this wave's reads of the tile are complete (lgkmcnt 0) and tile it+1 has
-            // landed (vmcnt); after the barrier that holds for every wave, so the stage just read
-            // can be refilled with tile it+NS while the last MFMAs of tile `it` are still to issue.
-            // After the last tile this runs once more unconditionally (the fragments it reads are
-            // never used): a branch here would make the compiler wait for the new reads before
-            // the MFMAs below.
-            if (NS >= 2 && n_tiles - 2 - it >= NS - 2) barrier_after_reads_and_loads<(NS >= 2 ? NS - 2 : 0) * L>();
-            else barrier_after_reads_and_loads<0>();
-            if (it + NS < n_tiles) issue_slice(kt_begin + (it + NS) * KG, stage, std::integral_constant<int, 0>{});
-            fill_stage = stage;
-            stage = stage + 1 == NS ? 0 : stage + 1;
-            if constexpr (IL) __builtin_amdgcn_sched_barrier(0);
-            read_group(stage, 0, xf[nxt], wf[nxt]);
-          }
-          if constexpr (!IL) __builtin_amdgcn_sched_barrier(0);
-          mfma_group(xf[cur], wf[cur]);
-          if constexpr (IL) {
-#pragma unroll
-            for (int i = 0; i < FM + FN; ++i) {
-              __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
-              __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // one LDS read
-            }
-            __builtin_amdgcn_sched_group_barrier(0x008, FM * FN - (FM + FN), 0);
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        };
-        group(std::integral_constant<int, 0>{});
-        group(std::integral_constant<int, 1>{});
-        if constexpr (NG > 2) {
-          group(std::integral_constant<int, 2>{});
-          group(std::integral_constant<int, 3>{});
-        }
-        static_assert(NG == 2 || NG == 4 || NG == 1, "fragment groups per k-tile");
-      } else {
-        // One fragment group per tile (small wave tiles): the same interleave per k-step.
-        constexpr int cur = P, nxt = P ^ 1;
-        __builtin_amdgcn_sched_barrier(0);
-        if (NS >= 2 && n_tiles - 2 - it >= NS - 2) barrier_after_reads_and_loads<(NS >= 2 ? NS - 2 : 0) * L>();
-        else barrier_after_reads_and_loads<0>();
-        const int nstage = stage + 1 == NS ? 0 : stage + 1;
+      group(LastGroup{}, LastSet{}, C0{}, C0{}, 0, false);
+    } else if constexpr (NS == 1) {
+      group(C0{}, C0{}, C0{}, C0{}, 0, false);
+    } else {
+      // One group per tile: the register sets swap roles every tile.  (Behind the last tile the turn and the reads run once more,
+      // to no use: a branch there would make the compiler wait for the new reads before the MFMAs.)
+      auto tile = [&](int it, auto setc, auto loadsc) {
         const bool more = it + NS < n_tiles;
-        auto step = [&](auto kc) {
-          constexpr int ks = decltype(kc)::value;
-          if (more) issue_slice(kt_begin + (it + NS) * KG, stage, kc);
-          read_step(nstage, ks, xf[nxt][ks], wf[nxt][ks]);
-          __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-          for (int a = 0; a < FN; ++a)
-#pragma unroll
-            for (int b = 0; b < FM; ++b) acc[a][b] = mfma_32x32x16(wf[cur][ks][a], xf[cur][ks][b], acc[a][b]);
-          __builtin_amdgcn_sched_barrier(0);
-        };
-        step(std::integral_constant<int, 0>{});
-        if constexpr (KS > 1) step(std::integral_constant<int, 1>{});
-        if constexpr (KS > 2) step(std::integral_constant<int, 2>{});
-        if constexpr (KS > 3) step(std::integral_constant<int, 3>{});
-        stage = nstage;
-      }
-    };
-    if constexpr (NG % 2 == 0) {
-      for (int it = 0; it < n_tiles; ++it) tile_body(it, std::integral_constant<int, 0>{});
-    } else {  // one group per tile: the register sets swap roles every tile
+        turn(it);
+        group(C0{}, setc, C1{}, loadsc, kt_begin + (it + NS) * KG, more);
+        if (decltype(loadsc)::value == 1 || more) {
+          xl.advance(p.cg);
+          wl.advance(p.cg);
+        }
+      };
+      using C2 = std::integral_constant<int, 2>;
       int it = 0;
-      for (; it + 1 < n_tiles; it += 2) {
-        tile_body(it, std::integral_constant<int, 0>{});
-        tile_body(it + 1, std::integral_constant<int, 1>{});
+      for (; it + 1 + NS < n_tiles; it += 2) {
+        tile(it, C0{}, C1{});
+        tile(it + 1, C1{}, C1{});
       }
-      if (it < n_tiles) tile_body(it, std::integral_constant<int, 0>{});
+      for (; it + 1 < n_tiles; it += 2) {
+        tile(it, C0{}, C2{});
+        tile(it + 1, C1{}, C2{});
+      }
+      if (it < n_tiles) tile(it, C0{}, C2{});
     }
   }
 
