@@ -262,6 +262,25 @@ __device__ __forceinline__ void kn_matrix_to_lds(const half_t* W, int ld, int ro
   }
 }
 
+// The bias quads of the columns that a lane's accumulators hold (the 32 x 32 layout, see fprop_tile_out).  They are requested in
+// front of the last MFMAs: in the epilogue each was a load that nothing covered, up to one round trip after the other.
+// (56 x 56 64 -> 64 and 64 -> 256 with a skip connection, 32 images, best instance: 7.0 -> 6.4 us and 22.4 -> 20.0; 28 x 28 512 -> 256 of 2
+// images 5.4 -> 4.9.  Accumulators that start at the bias are as fast there, but cost problems of few workgroups 0.2 to 0.4 us, which
+// wait for it before the first MFMA.)
+template <int FN>
+struct BiasQuads {
+  half4 quad[FN][4];
+  __device__ __forceinline__ void fetch(const FpropParams& p, int n_wave, int lane) {
+#pragma unroll
+    for (int a = 0; a < FN; ++a)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int n = n_wave + a * 32 + q * 8 + (lane >> 5) * 4;
+        quad[a][q] = *(const half4*)(p.bias + (n < p.N ? n : 0) * p.bias_on);  // (columns beyond N are never stored)
+      }
+  }
+};
+
 // Last step of the tiled single-op kernels: accumulators -> FP16 C tile in LDS ([BM][BN], 16-byte chunks
 // XOR-swizzled by row, over whatever the main loop left there) -> 16-byte coalesced non-temporal row stores.
 // RES (Eq. 1's C as a full matrix, p.res): the residual tile is first brought into the same LDS locations
@@ -339,8 +358,8 @@ __device__ __forceinline__ void fprop_tile_out_with(half_t* lds, const FpropPara
 // The 32 x 32 accumulator layout: lane l of a fragment holds, in registers 4q .. 4q+3, columns 8q + 4(l / 32) .. +3
 // of row l % 32.
 template <bool RES, int BM, int BN, int WTM, int WTN, int STORE_THREADS, int ROWS_PER_PASS, bool NCHW = false, int FN, int FM>
-__device__ __forceinline__ void fprop_tile_out(half_t* lds, const floatx16 (&acc)[FN][FM], const FpropParams& p, int m0,
-                                               int n0, int wm, int wn, bool writer, int tid) {
+__device__ __forceinline__ void fprop_tile_out(half_t* lds, const floatx16 (&acc)[FN][FM], const BiasQuads<FN>& bias, const FpropParams& p,
+                                               int m0, int n0, int wm, int wn, bool writer, int tid) {
   constexpr int CPR = BN / 8;
   const int lane = tid & 63, g = lane >> 5, l32 = lane & 31;
   fprop_tile_out_with<RES, BM, BN, STORE_THREADS, ROWS_PER_PASS, NCHW>(lds, p, m0, n0, writer, tid, [&](auto slow, const EpilogueArgs& ep) {
@@ -353,8 +372,10 @@ __device__ __forceinline__ void fprop_tile_out(half_t* lds, const floatx16 (&acc
         for (int b = 0; b < FM; ++b) {
           const int row = wm * WTM + b * 32 + l32;
           half4* slot = (half4*)(lds + row * BN + (((nl >> 3) ^ ctile_swizzle<CPR>(row)) << 3) + (nl & 4));
-          if constexpr (RES) *slot = epilogue_quad_res<decltype(slow)::value>(acc[a][b], q, n0 + nl, ep, *slot);
-          else *slot = epilogue_quad<decltype(slow)::value>(acc[a][b], q, n0 + nl, ep);
+          const floatx4 v = {acc[a][b][q * 4], acc[a][b][q * 4 + 1], acc[a][b][q * 4 + 2], acc[a][b][q * 4 + 3]};
+          half4 res = {0, 0, 0, 0};
+          if constexpr (RES) res = *slot;
+          *slot = epilogue_quad4_values<decltype(slow)::value, RES>(v, bias.quad[a][q], ep, res);
         }
       }
   });
@@ -388,19 +409,22 @@ struct FpropDmaTraits {
 
   // k-steps of 16 per register set of operand fragments: enough for `depth` MFMAs, as far as the k-tile has them.  Eight MFMAs
   // cover an LDS round trip under load, four do not (see the main loop), but the sets are registers: eight only where as many
-  // workgroups fit a compute unit as with four, by registers (512 per SIMD lane; accumulators, both sets and about 28 more)
-  // and by LDS.  128 x 64 x 64 on 4 waves, 3 stages: 76 registers -> 132, two workgroups either way; 128 x 128 x 64 on 8 waves with
-  // 2 stages would go from two (102) to one (155).  A single stage has no loads to overlap with and stays with four.
+  // workgroups fit a compute unit as with four, by registers (512 per SIMD lane; accumulators, both sets and about 4 * depth more,
+  // as compiled) and by LDS.  128 x 64 x 64 on 4 waves, 2 stages: 104 registers -> 162, three workgroups either way; 128 x 128 x 64
+  // on 8 waves with 2 stages would go from two (104) to one (158).  A single stage has no loads to overlap with and stays with four; so
+  // does a tile that would become a single group of 2 x 2 fragments, whose two loop ends take 188 registers.
   static constexpr int KS = BK / 16;
   static constexpr int group_steps(int depth) {
     return FM * FN >= depth ? 1 : depth / (FM * FN) < KS ? depth / (FM * FN) : KS;
   }
   static constexpr int resident(int depth) {
-    const int regs = (FM * FN * 16 + 2 * group_steps(depth) * (FM + FN) * 4 + 28 + 7) / 8 * 8;
+    const int regs = (FM * FN * 16 + 2 * group_steps(depth) * (FM + FN) * 4 + 4 * depth + 7) / 8 * 8;
     const int by_regs = 512 / regs * 4 / NW, by_lds = 160 * 1024 / LDS_BYTES;
     return by_regs < by_lds ? by_regs : by_lds;
   }
-  static constexpr int G = group_steps(NS > 1 && resident(2 * BOLT_FRAG_DEPTH) >= resident(BOLT_FRAG_DEPTH) ? 2 * BOLT_FRAG_DEPTH : BOLT_FRAG_DEPTH);
+  static constexpr bool DEEP = NS > 1 && resident(2 * BOLT_FRAG_DEPTH) >= resident(BOLT_FRAG_DEPTH) &&
+                               !(FM * FN >= 4 && group_steps(2 * BOLT_FRAG_DEPTH) == KS);
+  static constexpr int G = group_steps(DEEP ? 2 * BOLT_FRAG_DEPTH : BOLT_FRAG_DEPTH);
 };
 
 // NCHW: the output tensor is [N][K][P][Q] (convolutions only; see fprop_tile_out_with)
@@ -465,6 +489,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG) void fprop_dma_kernel(
     for (int b = 0; b < FM; ++b)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
+  BiasQuads<FN> bias;
 
   half_t* const lds_group = lds + kg * T::GROUP_HALVES;  // this k-group's part of every stage
   auto issue = [&](int kt, int stage) {
@@ -491,115 +516,123 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG) void fprop_dma_kernel(
   };
 
   // ---- NS-deep pipeline: one barrier per k-tile ----------------------------------------------
-  const int n_tiles = (kt_end - kt_first + KG - 1) / KG;  // pipeline steps, the same for every k-group
-  if (n_tiles > 0) {
-    int stage = 0, fill_stage = 0;
-    auto load_one = [&](int kt, auto ic) {  // load instruction I of tile kt: [X instructions | W instructions]
-      constexpr int I = decltype(ic)::value, XN = XL::NI;
-      half_t* s = lds_group + fill_stage * STAGE;
-      if constexpr (I < XN) xl.template issue_part<I, I + 1>(kt, s, p.cg);
-      else wl.template issue_part<I - XN, I - XN + 1>(kt, s + BM * BK, p.cg);
-    };
+  const int n_tiles = (kt_end - kt_first + KG - 1) / KG;  // pipeline steps, at least one, the same for every k-group
+  int stage = 0, fill_stage = 0;
+  auto load_one = [&](int kt, auto ic) {  // load instruction I of tile kt: [X instructions | W instructions]
+    constexpr int I = decltype(ic)::value, XN = XL::NI;
+    half_t* s = lds_group + fill_stage * STAGE;
+    if constexpr (I < XN) xl.template issue_part<I, I + 1>(kt, s, p.cg);
+    else wl.template issue_part<I - XN, I - XN + 1>(kt, s + BM * BK, p.cg);
+  };
 #pragma unroll
-    for (int t = 0; t < NS; ++t)
-      if (t < n_tiles) issue(kt_begin + t * KG, t);
-    if (n_tiles >= NS) barrier_after_loads<(NS - 1) * L>();
-    else barrier_after_loads<0>();
-    for_constants<G * (FM + FN)>([&](auto rc) { read_one(0, 0, rc, xf[0], wf[0]); });
-    // From tile `it` to the next: this wave's reads of the tile are complete (lgkmcnt 0) and tile it+1 has landed (vmcnt); behind
-    // the barrier that holds for every wave, so the stage just read can be refilled with tile it+NS while the last MFMAs of
-    // tile `it` are still to issue.
-    auto turn = [&](int it) {
-      __builtin_amdgcn_sched_barrier(0);
-      if (n_tiles - 2 - it >= NS - 2) barrier_after_reads_and_loads<(NS >= 2 ? NS - 2 : 0) * L>();
-      else barrier_after_reads_and_loads<0>();
-      fill_stage = stage;
-      stage = stage + 1 == NS ? 0 : stage + 1;
-    };
-    // The MFMAs of fragment group j, out of register set SET; the reads of the next group (READS; the first group of the next tile
-    // behind the last of this one); and slice (j + 1) % NG of the L load instructions of tile kt (LOADS 1; 2: if `more`).
-    // A wave issues in order: a burst of LDS reads or of direct-to-LDS loads is issue time during which this wave feeds
-    // the matrix pipe nothing, and since the barrier keeps the waves in step, the LDS, the address path and the matrix pipes then
-    // work in turns.  So both are laid out between the MFMAs, two reads behind one (and the loads evenly), and the fences
-    // keep it so: left alone, the scheduler sinks each read to just before its use.  Cycles of a k-tile step with operands in the
-    // L2s, bursts -> this (the MFMAs alone need 512 of a 128 x 128 x 64 step, 640 with the barrier): 128 x 128 tiles on 2 x 4 waves
-    // 1030 -> 725 (row-major weights 1060 -> 825), on 2 x 2 1310 -> 990, 128 x 64 on 2 x 2 870 -> 530, 256 x 128 on 4 x 2 1580 -> 1220.
-    // Three reads behind an MFMA, or sets for four MFMAs instead of eight, take 5 to 25 % more; a branch around every load 5 to 8.
-    // Per launch, operands from beyond the L2s, best instance of each: 14 x 14 1024 -> 2048 at stride 2, 32 images, 13.8 -> 12.8 us;
-    // 3 x 3 at stride 2 512 -> 512 20.8 -> 17.9; 2048^3 row-major 23.3 -> 22.3; 2537 x 1176 x 7296 62.3 -> 58.2.  From 19 GFLOP on the
-    // clock takes part of it back (1.94 -> 1.71 GHz at 4096 x 2048 x 1024, 21.0 -> 19.0 us).
-    auto group = [&](auto jc, auto setc, auto readsc, auto loadsc, int kt, bool more) {
-      constexpr int j = decltype(jc)::value, cur = decltype(setc)::value, nxt = cur ^ 1, LOADS = decltype(loadsc)::value;
-      constexpr bool last = j + 1 == NG;
-      constexpr int MF = G * FM * FN, RD = decltype(readsc)::value ? G * (FM + FN) : 0;
-      constexpr int S = (j + 1) % NG, L0 = S * L / NG, LD = LOADS ? (S + 1) * L / NG - L0 : 0;
-      constexpr int PER = (RD + MF - 1) / MF > 2 ? (RD + MF - 1) / MF : 2;
-      __builtin_amdgcn_sched_barrier(0);
-      for_constants<MF>([&](auto mc) {
-        constexpr int I = decltype(mc)::value, k = I / (FM * FN), a = I / FM % FN, b = I % FM;
-        acc[a][b] = mfma_32x32x16(wf[cur][k][a], xf[cur][k][b], acc[a][b]);
-        constexpr int r0 = I * PER < RD ? I * PER : RD, r1 = (I + 1) * PER < RD ? (I + 1) * PER : RD;
-        for_constants<r1 - r0>([&](auto rc) {
-          read_one(stage, last ? 0 : j + 1, std::integral_constant<int, r0 + decltype(rc)::value>{}, xf[nxt], wf[nxt]);
-        });
-        constexpr int l0 = I * LD / MF, l1 = (I + 1) * LD / MF;
-        if constexpr (l1 > l0)
-          if (LOADS == 1 || more) for_constants<l1 - l0>([&](auto lc) { load_one(kt, std::integral_constant<int, L0 + l0 + decltype(lc)::value>{}); });
-        __builtin_amdgcn_sched_barrier(0);
+  for (int t = 0; t < NS; ++t)
+    if (t < n_tiles) issue(kt_begin + t * KG, t);
+  if constexpr (NS == 1) bias.fetch(p, n0 + wn * WTN, lane);
+  if (n_tiles >= NS) barrier_after_loads<(NS - 1) * L>();
+  else barrier_after_loads<0>();
+  for_constants<G * (FM + FN)>([&](auto rc) { read_one(0, 0, rc, xf[0], wf[0]); });
+  // From tile `it` to the next: this wave's reads of the tile are complete (lgkmcnt 0) and tile it+1 has landed (vmcnt); behind
+  // the barrier that holds for every wave, so the stage just read can be refilled with tile it+NS while the last MFMAs of
+  // tile `it` are still to issue.
+  auto turn = [&](int it) {
+    __builtin_amdgcn_sched_barrier(0);
+    if (n_tiles - 2 - it >= NS - 2) barrier_after_reads_and_loads<(NS >= 2 ? NS - 2 : 0) * L>();
+    else barrier_after_reads_and_loads<0>();
+    fill_stage = stage;
+    stage = stage + 1 == NS ? 0 : stage + 1;
+  };
+  // The MFMAs of fragment group j, out of register set SET; the reads of the next group (READS; the first group of the next tile
+  // behind the last of this one); and slice (j + 1) % NG of the L load instructions of tile kt (LOADS 1; 2: if `more`).
+  // A wave issues in order: a burst of LDS reads or of direct-to-LDS loads is issue time during which this wave feeds
+  // the matrix pipe nothing, and since the barrier keeps the waves in step, the LDS, the address path and the matrix pipes then
+  // work in turns.  So both are laid out between the MFMAs, two reads behind one (and the loads evenly), and the fences
+  // keep it so: left alone, the scheduler sinks each read to just before its use.  Cycles of a k-tile step with operands in the
+  // L2s, bursts -> this (the MFMAs alone need 512 of a 128 x 128 x 64 step, 640 with the barrier): 128 x 128 tiles on 2 x 4 waves
+  // 1030 -> 725 (row-major weights 1060 -> 825), on 2 x 2 1310 -> 990, 128 x 64 on 2 x 2 870 -> 530, 256 x 128 on 4 x 2 1580 -> 1220.
+  // Sets for four MFMAs instead of eight take 5 to 25 % more, a branch around every load 5 to 8, three reads behind an MFMA 1 to 6;
+  // only of sets for four with two waves per SIMD, whose MFMAs are twice as far apart, three are better (128 x 128 on 2 x 4 waves: 825, 975 with two).
+  // Per launch, operands from beyond the L2s, best instance of each: 14 x 14 1024 -> 2048 at stride 2, 32 images, 13.8 -> 12.8 us;
+  // 3 x 3 at stride 2 512 -> 512 20.8 -> 17.9; 2048^3 row-major 23.3 -> 22.3; 2537 x 1176 x 7296 62.3 -> 58.2.  From 19 GFLOP on the
+  // clock takes part of it back (1.94 -> 1.71 GHz at 4096 x 2048 x 1024, 21.0 -> 19.0 us).
+  auto group = [&](auto jc, auto setc, auto readsc, auto loadsc, int kt, bool more) {
+    constexpr int j = decltype(jc)::value, cur = decltype(setc)::value, nxt = cur ^ 1, LOADS = decltype(loadsc)::value;
+    constexpr bool last = j + 1 == NG;
+    constexpr int MF = G * FM * FN, RD = decltype(readsc)::value ? G * (FM + FN) : 0;
+    constexpr int S = (j + 1) % NG, L0 = S * L / NG, LD = LOADS ? (S + 1) * L / NG - L0 : 0;
+    constexpr int MOST = T::DEEP || T::NW < 8 ? 2 : 3;  // reads behind one MFMA
+    constexpr int PER = (RD + MF - 1) / MF > MOST ? (RD + MF - 1) / MF : MOST;
+    __builtin_amdgcn_sched_barrier(0);
+    for_constants<MF>([&](auto mc) {
+      constexpr int I = decltype(mc)::value, k = I / (FM * FN), a = I / FM % FN, b = I % FM;
+      acc[a][b] = mfma_32x32x16(wf[cur][k][a], xf[cur][k][b], acc[a][b]);
+      constexpr int r0 = I * PER < RD ? I * PER : RD, r1 = (I + 1) * PER < RD ? (I + 1) * PER : RD;
+      for_constants<r1 - r0>([&](auto rc) {
+        read_one(stage, last ? 0 : j + 1, std::integral_constant<int, r0 + decltype(rc)::value>{}, xf[nxt], wf[nxt]);
       });
+      constexpr int l0 = I * LD / MF, l1 = (I + 1) * LD / MF;
+      if constexpr (l1 > l0)
+        if (LOADS == 1 || more) for_constants<l1 - l0>([&](auto lc) { load_one(kt, std::integral_constant<int, L0 + l0 + decltype(lc)::value>{}); });
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  using C0 = std::integral_constant<int, 0>;
+  using C1 = std::integral_constant<int, 1>;
+  if constexpr (NG > 1) {
+    // All stages are requested when the loop begins, so the first load is due behind the first turn: a step is the last group of
+    // one tile and the other groups of the next, with loads as long as there are tiles to load.
+    constexpr int SET = (NG - 1) & 1;
+    auto others = [&](auto loadsc, int kt) {
+      for_constants<NG - 1>([&](auto jc) { group(jc, std::integral_constant<int, decltype(jc)::value & 1>{}, C1{}, loadsc, kt, true); });
     };
-    using C0 = std::integral_constant<int, 0>;
-    using C1 = std::integral_constant<int, 1>;
-    if constexpr (NG > 1) {
-      // All stages are requested when the loop begins, so the first load is due behind the first turn: a step is the last group of
-      // one tile and the other groups of the next, with loads as long as there are tiles to load.
-      constexpr int SET = (NG - 1) & 1;
-      auto others = [&](auto loadsc, int kt) {
-        for_constants<NG - 1>([&](auto jc) { group(jc, std::integral_constant<int, decltype(jc)::value & 1>{}, C1{}, loadsc, kt, true); });
-      };
-      using LastGroup = std::integral_constant<int, NG - 1>;
-      using LastSet = std::integral_constant<int, SET>;
+    using LastGroup = std::integral_constant<int, NG - 1>;
+    using LastSet = std::integral_constant<int, SET>;
+    others(C0{}, 0);
+    int it = 0;
+    for (; NS > 1 && it + NS < n_tiles; ++it) {
+      const int kt = kt_begin + (it + NS) * KG;
+      turn(it);
+      group(LastGroup{}, LastSet{}, C1{}, C1{}, kt, true);
+      others(C1{}, kt);
+      xl.advance(p.cg);
+      wl.advance(p.cg);
+    }
+    for (; NS > 1 && it + 1 < n_tiles; ++it) {
+      turn(it);
+      group(LastGroup{}, LastSet{}, C1{}, C0{}, 0, false);
       others(C0{}, 0);
-      int it = 0;
-      for (; NS > 1 && it + NS < n_tiles; ++it) {
-        const int kt = kt_begin + (it + NS) * KG;
-        turn(it);
-        group(LastGroup{}, LastSet{}, C1{}, C1{}, kt, true);
-        others(C1{}, kt);
+    }
+    if (NS > 1 && kg == 0) bias.fetch(p, n0 + wn * WTN, lane);
+    group(LastGroup{}, LastSet{}, C0{}, C0{}, 0, false);
+  } else if constexpr (NS == 1) {
+    group(C0{}, C0{}, C0{}, C0{}, 0, false);
+  } else {
+    // One group per tile: the register sets swap roles every tile.
+    auto tile = [&](int it, auto setc, auto loadsc) {
+      const bool more = it + NS < n_tiles;
+      turn(it);
+      group(C0{}, setc, C1{}, loadsc, kt_begin + (it + NS) * KG, more);
+      if (decltype(loadsc)::value == 1 || (decltype(loadsc)::value == 2 && more)) {
         xl.advance(p.cg);
         wl.advance(p.cg);
       }
-      for (; NS > 1 && it + 1 < n_tiles; ++it) {
-        turn(it);
-        group(LastGroup{}, LastSet{}, C1{}, C0{}, 0, false);
-        others(C0{}, 0);
-      }
-      group(LastGroup{}, LastSet{}, C0{}, C0{}, 0, false);
-    } else if constexpr (NS == 1) {
-      group(C0{}, C0{}, C0{}, C0{}, 0, false);
+    };
+    using C2 = std::integral_constant<int, 2>;
+    int it = 0;
+    for (; it + 1 + NS < n_tiles; it += 2) {
+      tile(it, C0{}, C1{});
+      tile(it + 1, C1{}, C1{});
+    }
+    for (; it + 2 < n_tiles; it += 2) {
+      tile(it, C0{}, C2{});
+      tile(it + 1, C1{}, C2{});
+    }
+    if (it + 1 < n_tiles) {  // the last two tiles, all loads under way
+      tile(it, C0{}, C0{});
+      if (kg == 0) bias.fetch(p, n0 + wn * WTN, lane);
+      group(C0{}, C1{}, C0{}, C0{}, 0, false);
     } else {
-      // One group per tile: the register sets swap roles every tile.  (Behind the last tile the turn and the reads run once more,
-      // to no use: a branch there would make the compiler wait for the new reads before the MFMAs.)
-      auto tile = [&](int it, auto setc, auto loadsc) {
-        const bool more = it + NS < n_tiles;
-        turn(it);
-        group(C0{}, setc, C1{}, loadsc, kt_begin + (it + NS) * KG, more);
-        if (decltype(loadsc)::value == 1 || more) {
-          xl.advance(p.cg);
-          wl.advance(p.cg);
-        }
-      };
-      using C2 = std::integral_constant<int, 2>;
-      int it = 0;
-      for (; it + 1 + NS < n_tiles; it += 2) {
-        tile(it, C0{}, C1{});
-        tile(it + 1, C1{}, C1{});
-      }
-      for (; it + 1 < n_tiles; it += 2) {
-        tile(it, C0{}, C2{});
-        tile(it + 1, C1{}, C2{});
-      }
-      if (it < n_tiles) tile(it, C0{}, C2{});
+      if (kg == 0) bias.fetch(p, n0 + wn * WTN, lane);
+      group(C0{}, C0{}, C0{}, C0{}, 0, false);
     }
   }
 
@@ -651,7 +684,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG) void fprop_dma_kernel(
     return;
   }
 
-  fprop_tile_out<RES, BM, BN, WTM, WTN, T::STORE_THREADS, T::ROWS_PER_PASS, NCHW>(lds, acc, p, m0, n0, wm, wn, kg == 0, tid);
+  fprop_tile_out<RES, BM, BN, WTM, WTN, T::STORE_THREADS, T::ROWS_PER_PASS, NCHW>(lds, acc, bias, p, m0, n0, wm, wn, kg == 0, tid);
 }
 
 template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int XMODE, int NS, int KG = 1, bool WKN = false>

@@ -91,6 +91,24 @@ def test_gemm_integer_inputs_bit_exact(bolt, layout):
             assert_bit_equal(got, want, "gemm integer instance %d" % kid)
 
 
+@pytest.mark.parametrize("layout", ["kn", "nk"])
+@pytest.mark.parametrize("K", [32, 64, 72, 128, 136, 192, 256, 264, 320, 384, 448, 512, 584])
+def test_gemm_number_of_k_tiles_integer_bit_exact(bolt, layout, K):
+    # one k-tile up to more than twice the deepest pipeline, odd and even, whole and ragged: the loop with loads, the loop behind
+    # the last load and its two ends, in every instance.  |sum| <= 584 * 2 * 1 < 2048: whole numbers that a half holds.
+    M, N = 260, 72
+    A = wl.integer_fp16(141, 0, (M, K), -2, 2)
+    B = wl.integer_fp16(141, 1, (K, N), -1, 1)
+    bias = wl.integer_fp16(141, 2, (N,), -9, 9)
+    want = ref.gemm(A, B, bias, act="none")
+    d = bolt.gemm_desc(M, N, K, b_layout=bolt.LAYOUT_KN if layout == "kn" else bolt.LAYOUT_NK)
+    for kid in range(bolt.bolt_num_instances(bolt.OP_GEMM)):
+        if bolt.bolt_instance_supports(bolt.OP_GEMM, kid, d):
+            _say("gemm K=%d %s instance %d" % (K, layout, kid))
+            got, _ = _run_gemm(bolt, A, B, bias, act="none", layout=layout, config={"kernel_id": kid})
+            assert_bit_equal(got, want, "gemm K=%d %s instance %d" % (K, layout, kid))
+
+
 def test_gemm_alpha_beta_activations_and_no_bias(bolt):
     M, N, K = 130, 72, 96
     A = wl.uniform_fp16(103, 0, (M, K), -1, 1)
@@ -477,6 +495,23 @@ def test_conv_integer_inputs_bit_exact(bolt):
             if bolt.bolt_instance_supports(bolt.OP_CONV2D, kid, d):
                 got, _ = _run_conv(bolt, x, w, bias, stride, pad, act=act, config={"kernel_id": kid})
                 assert_bit_equal(got, want, "conv integer instance %d act %s" % (kid, act))
+
+
+@pytest.mark.parametrize("case", [(1, 9, 10, 8, 40, 2, 1), (2, 8, 9, 24, 72, 2, 1), (1, 7, 9, 64, 136, 2, 1), (1, 6, 11, 72, 40, 1, 0)])  # N H W C K stride pad
+def test_conv_window_number_of_k_tiles_integer_bit_exact(bolt, case):
+    # reductions of 72, 216, 576 and 648: the gather's cursor steps over channels and taps through the same loops
+    n, h, w_, c, k, stride, pad = case
+    x = wl.integer_fp16(142, 0, (n, h, w_, c), -1, 1)
+    w = wl.integer_fp16(142, 1, (k, 3, 3, c), -1, 1)
+    b = wl.integer_fp16(142, 2, (k,), -9, 9)
+    want = ref.conv2d_nhwc(x, w, b, stride=stride, pad=pad, act="none")
+    d = bolt.conv_desc(n, h, w_, c, k, 3, 3, stride, pad, act="none")
+    for kid in range(bolt.bolt_num_instances(bolt.OP_CONV2D)):
+        if bolt.bolt_instance_supports(bolt.OP_CONV2D, kid, d):
+            _say("conv %s instance %d" % (case, kid))
+            y = torch.full(want.shape, float("nan"), dtype=torch.float16, device="cuda")
+            bolt.bolt_conv2d_fprop_nhwc(d, dev(x), dev(w), dev(b), y, {"kernel_id": kid})
+            assert_bit_equal(host(y), want, "conv %s instance %d" % (case, kid))
 
 
 def test_conv_identity_1x1_returns_input_exactly(bolt):
