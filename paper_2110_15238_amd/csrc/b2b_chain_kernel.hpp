@@ -45,10 +45,11 @@ __global__ __launch_bounds__(64 * NW) void b2b_chain_kernel(const B2bParams p) {
   b2b_issue_weights<N2T, N1T, NW, WKN>(p.W2, p.ldw2, p.N2, p.N1, W2s, p.cg, wave, lane);
 
   floatx16 acc0[N0T / 32][FM];
-  b2b_dma_op0<BM, BK, NW, N0T, XMODE, NS, WKN>(p, lds, m0, wave, lane, acc0);
+  BiasQuads<N0T / 32> bias0;
+  b2b_dma_op0<BM, BK, NW, N0T, XMODE, NS, T::LDS_BYTES, WKN>(p, lds, m0, wave, lane, acc0, bias0);
 
   half8 d0[N0T / 16][FM];
-  b2b_make_d<N0T / 32, FM>(EpilogueArgs{p.b0, p.b0_on, p.N0, p.alpha0, p.beta0, p.act0}, acc0, d0, g);
+  b2b_make_d<N0T / 32, FM>(EpilogueArgs{p.b0, p.b0_on, p.N0, p.alpha0, p.beta0, p.act0}, bias0, acc0, d0, g);
   floatx16 acc1[N1T / 32][FM];
   b2b_rf_gemm<N0T, N1T, FM, WKN>(W1s, d0, acc1, l32, g);
 

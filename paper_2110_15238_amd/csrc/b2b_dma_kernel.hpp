@@ -54,22 +54,33 @@ __device__ __forceinline__ void b2b_issue_weights(const half_t* W, int ld, int n
   for (int kt = 0; kt < NKT; ++kt) wl.issue(kt, Ws + kt * NOUT_T * KB, cg);
 }
 
-// op0: acc0 = X tile (GEMM rows or implicit im2col) x W0^T over K0, NS-deep direct-to-LDS pipeline with the
-// fragments double-buffered across the k-tile barrier.  On return every load this wave has issued, the
-// resident weights of the later ops included, has landed (the loop's final wait is vmcnt 0).
+// k-steps per register set of op0's operand fragments (see dma_main_loop): enough for eight MFMAs if the registers that the
+// workgroups sharing a compute unit by LDS leave each other hold that, else for four, else one.
+template <int BM, int BK, int NW, int N0T, int LDS_BYTES>
+struct B2bOp0Steps {
+  static constexpr int FM = BM / NW / 32, FN = N0T / 32, KS = BK / 16;
+  static constexpr int PER_SIMD = (160 * 1024 / LDS_BYTES * NW + 3) / 4;
+  static constexpr int steps(int depth) { return FM * FN >= depth ? 1 : depth / (FM * FN) < KS ? depth / (FM * FN) : KS; }
+  static constexpr bool fits(int depth) {
+    return FM * FN * 16 + 2 * steps(depth) * (FM + FN) * 4 + 48 <= (PER_SIMD > 2 ? 512 / PER_SIMD / 8 * 8 : 256);
+  }
+  static constexpr int G = fits(2 * BOLT_FRAG_DEPTH) ? steps(2 * BOLT_FRAG_DEPTH) : fits(BOLT_FRAG_DEPTH) ? steps(BOLT_FRAG_DEPTH) : 1;
+};
+
+// op0: acc0 = X tile (GEMM rows or implicit im2col) x W0^T over K0, the pipeline of dma_main_loop: a workgroup has its SIMDs nearly to itself (the resident
+// weights take the LDS), so what its own MFMAs don't cover nobody covers.  (Reads and loads between the MFMAs instead of in front of them,
+// best instance: 4096 x 256 -> 128 -> 64 7.5 -> 7.0 us, 32768 x 576 -> 128 -> 64 13.2 -> 13.0, 9896 x 432 -> 24 -> 88 -> 48 9.5 -> 8.3;
+// 3 x 3 convolution of 128 channels to 64 with stride 2 at 56 x 56 and a 1 x 1 to 128, 32 images, 16.8 -> 14.6.)  On return every load this
+// wave has issued, the resident weights of the later ops included, has landed, but for `bias`: op0's, on its way.
 // WKN: W0 is row-major [K0][N0]; its k-tiles go to LDS as they lie in memory and are read with the LDS
 // transpose read (DmaKnTileLoader).
-template <int BM, int BK, int NW, int N0T, int XMODE, int NS, bool WKN = false>
+template <int BM, int BK, int NW, int N0T, int XMODE, int NS, int LDS_BYTES, bool WKN = false>
 __device__ __forceinline__ void b2b_dma_op0(const B2bParams& p, half_t* lds, int m0, int wave, int lane,
-                                            floatx16 (&acc0)[N0T / 32][BM / NW / 32]) {
-  constexpr int WTM = BM / NW, FM = WTM / 32, FN0 = N0T / 32, STAGE = (BM + N0T) * BK, KS = BK / 16;
+                                            floatx16 (&acc0)[N0T / 32][BM / NW / 32], BiasQuads<N0T / 32>& bias) {
+  constexpr int FM = BM / NW / 32, FN0 = N0T / 32;
   using XL = DmaTileLoader<BM, BK, NW, XMODE>;
   using WL = std::conditional_t<WKN, DmaKnTileLoader<BK, N0T, NW>, DmaTileLoader<N0T, BK, NW, 0>>;
-  constexpr int L = XL::NI + WL::NI;
-  static_assert((NS - 1) * L < 64, "vmcnt range");
-  static_assert(KS % 2 == 0, "fragment double buffering");
-  const int g = lane >> 5, l32 = lane & 31;
-  const int n_tiles = (p.K0 + BK - 1) / BK;
+  static_assert(NS > 1, "the last wait of the loop covers the resident weights");
   XL xl;
   WL wl;
   if constexpr (XMODE == 0) {
@@ -80,11 +91,8 @@ __device__ __forceinline__ void b2b_dma_op0(const B2bParams& p, half_t* lds, int
     const int64_t bytes = (int64_t)p.cg.H * p.cg.Wi * p.cg.C * 2 * (int64_t)(p.M / (p.cg.P * p.cg.Q));
     xl.init(p.X, (unsigned)bytes, 0, p.M - m0, p.K0, p.cg, m0, 0, wave, lane);
   }
-  int w0off[WKN ? FN0 : 1];
   if constexpr (WKN) {
     wl.init(p.W0, (unsigned)(((p.K0 - 1) * p.ldw0 + p.N0) * 2), p.ldw0, p.N0, p.K0, wave, lane);  // (under 2 GiB: host check)
-#pragma unroll
-    for (int a = 0; a < FN0; ++a) w0off[a] = kn_frag_offset<N0T>(a * 32, lane);
   } else {
     const int64_t bytes = ((int64_t)(p.N0 - 1) * p.ldw0 + p.K0) * 2;
     wl.init(p.W0, (unsigned)(bytes < 0x7fffffff ? bytes : 0x7fffffff), p.ldw0, p.N0, p.K0, p.cg, 0, 0, wave, lane);
@@ -95,52 +103,8 @@ __device__ __forceinline__ void b2b_dma_op0(const B2bParams& p, half_t* lds, int
     for (int b = 0; b < FM; ++b)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc0[a][b][r] = 0.f;
-
-  auto issue = [&](int kt, int stage) {
-    half_t* s = lds + stage * STAGE;
-    xl.issue(kt, s, p.cg);
-    wl.issue(kt, s + BM * BK, p.cg);
-  };
-  half8 xf[2][FM], wf[2][FN0];
-  auto read_frags = [&](int stage, int ks, half8 (&x)[FM], half8 (&w)[FN0]) {
-    const half_t* xs = lds + stage * STAGE;
-    const half_t* ws = xs + BM * BK;
-    const int chunk = ks * 2 + g;
-#pragma unroll
-    for (int b = 0; b < FM; ++b) x[b] = *(const half8*)(xs + dma_chunk_offset<BK>(wave * WTM + b * 32 + l32, chunk));
-#pragma unroll
-    for (int a = 0; a < FN0; ++a) {
-      if constexpr (WKN) w[a] = kn_frag_read<N0T>(ws, w0off[a], ks * 16);
-      else w[a] = *(const half8*)(ws + dma_chunk_offset<BK>(a * 32 + l32, chunk));
-    }
-  };
-#pragma unroll
-  for (int s = 0; s < NS; ++s)
-    if (s < n_tiles) issue(s, s);
-  if (n_tiles >= NS) barrier_after_loads<(NS - 1) * L>();
-  else barrier_after_loads<0>();
-  read_frags(0, 0, xf[0], wf[0]);
-  int stage = 0;
-  for (int it = 0; it < n_tiles; ++it) {
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      if (ks + 1 < KS) {
-        read_frags(stage, ks + 1, xf[(ks + 1) & 1], wf[(ks + 1) & 1]);
-      } else {
-        __builtin_amdgcn_sched_barrier(0);
-        if (n_tiles - 2 - it >= NS - 2) barrier_after_reads_and_loads<(NS - 2) * L>();
-        else barrier_after_reads_and_loads<0>();
-        if (it + NS < n_tiles) issue(it + NS, stage);
-        stage = stage + 1 == NS ? 0 : stage + 1;
-        read_frags(stage, 0, xf[0], wf[0]);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-#pragma unroll
-      for (int a = 0; a < FN0; ++a)
-#pragma unroll
-        for (int b = 0; b < FM; ++b) acc0[a][b] = mfma_32x32x16(wf[ks & 1][a], xf[ks & 1][b], acc0[a][b]);
-    }
-  }
+  dma_main_loop<BM, N0T, BK, NW, 1, NS, 1, B2bOp0Steps<BM, BK, NW, N0T, LDS_BYTES>::G, 2, WKN>(
+      xl, wl, lds, p.cg, 0, (p.K0 + BK - 1) / BK, wave, 0, lane, acc0, [&] { bias.fetch(p.b0, p.b0_on, p.N0, 0, lane); });
 }
 
 // A later op entirely out of registers and LDS: acc[NOUT_T columns] = d (FP16 fragments of the previous
@@ -269,11 +233,12 @@ __global__ __launch_bounds__(64 * NW, (B2bDmaTraits<BM, BK, NW, N0T, N1T, XMODE,
   b2b_issue_weights<N1T, N0T, NW, WKN>(p.W1, p.ldw1, p.N1, p.N0, W1s, p.cg, wave, lane);
 
   floatx16 acc0[FN0][FM];
-  b2b_dma_op0<BM, BK, NW, N0T, XMODE, NS, WKN>(p, lds, m0, wave, lane, acc0);
+  BiasQuads<FN0> bias0;
+  b2b_dma_op0<BM, BK, NW, N0T, XMODE, NS, T::LDS_BYTES, WKN>(p, lds, m0, wave, lane, acc0, bias0);
 
   // epilogue0 in registers: accumulators -> FP16 B-operand fragments of op1 (b2b_make_d0)
   half8 d0[FN0 * 2][FM];
-  b2b_make_d0<FN0, FM>(p, acc0, d0, g);
+  b2b_make_d<FN0, FM>(EpilogueArgs{p.b0, p.b0_on, p.N0, p.alpha0, p.beta0, p.act0}, bias0, acc0, d0, g);
 
   // op1: all N1 columns accumulate in registers
   floatx16 acc1[FN1][FM];

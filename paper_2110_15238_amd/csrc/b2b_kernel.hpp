@@ -102,9 +102,10 @@ __device__ __forceinline__ void b2b_preload_weights(const B2bParams& p, half_t* 
 // op1.  Step t = 2a + h of op1 reduces over D0 columns [32a + 16h, 32a + 16h + 16): lane group g
 // holds columns 32a+16h+4g+{0..3} (accumulator quad 2h) and 32a+16h+8+4g+{0..3} (quad 2h+1), and the
 // W1 fragment reads apply the same permutation of the reduction index.  Columns >= N0 become 0.
-template <int FN0, int FM>
-__device__ __forceinline__ void b2b_make_d(const EpilogueArgs& ep, const floatx16 (&acc0)[FN0][FM], half8 (&d0)[FN0 * 2][FM],
-                                           int g) {
+// ``bias(a, q)`` is the bias quad of columns 32a + 8q + 4g.
+template <int FN0, int FM, typename Bias>
+__device__ __forceinline__ void b2b_make_d(const EpilogueArgs& ep, Bias&& bias, const floatx16 (&acc0)[FN0][FM],
+                                           half8 (&d0)[FN0 * 2][FM], int g) {
   auto make = [&](auto slow) {
 #pragma unroll
     for (int a = 0; a < FN0; ++a)
@@ -113,9 +114,12 @@ __device__ __forceinline__ void b2b_make_d(const EpilogueArgs& ep, const floatx1
         const int c0 = a * 32 + h * 16 + g * 4;
 #pragma unroll
         for (int b = 0; b < FM; ++b) {
-          half4 lo = epilogue_quad<decltype(slow)::value>(acc0[a][b], 2 * h, c0, ep);
-          half4 hi = epilogue_quad<decltype(slow)::value>(acc0[a][b], 2 * h + 1, c0 + 8, ep);
           const half4 z = {0, 0, 0, 0};
+          auto quad = [&](int q) {
+            const floatx4 v = {acc0[a][b][q * 4], acc0[a][b][q * 4 + 1], acc0[a][b][q * 4 + 2], acc0[a][b][q * 4 + 3]};
+            return epilogue_quad4_values<decltype(slow)::value, false>(v, bias(a, q), ep, z);
+          };
+          half4 lo = quad(2 * h), hi = quad(2 * h + 1);
           if (c0 >= ep.N) lo = z;
           if (c0 + 8 >= ep.N) hi = z;
           const half8 d = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
@@ -125,6 +129,13 @@ __device__ __forceinline__ void b2b_make_d(const EpilogueArgs& ep, const floatx1
   };
   if (ep.act > ACT_RELU) make(std::true_type{});
   else make(std::false_type{});
+}
+template <int FN0, int FM>
+__device__ __forceinline__ void b2b_make_d(const EpilogueArgs& ep, const floatx16 (&acc0)[FN0][FM], half8 (&d0)[FN0 * 2][FM], int g) {
+  b2b_make_d<FN0, FM>(ep, [&](int a, int q) {
+    const int n = a * 32 + q * 8 + g * 4;
+    return *(const half4*)(ep.bias + (n < ep.N ? n : 0) * ep.bias_on);
+  }, acc0, d0, g);
 }
 template <int FN0, int FM>
 __device__ __forceinline__ void b2b_make_d0(const B2bParams& p, const floatx16 (&acc0)[FN0][FM], half8 (&d0)[FN0 * 2][FM],
@@ -322,8 +333,10 @@ struct B2bLdsTraits {
   }
 };
 
+// (Wide second op: the compiler is kept from saving registers for a fourth wave per SIMD, for which it would read LDS in smaller
+// portions: 4344 x 104 -> 8 -> 56 on 64 x 64 tiles 4.85 us with three waves, 5.26 with four.)
 template <int BM, int BK, int WM0, int WN0, int WM1, int WN1, int N0T, int N1T, int XMODE, int WMODE, bool RES = false>
-__global__ __launch_bounds__(64 * WM0 * WN0) void b2b_lds_kernel(const B2bParams p) {
+__global__ __launch_bounds__(64 * WM0 * WN0) __attribute__((amdgpu_waves_per_eu(1, N1T > 64 ? 3 : 8))) void b2b_lds_kernel(const B2bParams p) {
   using T = B2bLdsTraits<BM, BK, WM0, WN0, WM1, WN1, N0T, N1T, XMODE, WMODE>;
   constexpr int NT = T::NT, FM0 = T::FM0, FN0 = T::FN0, FM1 = T::FM1, FN1 = T::FN1;
   constexpr int WTM0 = T::WTM0, WTN0 = T::WTN0, WTM1 = T::WTM1, WTN1 = T::WTN1;

@@ -208,6 +208,26 @@ __device__ __forceinline__ half4 epilogue_quad_res(const floatx16& acc, int q, i
   return epilogue_quad_impl<SLOW, true>(acc, q, n, ep, res);
 }
 
+// The bias quads of the columns that a lane's accumulators hold (the 32 x 32 layout: registers 4q .. 4q + 3 of fragment a are columns 32a + 8q + 4(lane / 32) .. + 3).  They are requested in
+// front of the last MFMAs: in the epilogue each was a load that nothing covered, up to one round trip after the other.
+// (56 x 56 64 -> 64 and 64 -> 256 with a skip connection, 32 images, best instance: 7.0 -> 6.4 us and 22.4 -> 20.0; 28 x 28 512 -> 256 of 2
+// images 5.4 -> 4.9.  Accumulators that start at the bias are as fast there, but cost problems of few workgroups 0.2 to 0.4 us, which
+// wait for it before the first MFMA.)
+template <int FN>
+struct BiasQuads {
+  half4 quad[FN][4];
+  __device__ __forceinline__ const half4& operator()(int a, int q) const { return quad[a][q]; }
+  __device__ __forceinline__ void fetch(const half_t* bias, int bias_on, int N, int n_wave, int lane) {
+#pragma unroll
+    for (int a = 0; a < FN; ++a)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int n = n_wave + a * 32 + q * 8 + (lane >> 5) * 4;
+        quad[a][q] = *(const half4*)(bias + (n < N ? n : 0) * bias_on);  // (columns beyond N: what the first ones have)
+      }
+  }
+};
+
 // XOR term of the FP16 C tile staged in LDS ([rows][BN], 16-byte chunks): physical chunk = chunk ^ term(row).
 // The term walks through all 16 bank groups (256 bytes) over 16 consecutive rows whatever the row length,
 // so the 8-byte accumulator-quad writes of 32 rows conflict two ways (rows r and r + 16) instead of four, and

@@ -344,7 +344,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG) void conv_halo_kernel(
 
   // ---- epilogue: registers -> FP16 C tile in LDS -> coalesced stores (fprop_dma_kernel.hpp) ----------------
   BiasQuads<FN> bias;
-  bias.fetch(p, n0 + wn * WTN, lane);
+  bias.fetch(p.bias, p.bias_on, p.N, n0 + wn * WTN, lane);
   fprop_tile_out<RES, BM, BN, WTM, WTN, T_::STORE_THREADS, T_::ROWS_PER_PASS>(lds, acc, bias, p, m0, n0, wm, wn, kg == 0, tid);
 }
 

@@ -262,25 +262,6 @@ __device__ __forceinline__ void kn_matrix_to_lds(const half_t* W, int ld, int ro
   }
 }
 
-// The bias quads of the columns that a lane's accumulators hold (the 32 x 32 layout, see fprop_tile_out).  They are requested in
-// front of the last MFMAs: in the epilogue each was a load that nothing covered, up to one round trip after the other.
-// (56 x 56 64 -> 64 and 64 -> 256 with a skip connection, 32 images, best instance: 7.0 -> 6.4 us and 22.4 -> 20.0; 28 x 28 512 -> 256 of 2
-// images 5.4 -> 4.9.  Accumulators that start at the bias are as fast there, but cost problems of few workgroups 0.2 to 0.4 us, which
-// wait for it before the first MFMA.)
-template <int FN>
-struct BiasQuads {
-  half4 quad[FN][4];
-  __device__ __forceinline__ void fetch(const FpropParams& p, int n_wave, int lane) {
-#pragma unroll
-    for (int a = 0; a < FN; ++a)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int n = n_wave + a * 32 + q * 8 + (lane >> 5) * 4;
-        quad[a][q] = *(const half4*)(p.bias + (n < p.N ? n : 0) * p.bias_on);  // (columns beyond N are never stored)
-      }
-  }
-};
-
 // Last step of the tiled single-op kernels: accumulators -> FP16 C tile in LDS ([BM][BN], 16-byte chunks
 // XOR-swizzled by row, over whatever the main loop left there) -> 16-byte coalesced non-temporal row stores.
 // RES (Eq. 1's C as a full matrix, p.res): the residual tile is first brought into the same LDS locations
@@ -427,87 +408,41 @@ struct FpropDmaTraits {
   static constexpr int G = group_steps(DEEP ? 2 * BOLT_FRAG_DEPTH : BOLT_FRAG_DEPTH);
 };
 
-// NCHW: the output tensor is [N][K][P][Q] (convolutions only; see fprop_tile_out_with)
-// WKN: the weights are row-major [K][N] (GEMM only), see DmaKnTileLoader.
-template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int XMODE, int NS, int KG = 1, bool RES = false, bool NCHW = false,
-          bool WKN = false>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG) void fprop_dma_kernel(const FpropParams p) {
-  using T = FpropDmaTraits<BM, BN, BK, WAVES_M, WAVES_N, XMODE, NS, KG>;
-  constexpr int WPG = T::WPG, WTM = T::WTM, WTN = T::WTN, FM = T::FM, FN = T::FN;
-  constexpr int STAGE = T::STAGE_HALVES;
-  using XL = DmaTileLoader<BM, BK, WPG, XMODE, KG>;
-  using WL = std::conditional_t<WKN, DmaKnTileLoader<BK, BN, WPG>, DmaTileLoader<BN, BK, WPG, 0, KG>>;
-  static_assert(!WKN || XMODE == 0, "row-major weights: GEMM only");
+// The main loop of a workgroup (of a k-group: of KG sets of WAVES_M x WAVES_N waves each takes k-tiles kt_begin, kt_begin + KG, ...)
+// over a BM x BN tile: n_tiles steps, at least one, through NS stages at `stages`, KG * (BM + BN) * BK halves apart.  `acc` holds this
+// wave's part on top of what it held.  Every load that the wave has requested has landed behind the last step, but for those of
+// `before_last`, which is called in front of the last MFMAs.
+// G: k-steps of 16 per register set of operand fragments; MOST: LDS reads behind one MFMA.
+template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int NS, int KG, int G, int MOST, bool WKN, typename XL, typename WL, int FM, int FN,
+          typename BeforeLast>
+__device__ __forceinline__ void dma_main_loop(XL& xl, WL& wl, half_t* stages, const ConvGeom& cg, int kt_begin, int n_tiles, int wm, int wn, int lane,
+                                              floatx16 (&acc)[FN][FM], BeforeLast&& before_last) {
+  constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N, STAGE = KG * (BM + BN) * BK;
+  static_assert(WTM == FM * 32 && WTN == FN * 32, "wave tile");
   constexpr int L = XL::NI + WL::NI;  // load instructions per wave per k-tile
   static_assert((NS - 1) * L < 64, "vmcnt range");
-
-  extern __shared__ __attribute__((aligned(16))) half_t lds[];
-
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int kg = wave_all / WPG, wave = wave_all - kg * WPG;  // k-group, wave inside the group
-  const int wm = wave % WAVES_M, wn = wave / WAVES_M;
   const int g = lane >> 5, l32 = lane & 31;
-  int tm, tn;
-  tile_of_workgroup(blockIdx.x, p.tiles_m, p.tiles_n, p.swizzle, tm, tn);
-  const int m0 = tm * BM, n0 = tn * BN;
-  const int z = blockIdx.y;
-  const int nk_total = (p.K + BK - 1) / BK;
-  const int kt_first = z * p.ktiles_per_split;
-  const int kt_end = (kt_first + p.ktiles_per_split) < nk_total ? (kt_first + p.ktiles_per_split) : nk_total;
-  // This group's k-tiles are kt_begin, kt_begin + KG, ...; every group runs the same number of
-  // pipeline steps (the barriers are shared), tiles at or past kt_end load zeros.
-  const int kt_begin = kt_first + kg;
-  const int k_limit = kt_end * BK < p.K ? kt_end * BK : p.K;
-
-  XL xl;
-  WL wl;
-  if constexpr (XMODE == 0) {
-    const int64_t rem = ((int64_t)(p.M - m0 - 1) * p.ldx + p.K) * 2;
-    xl.init(p.X + (int64_t)m0 * p.ldx, (unsigned)(rem < 0x7fffffff ? rem : 0x7fffffff), p.ldx, p.M - m0, k_limit, p.cg,
-            m0, kt_begin, wave, lane);
-  } else {
-    const int64_t bytes = (int64_t)p.cg.H * p.cg.Wi * p.cg.C * 2 * (int64_t)(p.M / (p.cg.P * p.cg.Q));
-    xl.init(p.X, (unsigned)bytes, 0, p.M - m0, k_limit, p.cg, m0, kt_begin, wave, lane);
-  }
   int wfo[WKN ? FN : 1];  // row-major weights: this lane's offset inside the tile, per fragment column
   if constexpr (WKN) {
-    const int64_t rem = ((int64_t)(p.K - 1) * p.ldw + (p.N - n0)) * 2;  // (the host keeps the matrix under 2 GiB)
-    wl.init(p.W + n0, (unsigned)rem, p.ldw, p.N - n0, k_limit, wave, lane);
 #pragma unroll
     for (int a = 0; a < FN; ++a) wfo[a] = kn_frag_offset<BN>(wn * WTN + a * 32, lane);
-  } else {
-    const int64_t rem = ((int64_t)(p.N - n0 - 1) * p.ldw + p.K) * 2;
-    wl.init(p.W + (int64_t)n0 * p.ldw, (unsigned)(rem < 0x7fffffff ? rem : 0x7fffffff), p.ldw, p.N - n0, k_limit, p.cg,
-            n0, kt_begin, wave, lane);
   }
-
-  floatx16 acc[FN][FM];
-#pragma unroll
-  for (int a = 0; a < FN; ++a)
-#pragma unroll
-    for (int b = 0; b < FM; ++b)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
-  BiasQuads<FN> bias;
-
-  half_t* const lds_group = lds + kg * T::GROUP_HALVES;  // this k-group's part of every stage
   auto issue = [&](int kt, int stage) {
-    half_t* s = lds_group + stage * STAGE;
-    xl.issue(kt, s, p.cg);
-    wl.issue(kt, s + BM * BK, p.cg);
+    half_t* s = stages + stage * STAGE;
+    xl.issue(kt, s, cg);
+    wl.issue(kt, s + BM * BK, cg);
   };
   // Fragments are double-buffered in registers in groups of G k-steps: the LDS reads of the next
   // group (or of the first group of the next tile) are in flight while the MFMAs of the current one
   // execute, so the matrix pipe keeps working across the workgroup barrier that separates two
   // k-tiles.
-  constexpr int G = T::G, NG = T::KS / G;  // k-steps per group, groups per k-tile
-  static_assert(T::KS % G == 0 && (NG == 1 || NG == 2 || NG == 4), "fragment groups per k-tile; register sets alternate per group");
+  constexpr int KS = BK / 16, NG = KS / G;  // groups per k-tile
+  static_assert(KS % G == 0 && (NG == 1 || NG == 2 || NG == 4), "fragment groups per k-tile; register sets alternate per group");
   half8 xf[2][G][FM], wf[2][G][FN];
   // Fragment R (x first) of the reads of group `grp` of the tile in stage `stg`.
   auto read_one = [&](int stg, int grp, auto rc, half8 (&x)[G][FM], half8 (&w)[G][FN]) {
     constexpr int R = decltype(rc)::value, k = R / (FM + FN), f = R % (FM + FN);
-    const half_t* xs = lds_group + stg * STAGE;
+    const half_t* xs = stages + stg * STAGE;
     const half_t* ws = xs + BM * BK;
     const int chunk = (grp * G + k) * 2 + g;
     if constexpr (f < FM) x[k][f] = *(const half8*)(xs + dma_chunk_offset<BK>(wm * WTM + f * 32 + l32, chunk));
@@ -515,19 +450,17 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG) void fprop_dma_kernel(
     else w[k][f - FM] = *(const half8*)(ws + dma_chunk_offset<BK>(wn * WTN + (f - FM) * 32 + l32, chunk));
   };
 
-  // ---- NS-deep pipeline: one barrier per k-tile ----------------------------------------------
-  const int n_tiles = (kt_end - kt_first + KG - 1) / KG;  // pipeline steps, at least one, the same for every k-group
   int stage = 0, fill_stage = 0;
   auto load_one = [&](int kt, auto ic) {  // load instruction I of tile kt: [X instructions | W instructions]
     constexpr int I = decltype(ic)::value, XN = XL::NI;
-    half_t* s = lds_group + fill_stage * STAGE;
-    if constexpr (I < XN) xl.template issue_part<I, I + 1>(kt, s, p.cg);
-    else wl.template issue_part<I - XN, I - XN + 1>(kt, s + BM * BK, p.cg);
+    half_t* s = stages + fill_stage * STAGE;
+    if constexpr (I < XN) xl.template issue_part<I, I + 1>(kt, s, cg);
+    else wl.template issue_part<I - XN, I - XN + 1>(kt, s + BM * BK, cg);
   };
 #pragma unroll
   for (int t = 0; t < NS; ++t)
     if (t < n_tiles) issue(kt_begin + t * KG, t);
-  if constexpr (NS == 1) bias.fetch(p, n0 + wn * WTN, lane);
+  if constexpr (NS == 1) before_last();
   if (n_tiles >= NS) barrier_after_loads<(NS - 1) * L>();
   else barrier_after_loads<0>();
   for_constants<G * (FM + FN)>([&](auto rc) { read_one(0, 0, rc, xf[0], wf[0]); });
@@ -559,7 +492,6 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG) void fprop_dma_kernel(
     constexpr bool last = j + 1 == NG;
     constexpr int MF = G * FM * FN, RD = decltype(readsc)::value ? G * (FM + FN) : 0;
     constexpr int S = (j + 1) % NG, L0 = S * L / NG, LD = LOADS ? (S + 1) * L / NG - L0 : 0;
-    constexpr int MOST = T::DEEP || T::NW < 8 ? 2 : 3;  // reads behind one MFMA
     constexpr int PER = (RD + MF - 1) / MF > MOST ? (RD + MF - 1) / MF : MOST;
     __builtin_amdgcn_sched_barrier(0);
     for_constants<MF>([&](auto mc) {
@@ -593,15 +525,15 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG) void fprop_dma_kernel(
       turn(it);
       group(LastGroup{}, LastSet{}, C1{}, C1{}, kt, true);
       others(C1{}, kt);
-      xl.advance(p.cg);
-      wl.advance(p.cg);
+      xl.advance(cg);
+      wl.advance(cg);
     }
     for (; NS > 1 && it + 1 < n_tiles; ++it) {
       turn(it);
       group(LastGroup{}, LastSet{}, C1{}, C0{}, 0, false);
       others(C0{}, 0);
     }
-    if (NS > 1 && kg == 0) bias.fetch(p, n0 + wn * WTN, lane);
+    if constexpr (NS > 1) before_last();
     group(LastGroup{}, LastSet{}, C0{}, C0{}, 0, false);
   } else if constexpr (NS == 1) {
     group(C0{}, C0{}, C0{}, C0{}, 0, false);
@@ -612,8 +544,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG) void fprop_dma_kernel(
       turn(it);
       group(C0{}, setc, C1{}, loadsc, kt_begin + (it + NS) * KG, more);
       if (decltype(loadsc)::value == 1 || (decltype(loadsc)::value == 2 && more)) {
-        xl.advance(p.cg);
-        wl.advance(p.cg);
+        xl.advance(cg);
+        wl.advance(cg);
       }
     };
     using C2 = std::integral_constant<int, 2>;
@@ -628,13 +560,79 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG) void fprop_dma_kernel(
     }
     if (it + 1 < n_tiles) {  // the last two tiles, all loads under way
       tile(it, C0{}, C0{});
-      if (kg == 0) bias.fetch(p, n0 + wn * WTN, lane);
+      before_last();
       group(C0{}, C1{}, C0{}, C0{}, 0, false);
     } else {
-      if (kg == 0) bias.fetch(p, n0 + wn * WTN, lane);
+      before_last();
       group(C0{}, C0{}, C0{}, C0{}, 0, false);
     }
   }
+}
+
+// NCHW: the output tensor is [N][K][P][Q] (convolutions only; see fprop_tile_out_with)
+// WKN: the weights are row-major [K][N] (GEMM only), see DmaKnTileLoader.
+template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int XMODE, int NS, int KG = 1, bool RES = false, bool NCHW = false,
+          bool WKN = false>
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG) void fprop_dma_kernel(const FpropParams p) {
+  using T = FpropDmaTraits<BM, BN, BK, WAVES_M, WAVES_N, XMODE, NS, KG>;
+  constexpr int WPG = T::WPG, WTM = T::WTM, WTN = T::WTN, FM = T::FM, FN = T::FN;
+  using XL = DmaTileLoader<BM, BK, WPG, XMODE, KG>;
+  using WL = std::conditional_t<WKN, DmaKnTileLoader<BK, BN, WPG>, DmaTileLoader<BN, BK, WPG, 0, KG>>;
+  static_assert(!WKN || XMODE == 0, "row-major weights: GEMM only");
+
+  extern __shared__ __attribute__((aligned(16))) half_t lds[];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kg = wave_all / WPG, wave = wave_all - kg * WPG;  // k-group, wave inside the group
+  const int wm = wave % WAVES_M, wn = wave / WAVES_M;
+  const int g = lane >> 5, l32 = lane & 31;
+  int tm, tn;
+  tile_of_workgroup(blockIdx.x, p.tiles_m, p.tiles_n, p.swizzle, tm, tn);
+  const int m0 = tm * BM, n0 = tn * BN;
+  const int z = blockIdx.y;
+  const int nk_total = (p.K + BK - 1) / BK;
+  const int kt_first = z * p.ktiles_per_split;
+  const int kt_end = (kt_first + p.ktiles_per_split) < nk_total ? (kt_first + p.ktiles_per_split) : nk_total;
+  // This group's k-tiles are kt_begin, kt_begin + KG, ...; every group runs the same number of
+  // pipeline steps (the barriers are shared), tiles at or past kt_end load zeros.
+  const int kt_begin = kt_first + kg;
+  const int k_limit = kt_end * BK < p.K ? kt_end * BK : p.K;
+
+  XL xl;
+  WL wl;
+  if constexpr (XMODE == 0) {
+    const int64_t rem = ((int64_t)(p.M - m0 - 1) * p.ldx + p.K) * 2;
+    xl.init(p.X + (int64_t)m0 * p.ldx, (unsigned)(rem < 0x7fffffff ? rem : 0x7fffffff), p.ldx, p.M - m0, k_limit, p.cg,
+            m0, kt_begin, wave, lane);
+  } else {
+    const int64_t bytes = (int64_t)p.cg.H * p.cg.Wi * p.cg.C * 2 * (int64_t)(p.M / (p.cg.P * p.cg.Q));
+    xl.init(p.X, (unsigned)bytes, 0, p.M - m0, k_limit, p.cg, m0, kt_begin, wave, lane);
+  }
+  if constexpr (WKN) {
+    const int64_t rem = ((int64_t)(p.K - 1) * p.ldw + (p.N - n0)) * 2;  // (the host keeps the matrix under 2 GiB)
+    wl.init(p.W + n0, (unsigned)rem, p.ldw, p.N - n0, k_limit, wave, lane);
+  } else {
+    const int64_t rem = ((int64_t)(p.N - n0 - 1) * p.ldw + p.K) * 2;
+    wl.init(p.W + (int64_t)n0 * p.ldw, (unsigned)(rem < 0x7fffffff ? rem : 0x7fffffff), p.ldw, p.N - n0, k_limit, p.cg,
+            n0, kt_begin, wave, lane);
+  }
+
+  floatx16 acc[FN][FM];
+#pragma unroll
+  for (int a = 0; a < FN; ++a)
+#pragma unroll
+    for (int b = 0; b < FM; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
+  BiasQuads<FN> bias;
+
+  // ---- NS-deep pipeline: one barrier per k-tile ----------------------------------------------
+  const int n_tiles = (kt_end - kt_first + KG - 1) / KG;  // pipeline steps, at least one, the same for every k-group
+  dma_main_loop<BM, BN, BK, WAVES_M, WAVES_N, NS, KG, T::G, (T::DEEP || T::NW < 8 ? 2 : 3), WKN>(
+      xl, wl, lds + kg * T::GROUP_HALVES, p.cg, kt_begin, n_tiles, wm, wn, lane, acc, [&] {
+        if (kg == 0) bias.fetch(p.bias, p.bias_on, p.N, n0 + wn * WTN, lane);
+      });
 
   // ---- k-groups: sum the accumulators through LDS, group 0 carries on ------------------------------
   if constexpr (KG > 1) {

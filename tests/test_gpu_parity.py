@@ -1773,6 +1773,35 @@ def test_conv_chain3_every_instance_and_tuner(bolt, shape):
     assert_close(host(y), want, "conv chain %s tuned" % (shape,))
 
 
+@pytest.mark.parametrize("layout", ["kn", "nk"])
+@pytest.mark.parametrize("K0", [8, 64, 72, 128, 192, 200, 256, 264, 320, 448])
+def test_fused_gemms_number_of_k_tiles_integer_bit_exact(bolt, layout, K0):
+    # one k-tile of the first op up to more than twice the deepest pipeline, in every instance of pairs and of chains of three.
+    # |d0| <= 450 and |d1| <= 40 * 450 + 2 = 18002: sums below 2^24, so every op rounds the same exact value
+    M, widths = 260, (K0, 40, 56, 24)
+    A = wl.integer_fp16(143, 0, (M, K0), -1, 1)
+    ws = [wl.integer_fp16(143, 1 + i, (k, n), -1, 1) for i, (k, n) in enumerate(zip(widths, widths[1:]))]
+    bs = [wl.integer_fp16(143, 4 + i, (n,), -2, 2) for i, n in enumerate(widths[1:])]
+    lay = bolt.LAYOUT_KN if layout == "kn" else bolt.LAYOUT_NK
+    wd = [dev(w if layout == "kn" else np.ascontiguousarray(w.T)) for w in ws]
+    descs = [bolt.gemm_desc(M, n, k, act="relu" if i < 2 else "none", b_layout=lay) for i, (k, n) in enumerate(zip(widths, widths[1:]))]
+    d0 = ref.gemm(A, ws[0], bs[0], act="relu")
+    want = ref.gemm(d0, ws[1], bs[1], act="relu")
+    for kid in range(bolt.bolt_num_instances(bolt.OP_B2B_GEMM)):
+        if bolt.bolt_instance_supports(bolt.OP_B2B_GEMM, kid, *descs[:2]):
+            _say("pair K0=%d %s instance %d" % (K0, layout, kid))
+            D = torch.full((M, widths[2]), float("nan"), dtype=torch.float16, device="cuda")
+            bolt.bolt_b2b_gemm(*descs[:2], dev(A), wd[0], dev(bs[0]), wd[1], dev(bs[1]), D, {"kernel_id": kid})
+            assert_bit_equal(host(D), want, "pair K0=%d %s instance %d" % (K0, layout, kid))
+    want = ref.gemm(want, ws[2], bs[2], act="none")
+    for kid in range(bolt.bolt_num_instances(bolt.OP_GEMM_CHAIN3)):
+        if bolt.bolt_chain_instance_supports(bolt.OP_GEMM_CHAIN3, kid, descs):
+            _say("chain K0=%d %s instance %d" % (K0, layout, kid))
+            D = torch.full((M, widths[3]), float("nan"), dtype=torch.float16, device="cuda")
+            bolt.bolt_b2b_gemm_chain(descs, dev(A), wd, [dev(b) for b in bs], D, {"kernel_id": kid})
+            assert_bit_equal(host(D), want, "chain K0=%d %s instance %d" % (K0, layout, kid))
+
+
 def test_gemm_chain3_integer_bit_exact(bolt):
     M, K0, N0, N1, N2 = 300, 72, 64, 64, 128
     A = wl.integer_fp16(303, 0, (M, K0), -2, 2)
