@@ -14,11 +14,14 @@
 //     residual are requested before the loop.
 // Row-major weights ([K][N]) lie in LDS as in memory and are read with the transposing read.
 // What bounds it: launch (2.3 us), one round trip to memory and the sum over the waves (waves wait for 48 to 72 % of their life); with many units per wave the rate
-// at which one compute unit gets operands that come from the memory-side cache (about 60 GB/s).  Deeper prefetch (D = 4 to
-// 6) was slower: the requests past a wave's last unit cost as much as they hide.
+// at which one compute unit gets operands that come from the memory-side cache (about 60 GB/s).  A wave has few units (1 to 9 in a
+// network of one image), so no request is made past the last one: requests that bring only zeros take their turn in the address
+// unit like any other, and D of them per wave cost 0.1 to 0.4 us (1024 -> 256 at 14 x 14 3.99 -> 3.84 us, 3 x 3 256 -> 256 5.94 -> 5.5,
+// 128 -> 512 with a skip connection at 28 x 28 4.3 -> 3.7, 32 x 1000 x 2048 5.8 -> 5.65; the network's 52 layers 248 -> 221).  Deeper prefetch is
+// slower still: D = 4 to 6 2 to 20 %, by registers, and because the first unit then waits for all of them.
 // Measured back to back under the tuner's picks, tiled kernels -> this one: 32 x 1000 x 2048 row-major 8.1 -> 5.0 us,
-// 256 x 256 x 256 4.1 -> 3.2; convolutions of one image: 14 x 14, 3 x 3, 256 -> 256 9.5 -> 5.9, 1024 -> 256 6.1 -> 3.8,
-// 7 x 7, 3 x 3, 512 -> 512 10.5 -> 7.3, 2048 -> 512 8.0 -> 4.5.
+// 256 x 256 x 256 4.1 -> 3.2; convolutions of one image: 14 x 14, 3 x 3, 256 -> 256 9.5 -> 5.5, 1024 -> 256 6.1 -> 3.8,
+// 7 x 7, 3 x 3, 512 -> 512 10.5 -> 7.2, 2048 -> 512 8.0 -> 4.5.
 #pragma once
 #include <algorithm>
 #include <cmath>
@@ -158,9 +161,9 @@ __global__ __launch_bounds__(64 * NW) void fprop_ws_kernel(const FpropParams p) 
   const int units = (p.K + 63) >> 6, upw = (units + NW - 1) / NW, u0 = wave * upw;
   const int n_units = units - u0 < upw ? units - u0 : upw;  // (may be negative: no work)
   uintx4 xv[D][2 * FM], wv[D][2 * FN];
-  auto fetch = [&](int i, int set) {  // operands of this wave's unit i (past its last one: zeros, no traffic)
+  auto fetch = [&](int i, int set) {  // operands of this wave's unit i
     const int k0 = (u0 + i) * 64, k = k0 + lk;
-    const bool on = i < n_units && k < p.K;
+    const bool on = k < p.K;
     if constexpr (XMODE == 0) {
 #pragma unroll
       for (int b = 0; b < 2 * FM; ++b) {
@@ -182,7 +185,7 @@ __global__ __launch_bounds__(64 * NW) void fprop_ws_kernel(const FpropParams p) 
     if constexpr (WKN) {
 #pragma unroll
       for (int a = 0; a < 2 * FN; ++a) {
-        const bool ok = i < n_units && k0 + a * KROWS + krow < p.K && w_at[0] != kInvalidOffset;
+        const bool ok = k0 + a * KROWS + krow < p.K && w_at[0] != kInvalidOffset;
         const unsigned off = ok ? (unsigned)(k0 + a * KROWS) * (unsigned)p.ldw * 2u + w_at[0] : kInvalidOffset;
         wv[set][a] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(wr, off, 0, 0));
       }
@@ -195,7 +198,8 @@ __global__ __launch_bounds__(64 * NW) void fprop_ws_kernel(const FpropParams p) 
     }
   };
 #pragma unroll
-  for (int k = 0; k < D; ++k) fetch(k, k);
+  for (int k = 0; k < D; ++k)
+    if (k < n_units) fetch(k, k);
 
   // bias and residual of this thread's output quads, while the operands are on their way
   half4 hb[Tr::QPT], res[Tr::QPT];
@@ -247,7 +251,7 @@ __global__ __launch_bounds__(64 * NW) void fprop_ws_kernel(const FpropParams p) 
           else *(uintx4*)(wstage + (a >> 1) * 2048 + put[a & 1]) = wv[k][a];
         }
         asm volatile("" ::: "memory");  // reads of what other lanes wrote stay behind the writes (and the next unit's writes behind them)
-        fetch(i + k + D, k);
+        if (i + k + D < n_units) fetch(i + k + D, k);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           half8 xf[FM], wf[FN];
@@ -279,7 +283,7 @@ __global__ __launch_bounds__(64 * NW) void fprop_ws_kernel(const FpropParams p) 
 #pragma unroll
     for (int a = 0; a < FN; ++a) *(floatx4*)(row + a * 16 + g4 * 4) = acc[a][b];
   }
-  __syncthreads();
+  barrier_after_lds_writes();
   const EpilogueArgs ep{p.bias, p.bias_on, p.N, p.alpha, p.beta, p.act, p.gamma};
 #pragma unroll
   for (int i = 0; i < Tr::QPT; ++i) {

@@ -109,6 +109,24 @@ def test_gemm_number_of_k_tiles_integer_bit_exact(bolt, layout, K):
             assert_bit_equal(got, want, "gemm K=%d %s instance %d" % (K, layout, kid))
 
 
+@pytest.mark.parametrize("layout", ["kn", "nk"])
+@pytest.mark.parametrize("K", [8, 448, 520, 768, 1000, 1288, 1544, 1800])
+def test_gemm_few_tiles_number_of_units_integer_bit_exact(bolt, layout, K):
+    # a wave of the kernels that split the reduction over 4, 8 or 16 waves gets 0 to 8 units of 64: fewer than it keeps in flight, as
+    # many, and several rounds, whole and ragged.  |sum| <= 1800 + 9 < 2048
+    M, N = 40, 24
+    A = wl.integer_fp16(144, 0, (M, K), -1, 1)
+    B = wl.integer_fp16(144, 1, (K, N), -1, 1)
+    bias = wl.integer_fp16(144, 2, (N,), -9, 9)
+    want = ref.gemm(A, B, bias, act="none")
+    d = bolt.gemm_desc(M, N, K, b_layout=bolt.LAYOUT_KN if layout == "kn" else bolt.LAYOUT_NK)
+    for kid in range(bolt.bolt_num_instances(bolt.OP_GEMM)):
+        if bolt.bolt_instance_supports(bolt.OP_GEMM, kid, d):
+            _say("gemm K=%d %s instance %d" % (K, layout, kid))
+            got, _ = _run_gemm(bolt, A, B, bias, act="none", layout=layout, config={"kernel_id": kid})
+            assert_bit_equal(got, want, "gemm K=%d %s instance %d" % (K, layout, kid))
+
+
 def test_gemm_alpha_beta_activations_and_no_bias(bolt):
     M, N, K = 130, 72, 96
     A = wl.uniform_fp16(103, 0, (M, K), -1, 1)
@@ -386,6 +404,25 @@ def test_conv_even_channels_integer_bit_exact_every_instance(bolt, case):
         assert_bit_equal(host(y), want_res, "even channels + residual %s instance %d" % (case, kid))
     bolt.bolt_conv2d_fprop_nhwc(d, tx, tw, tb, y)  # built-in pick rule
     assert_bit_equal(host(y), want, "even channels %s pick rule" % (case,))
+
+
+@pytest.mark.parametrize("case", [(10, 1, 3), (10, 5, 5), (22, 5, 7), (46, 5, 7), (78, 5, 5)])  # C R S
+def test_conv_even_channels_number_of_steps_integer_bit_exact(bolt, case):
+    # k-steps of 4 chunks of 8 channels, split over 4 or 8 waves: 6, 50, 105, 210 and 250 chunks are 0 to 16 steps per wave, below,
+    # at and above two rounds of what is in flight.  |sum| <= 78 * 25 + 9 < 2048
+    c, r, s_ = case
+    x = wl.integer_fp16(145, 0, (2, 9, 11, c), -1, 1)
+    w = wl.integer_fp16(145, 1, (24, r, s_, c), -1, 1)
+    b = wl.integer_fp16(145, 2, (24,), -9, 9)
+    pad = (r // 2, s_ // 2)
+    want = ref.conv2d_nhwc(x, w, b, stride=1, pad=pad, act="none")
+    d = bolt.conv_desc(2, 9, 11, c, 24, r, s_, 1, pad, act="none")
+    for kid in range(bolt.bolt_num_instances(bolt.OP_CONV2D)):
+        if bolt.bolt_instance_supports(bolt.OP_CONV2D, kid, d):
+            _say("even channels steps %s instance %d" % (case, kid))
+            y = torch.full(want.shape, float("nan"), dtype=torch.float16, device="cuda")
+            bolt.bolt_conv2d_fprop_nhwc(d, dev(x), dev(w), dev(b), y, {"kernel_id": kid})
+            assert_bit_equal(host(y), want, "even channels steps %s instance %d" % (case, kid))
 
 
 def test_conv_even_channels_infinities_stay_where_they_belong(bolt):
