@@ -111,10 +111,11 @@ __device__ __forceinline__ void b2b_dma_op0(const B2bParams& p, half_t* lds, int
 // op's output, NIN_T columns) x Ws^T, Ws as b2b_issue_weights leaves it.  Step t reduces over input columns
 // [16t, 16t + 16); the fragment reads apply the permutation of the reduction index that b2b_make_d documents.
 // WKN: Ws holds the row-major matrix as [NIN_T][NOUT_T]; the transpose read gathers the same permuted rows.
-template <int NIN_T, int NOUT_T, int FM, bool WKN = false>
-__device__ __forceinline__ void b2b_rf_gemm(const half_t* Ws, const half8 (&d)[NIN_T / 16][FM],
-                                            floatx16 (&acc)[NOUT_T / 32][FM], int l32, int g) {
-  constexpr int KB = NIN_T < 64 ? NIN_T : 64, FNO = NOUT_T / 32;
+// NIN_U, NOUT_U: columns of either side that are multiplied, of those that Ws is laid out for.
+template <int NIN_T, int NOUT_T, int FM, bool WKN = false, int NIN_U = NIN_T, int NOUT_U = NOUT_T>
+__device__ __forceinline__ void b2b_rf_gemm(const half_t* Ws, const half8 (&d)[NIN_U / 16][FM],
+                                            floatx16 (&acc)[NOUT_U / 32][FM], int l32, int g) {
+  constexpr int KB = NIN_T < 64 ? NIN_T : 64, FNO = NOUT_U / 32;
   int woff[WKN ? FNO : 1];
   if constexpr (WKN) {
 #pragma unroll
@@ -127,7 +128,7 @@ __device__ __forceinline__ void b2b_rf_gemm(const half_t* Ws, const half8 (&d)[N
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
 #pragma unroll
-  for (int t = 0; t < NIN_T / 16; ++t) {
+  for (int t = 0; t < NIN_U / 16; ++t) {
     const int kbase = t * 16;
     const half_t* ws = Ws + (kbase / KB) * NOUT_T * KB;
     const int chunk = (kbase % KB) / 8;

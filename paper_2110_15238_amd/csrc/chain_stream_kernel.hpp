@@ -64,10 +64,13 @@ __device__ __forceinline__ void chain_stream_make_d(const EpilogueArgs& ep, cons
   else make(std::false_type{});
 }
 
-template <int NW, int KT, int N0T, int N1T, int N2T, bool RES, bool WKN>
+// KU, NU: reduction indices of the first op and columns of a 128-wide one that are computed, of KT and 128 that the layouts are made for.
+template <int NW, int KT, int N0T, int N1T, int N2T, int KU, int NU, bool RES, bool WKN>
 __global__ __launch_bounds__(64 * NW, 2) void chain_stream_kernel(const B2bParams p) {
   using T = ChainStreamTraits<NW, KT, N0T, N1T, N2T>;
-  constexpr int KS = KT / 16, FN0 = N0T / 32, NLT = T::NLT, FNL = NLT / 32, CPR = NLT / 8;
+  constexpr int NLT = T::NLT, CPR = NLT / 8;
+  constexpr int N0U = N0T < NU ? N0T : NU, N1U = N1T < NU ? N1T : NU, NLU = NLT < NU ? NLT : NU;
+  constexpr int KS = KU / 16, FN0 = N0U / 32, FNL = NLU / 32;
   extern __shared__ __attribute__((aligned(16))) half_t lds[];
   half_t* const W0s = lds;
   half_t* const W1s = W0s + KT * N0T;
@@ -169,15 +172,15 @@ __global__ __launch_bounds__(64 * NW, 2) void chain_stream_kernel(const B2bParam
     if (t + step < tiles) load_rows(t + step);
     __builtin_amdgcn_sched_barrier(0);
 
-    half8 d0[N0T / 16][1];
+    half8 d0[N0U / 16][1];
     chain_stream_make_d<FN0>(EpilogueArgs{p.b0, p.b0_on, p.N0, p.alpha0, p.beta0, p.act0}, bias0, acc0, d0, g);
-    floatx16 acc1[N1T / 32][1];
-    b2b_rf_gemm<N0T, N1T, 1, WKN>(W1s, d0, acc1, l32, g);
+    floatx16 acc1[N1U / 32][1];
+    b2b_rf_gemm<N0T, N1T, 1, WKN, N0U, N1U>(W1s, d0, acc1, l32, g);
     if constexpr (N2T > 0) {
-      half8 d1[N1T / 16][1];
-      chain_stream_make_d<N1T / 32>(EpilogueArgs{p.b1, p.b1_on, p.N1, p.alpha1, p.beta1, p.act1}, bias1, acc1, d1, g);
+      half8 d1[N1U / 16][1];
+      chain_stream_make_d<N1U / 32>(EpilogueArgs{p.b1, p.b1_on, p.N1, p.alpha1, p.beta1, p.act1}, bias1, acc1, d1, g);
       floatx16 acc2[FNL][1];
-      b2b_rf_gemm<N1T, NLT, 1, WKN>(W2s, d1, acc2, l32, g);
+      b2b_rf_gemm<N1T, NLT, 1, WKN, N1U, NLU>(W2s, d1, acc2, l32, g);
       tile_out(t, acc2, EpilogueArgs{p.b2, p.b2_on, p.N2, p.alpha2, p.beta2, p.act2, RES ? p.gamma : 0.f}, bias2);
     } else {
       tile_out(t, acc1, EpilogueArgs{p.b1, p.b1_on, p.N1, p.alpha1, p.beta1, p.act1, RES ? p.gamma : 0.f}, bias1);
@@ -185,15 +188,31 @@ __global__ __launch_bounds__(64 * NW, 2) void chain_stream_kernel(const B2bParam
   }
 }
 
-template <int NW, int KT, int N0T, int N1T, int N2T, bool WKN>
-hipError_t launch_chain_stream(const B2bParams& p, hipStream_t stream) {
+template <int NW, int KT, int N0T, int N1T, int N2T, int KU, int NU, bool WKN>
+hipError_t launch_chain_stream_as(const B2bParams& p, hipStream_t stream) {
   static LdsOptIn opt_in[2];
   using T = ChainStreamTraits<NW, KT, N0T, N1T, N2T>;
   if (p.res)
-    return b2b_launch_common(chain_stream_kernel<NW, KT, N0T, N1T, N2T, true, WKN>, opt_in[1], p, T::grid(p), 64 * NW,
+    return b2b_launch_common(chain_stream_kernel<NW, KT, N0T, N1T, N2T, KU, NU, true, WKN>, opt_in[1], p, T::grid(p), 64 * NW,
                              T::LDS_BYTES, stream);
-  return b2b_launch_common(chain_stream_kernel<NW, KT, N0T, N1T, N2T, false, WKN>, opt_in[0], p, T::grid(p), 64 * NW,
+  return b2b_launch_common(chain_stream_kernel<NW, KT, N0T, N1T, N2T, KU, NU, false, WKN>, opt_in[0], p, T::grid(p), 64 * NW,
                            T::LDS_BYTES, stream);
+}
+// What of the compiled widths is only padding is not computed: loads, products and epilogues of it take the issue slots that bound
+// the kernel.  (32 at a time of 128: up to 96 and above, of the reduction and of the 128-wide op.  128320 x 96 -> 32 -> 96 -> 32 11.8 -> 10.6 us,
+// 70992 x 88 -> 48 -> 72 12.2 -> 10.7, 56016 x 16 -> 40 -> 72 7.9 -> 7.1, 98632 x 32 -> 32 -> 56 -> 16 10.6 -> 10.0, 41440 x 88 -> 64 -> 32 5.7 -> 5.5.  A
+// reduction of up to 64 as a third form would save another quarter of the loads, for half as many kernels again.)
+template <int NW, int KT, int N0T, int N1T, int N2T, bool WKN>
+hipError_t launch_chain_stream(const B2bParams& p, hipStream_t stream) {
+  static_assert(KT == 128 && N0T <= 128 && N1T <= 128 && N2T <= 128, "widths that the rule below knows");
+  const bool narrow = (N0T < 128 || p.N0 <= 96) && (N1T < 128 || p.N1 <= 96) && (N2T < 128 || p.N2 <= 96);
+  if constexpr (N0T == 128 || N1T == 128 || N2T == 128) {
+    if (narrow)
+      return p.K0 <= 96 ? launch_chain_stream_as<NW, KT, N0T, N1T, N2T, 96, 96, WKN>(p, stream)
+                        : launch_chain_stream_as<NW, KT, N0T, N1T, N2T, KT, 96, WKN>(p, stream);
+  }
+  return p.K0 <= 96 ? launch_chain_stream_as<NW, KT, N0T, N1T, N2T, 96, 128, WKN>(p, stream)
+                    : launch_chain_stream_as<NW, KT, N0T, N1T, N2T, KT, 128, WKN>(p, stream);
 }
 
 // The GEMM pair on the same kernel: N2T = 0.

@@ -1733,6 +1733,36 @@ def test_gemm_chain3_rows_streamed_in_rounds(bolt, shape, layout):
     assert_close(host(D), want, "gemm chain %s heuristic" % (shape,))
 
 
+@pytest.mark.parametrize("layout", ["kn", "nk"])
+@pytest.mark.parametrize("widths", [(88, 24, 96, 32), (96, 32, 104, 24), (104, 64, 96, 64), (128, 40, 72, 56), (96, 64, 64, 96), (104, 56, 40, 104), (96, 96, 64), (104, 104, 40), (16, 40, 96)])
+def test_streamed_gemms_padded_widths_integer_bit_exact(bolt, layout, widths):
+    # 96 is where the reduction of the first op and the columns of a 128-wide op stop being computed as 96: at, below and above it, in
+    # every instance.  |d0| <= 128 and |d1| <= 104 * 128 + 2: sums below 2^24, so every op rounds the same exact value
+    M, n = 330, len(widths) - 1
+    A = wl.integer_fp16(146, 0, (M, widths[0]), -1, 1)
+    ws = [wl.integer_fp16(146, 1 + i, (k, c), -1, 1) for i, (k, c) in enumerate(zip(widths, widths[1:]))]
+    bs = [wl.integer_fp16(146, 4 + i, (c,), -2, 2) for i, c in enumerate(widths[1:])]
+    lay = bolt.LAYOUT_KN if layout == "kn" else bolt.LAYOUT_NK
+    wd = [dev(w if layout == "kn" else np.ascontiguousarray(w.T)) for w in ws]
+    acts = ["relu"] * (n - 1) + ["none"]
+    descs = [bolt.gemm_desc(M, c, k, act=a, b_layout=lay) for k, c, a in zip(widths, widths[1:], acts)]
+    want = A
+    for w, b, a in zip(ws, bs, acts):
+        want = ref.gemm(want, w, b, act=a)
+    op = bolt.OP_GEMM_CHAIN3 if n == 3 else bolt.OP_B2B_GEMM
+    ran = 0
+    for kid in range(bolt.bolt_num_instances(op)):
+        if not (bolt.bolt_chain_instance_supports(op, kid, descs) if n == 3 else bolt.bolt_instance_supports(op, kid, *descs)):
+            continue
+        _say("streamed %s %s instance %d" % (widths, layout, kid))
+        D = torch.full((M, widths[-1]), float("nan"), dtype=torch.float16, device="cuda")
+        if n == 3: bolt.bolt_b2b_gemm_chain(descs, dev(A), wd, [dev(b) for b in bs], D, {"kernel_id": kid})
+        else: bolt.bolt_b2b_gemm(*descs, dev(A), wd[0], dev(bs[0]), wd[1], dev(bs[1]), D, {"kernel_id": kid})
+        assert_bit_equal(host(D), want, "streamed %s %s instance %d" % (widths, layout, kid))
+        ran += 1
+    assert ran > 0
+
+
 def test_chain_tuner_times_the_tightest_streaming_instance_only(bolt):
     """A chain that two streaming widths fit: both are legal, the one without a tighter neighbour is timed."""
     g = [bolt.gemm_desc(4000, n, k) for k, n in ((96, 32), (32, 96), (96, 32))]
