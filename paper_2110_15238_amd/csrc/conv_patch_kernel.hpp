@@ -158,7 +158,7 @@ __device__ __forceinline__ half2v pk_max(half2v v, unsigned lo) {
 #endif
 
 // GEN: any activation and any alpha, the epilogues in single precision and one unit after the other.
-template <int CP, int N0T, int RS, int ST, bool PAIR, bool RES, bool GEN>
+template <int CP, int N0T, int RS, int ST, bool PAIR, bool RES, bool GEN, bool SHARE = false>
 __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const ConvPatchParams p) {
 #if defined(__HIP_DEVICE_COMPILE__)
   using T = ConvPatchTraits<CP, N0T, RS, ST, PAIR>;
@@ -217,7 +217,31 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const ConvPatchParam
   const int per = p.units / nx, rem = p.units - per * nx;
   const int u_end = __builtin_amdgcn_readfirstlane(per * (xcd + 1) + (xcd + 1 < rem ? xcd + 1 : rem));
   const int step = grid < 8 ? NW : ((grid - xcd + 7) >> 3) * NW;
-  int u = __builtin_amdgcn_readfirstlane(per * xcd + (xcd < rem ? xcd : rem) + wg * NW + wave);
+  const int u_first = per * xcd + (xcd < rem ? xcd : rem);
+  int u = __builtin_amdgcn_readfirstlane(u_first + wg * NW + wave);
+  // SHARE: the units behind the last whole round, where there are some for half of the waves at most, are taken by two to four waves
+  // together, each with its share of the columns of op1 (op0 they all compute).  They would be all that runs for a while, and the residual
+  // makes their outputs long: 56 x 56 64 -> 64 -> 256 with a skip connection, 32 images, 3136 units for 1024 waves, 31.7 -> 28.9 us; 112 x 112
+  // 48 -> 48 -> 192 / 2 29.8 -> 29.0.  (Without a residual nothing was won, 21.0 us either way; where no unit is shared the code cost 0 to 3 %.)
+  constexpr int WAVES = T::MOST_WGS / 8 * NW;  // of an XCD in a launch whose waves have several units
+  static_assert((WAVES & (WAVES - 1)) == 0, "whole rounds by a mask");
+  const int left = (u_end - u_first) & (WAVES - 1), tail = u_end - left;
+  int share = 1;
+  if (SHARE && step == WAVES && tail > u_first && nch > 1) share = left * 4 <= WAVES && nch > 3 ? 4 : left * 3 <= WAVES && nch > 2 ? 3 : left * 2 <= WAVES ? 2 : 1;
+  const int rcp_share = share == 1 ? 1 << 17 : share == 2 ? 1 << 16 : share == 3 ? 43691 : 1 << 15;  // (exact below 2^15)
+  int c_first = 0, c_end = nch;  // columns of the last unit, in 64s
+  auto next_of = [&](int at) {  // this wave's unit behind unit `at`
+    int n = at + step;
+    if (SHARE && share > 1 && n >= tail) n = at >= tail ? u_end : tail + ((n - tail) * rcp_share >> 17);
+    return n;
+  };
+  auto part_of_last = [&](int at) {
+    if (SHARE && share > 1 && at >= tail) {
+      const int w = wg * NW + wave, part = w - (w * rcp_share >> 17) * share;
+      c_first = part * nch * rcp_share >> 17;
+      c_end = (part + 1) * nch * rcp_share >> 17;
+    }
+  };
 
   // ---- patches: one row at a time through a descriptor of that image row, so that whatever lies outside the image, on any
   // side, is beyond the buffer and reads as zeros ---------------------------------------------------------------------------------
@@ -470,15 +494,15 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const ConvPatchParam
   };
 
   auto all_out = [&]() {  // op1 and output of the unit in d
-    if constexpr (RES1) fetch_res(0);
-    for (int c = 0; c < nch; ++c) {
+    if constexpr (RES1) fetch_res(c_first);
+    for (int c = c_first; c < c_end; ++c) {
       if constexpr (RES1) stage_res();
       op1(c);
 #pragma unroll
       for (int q = 0; q < 4; ++q) octet_out(q, c);
       store_out(c);
       if constexpr (RES1)
-        if (c + 1 < nch) fetch_res(c + 1);
+        if (c + 1 < c_end) fetch_res(c + 1);
     }
   };
   auto wait_patch = [&]() {
@@ -506,7 +530,7 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const ConvPatchParam
 
     int buf = 0;
     Unit cur = first;
-    int un = u + step;
+    int un = next_of(u);
     Unit nxt = unit_at(un);
     if constexpr (RES0) {
       set_res(cur);
@@ -519,7 +543,7 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const ConvPatchParam
     asm volatile("" ::: "memory");
     while (un < u_end) {
       // d: the unit cur, its op1 and output in up to four segments, each beside a quarter of the next unit's op0
-      const int un2 = un + step;
+      const int un2 = next_of(un);
       const Unit nxt2 = unit_at(un2);
       const Patch np = patch_of(nxt2, un2 < u_end);
       half_t* const x_next = patch0 + buf * (NW * T::PATCH / 2);
@@ -568,10 +592,12 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const ConvPatchParam
       make_d();
       wait_patch();
       cur = nxt;
+      u = un;
       un = un2;
       nxt = nxt2;
     }
     set_out(cur);
+    part_of_last(u);
     all_out();
   } else {
     // ---- one unit after the other: the next patch is requested as soon as op0 has read the last one
@@ -594,7 +620,7 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const ConvPatchParam
       }
       __builtin_amdgcn_s_waitcnt(0xC07F);  // the patch has been read
       asm volatile("" ::: "memory");
-      const int un = u + step;
+      const int un = next_of(u);
       const Unit nxt = unit_at(un);
       issue_patch(patch_of(nxt, un < u_end), patch0);
       if constexpr (RES0) {
@@ -604,6 +630,7 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const ConvPatchParam
       }
       make_d();
       set_out(cur);
+      part_of_last(u);
       all_out();
       if (un >= u_end) break;
       wait_patch();
@@ -626,6 +653,15 @@ hipError_t launch_conv_patch(const B2bParams& p, int /*grid*/, int lds_bytes, hi
   // (every XCD, ids are dealt round-robin over 8, has the same number of waves for its eighth of the units)
   int grid = std::min((q.units + T::NW - 1) / T::NW, T::MOST_WGS);
   if (grid > 8) grid = (grid + 7) / 8 * 8;
+  if constexpr (PAIR) {
+    // an XCD's units behind the last whole round of its waves; XCDs differ by one unit at most
+    const int waves = T::MOST_WGS / 8 * T::NW, left = (q.units + 7) / 8 % waves;
+    if (res && p.N1 > 64 && grid == T::MOST_WGS && q.units >= 8 * waves && left > 0 && left * 2 <= waves) {
+      kern = gen ? conv_patch_kernel<CP, N0T, RS, ST, true, true, true, true> : conv_patch_kernel<CP, N0T, RS, ST, true, true, false, true>;
+      static LdsOptIn shared[2];
+      if (hipError_t e = shared[gen].ensure((const void*)kern, 160 * 1024); e != hipSuccess) return e;
+    }
+  }
   hipLaunchKernelGGL(kern, dim3(grid), dim3(T::NT), lds_bytes, stream, q);
   return hipGetLastError();
 }

@@ -915,6 +915,27 @@ def test_conv_patch_pairs_and_single_op_integer_bit_exact(bolt, case):
         assert ran >= 3
 
 
+# 1029, 1225, 1519 and 1764 units for 1024 waves: the last ones shared by as many waves as there are column chunks, by four, two and one
+@pytest.mark.parametrize("case", [(21, 28, 56, 8, 24, 3, 1, 1, 256), (25, 28, 56, 8, 24, 3, 1, 1, 256), (25, 28, 56, 16, 40, 1, 1, 0, 136), (31, 28, 56, 8, 24, 3, 1, 1, 200), (36, 28, 56, 8, 24, 1, 1, 0, 256),
+                                  (25, 55, 111, 8, 24, 3, 2, 1, 72)])
+def test_conv_patch_pairs_shared_last_units_integer_bit_exact(bolt, case):
+    test_conv_patch_pairs_and_single_op_integer_bit_exact(bolt, case)
+    N, H, W, Cc, K0, R, stride, pad, K1 = case
+    x, w0 = wl.integer_fp16(511, 0, (N, H, W, Cc), 0, 1), wl.integer_fp16(511, 1, (K0, R, R, Cc), -1, 1)
+    w1 = wl.integer_fp16(511, 3, (K1, 1, 1, K0), -1, 1)
+    c0 = bolt.conv_desc(N, H, W, Cc, K0, R, R, stride, pad)
+    P, Q = bolt.conv_out_hw(c0)
+    c1 = bolt.conv_desc(N, P, Q, K0, K1, 1, 1, alpha=0.5)  # the form for any alpha: halves of whole numbers, |sum| < 1024
+    want = ref.b2b_conv(x, w0, None, w1, None, stride=stride, pad=pad, alpha1=0.5)
+    for kid in range(bolt.bolt_num_instances(bolt.OP_B2B_CONV)):
+        cfg = bolt.bolt_instance_config(bolt.OP_B2B_CONV, kid)
+        if cfg.tile_n == 256 and cfg.tile_m == 128 and cfg.stages == 1 and bolt.bolt_instance_supports(bolt.OP_B2B_CONV, kid, c0, c1):
+            y = torch.full((N, P, Q, K1), float("nan"), dtype=torch.float16, device="cuda")
+            bolt.bolt_b2b_conv(c0, c1, dev(x), dev(w0), None, dev(w1), None, y, {"kernel_id": kid})
+            assert_bit_equal(host(y), want, "conv patch pair %s alpha 0.5, instance %d" % (case, kid))
+
+
+
 @pytest.mark.parametrize("case", [c for c in PATCH_EDGES if c[0] * c[1] * c[2] > 5000 or c[0] in (3, 5)] + [(2, 17, 19, 64, 64, 3, 2, 1, 256), (1, 5, 9, 128, 64, 1, 1, 0, 256)])
 def test_conv_patch_other_activations_and_alpha(bolt, case):
     """What conv_patch_kernel's overlapped loop does not compute runs on its general form: a config that was tuned with ReLU is valid
