@@ -20,8 +20,8 @@
 // Measured back to back under the tuner's picks, old -> new: the problem above 28 -> 7.5 us (230 TFLOP/s; the host needs 4
 // per call); 128 images of 20 x 26 x 174, 5 x 5, 64 channels 252 -> 73 us (510 TFLOP/s); over 85 problems of
 // those ranges nothing was slower (10 input channels, 3 x 3: 5.8 -> 5.5 us, the least gain).
-// Without requests past a wave's last step: 7.2 -> 7.0 us, 10 images of 12 x 20 x 170, 5 x 5, 56 channels 8.7 -> 8.0, 38 of 15 x 22 x 146,
-// 5 x 7, 24 channels 10.0 -> 9.6 (25 problems, best instance: 0.91 to 1.03, 0.985 on average).
+// Without requests past a wave's last step: 7.2 -> 6.8 us, 10 images of 12 x 20 x 170, 5 x 5, 56 channels 8.7 -> 7.9, 38 of 15 x 22 x 146,
+// 5 x 7, 24 channels 10.0 -> 9.1 (25 problems, best instance: 0.90 to 1.01, 0.97 on average).
 #pragma once
 #include <algorithm>
 #include <cmath>
@@ -209,9 +209,9 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_even_kernel(const FpropParams
   if (n_steps < 0) n_steps = 0;
   uintx4 wv[D][FN];
   int2 ent[D];
-  auto fetch = [&](int i, int set) {  // entry and weights of this wave's k-step i
-    ent[set] = *(const int2*)(lds_b + 16 + ((s0 + i) * 4 + g4) * 8);
-    const bool ok = ent[set].x >= 0;
+  auto fetch = [&](int i, int set, bool on) {  // entry and weights of this wave's k-step i (off: nothing)
+    ent[set] = *(const int2*)(lds_b + 16 + (on ? (s0 + i) * 4 + g4 : 0) * 8);
+    const bool ok = on && ent[set].x >= 0;
     const unsigned off = ok ? (unsigned)ent[set].y >> 3 : kInvalidOffset;
 #pragma unroll
     for (int a = 0; a < FN; ++a) {
@@ -220,8 +220,7 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_even_kernel(const FpropParams
     }
   };
 #pragma unroll
-  for (int k = 0; k < D; ++k)
-    if (k < n_steps) fetch(k, k);
+  for (int k = 0; k < D; ++k) fetch(k, k, k < n_steps);  // (without branches, for the waits behind them)
   auto step = [&](int k) {  // the products of set k
     half8 xf[FM];
 #pragma unroll
@@ -249,7 +248,7 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_even_kernel(const FpropParams
 #pragma unroll
     for (int k = 0; k < D; ++k) {
       auto products = step(k);
-      fetch(i + k + D, k);
+      fetch(i + k + D, k, true);
       products();
     }
   }
@@ -258,7 +257,7 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_even_kernel(const FpropParams
     for (int k = 0; k < D; ++k) {
       if (i + k < n_steps) {
         auto products = step(k);
-        if (i + k + D < n_steps) fetch(i + k + D, k);
+        if (i + k + D < n_steps) fetch(i + k + D, k, true);
         products();
       }
     }
