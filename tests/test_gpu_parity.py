@@ -551,6 +551,23 @@ def test_conv_window_number_of_k_tiles_integer_bit_exact(bolt, case):
             assert_bit_equal(host(y), want, "conv %s instance %d" % (case, kid))
 
 
+@pytest.mark.parametrize("case", [(37, 1, 1, 1), (40, 3, 1, 2), (9, 1, 5, 1), (3, 2, 33, 1), (2, 65, 1, 1), (5, 7, 3, 2)])  # N H W stride
+def test_conv_few_tiles_pixels_of_a_tile_integer_bit_exact(bolt, case):
+    # a tile's 16 to 32 pixels lie in one image row, in many rows and in many images, whole and ragged: |sum| <= 144 + 9
+    n, h, w_, stride = case
+    x = wl.integer_fp16(147, 0, (n, h, w_, 16), -1, 1)
+    w = wl.integer_fp16(147, 1, (24, 3, 3, 16), -1, 1)
+    b = wl.integer_fp16(147, 2, (24,), -9, 9)
+    want = ref.conv2d_nhwc(x, w, b, stride=stride, pad=1, act="none")
+    d = bolt.conv_desc(n, h, w_, 16, 24, 3, 3, stride, 1, act="none")
+    for kid in range(bolt.bolt_num_instances(bolt.OP_CONV2D)):
+        if bolt.bolt_instance_supports(bolt.OP_CONV2D, kid, d):
+            _say("conv %s instance %d" % (case, kid))
+            y = torch.full(want.shape, float("nan"), dtype=torch.float16, device="cuda")
+            bolt.bolt_conv2d_fprop_nhwc(d, dev(x), dev(w), dev(b), y, {"kernel_id": kid})
+            assert_bit_equal(host(y), want, "conv %s instance %d" % (case, kid))
+
+
 def test_conv_identity_1x1_returns_input_exactly(bolt):
     x = wl.uniform_fp16(203, 0, (2, 9, 7, 64), -1, 1)
     w = np.zeros((64, 1, 1, 64), np.float16)
