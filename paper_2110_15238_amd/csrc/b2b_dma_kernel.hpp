@@ -163,6 +163,16 @@ __device__ __forceinline__ void b2b_tile_out(half_t* lds, const floatx16 (&acc)[
   constexpr int CPR = NOUT_T / 8, ROWS_PER_PASS = NT / CPR;
   static_assert(NT % CPR == 0 && BM % ROWS_PER_PASS == 0, "C tile store mapping");
   const int lane = tid & 63, g = lane >> 5, l32 = lane & 31;
+  // Wide tiles request the bias two fragments ahead, behind a fence: left alone, the compiler may put each quad's load right in front of its use, 32 round
+  // trips in turn at the end of every workgroup.  (8648 x 56 -> 24 -> 176 10.8 -> 7.6 us, 105648 x 520 -> 56 -> 168 41.8 -> 37.0, with GELU
+  // 1488 x 40 -> 56 -> 168 22.7 -> 20.0; ten registers short of all quads at once, which the widest chains don't have.)  Narrower tiles it
+  // overlaps by itself, in fewer registers.
+  constexpr bool WIDE = NOUT_T > 128;
+  BiasQuads<1> bias[2];
+  if constexpr (WIDE) {
+    bias[0].fetch(ep.bias, ep.bias_on, ep.N, 0, lane);
+    bias[1].fetch(ep.bias, ep.bias_on, ep.N, 32, lane);
+  }
   barrier_after_lds_writes();
   if constexpr (RES) {
     constexpr int RPI = 64 / CPR;  // tile rows per load instruction (1024 contiguous LDS bytes)
@@ -180,7 +190,7 @@ __device__ __forceinline__ void b2b_tile_out(half_t* lds, const floatx16 (&acc)[
   }
   auto tile_to_lds = [&](auto slow) {
 #pragma unroll
-    for (int a = 0; a < FNO; ++a)
+    for (int a = 0; a < FNO; ++a) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int nl = a * 32 + q * 8 + g * 4;
@@ -188,7 +198,13 @@ __device__ __forceinline__ void b2b_tile_out(half_t* lds, const floatx16 (&acc)[
         for (int b = 0; b < FM; ++b) {
           const int row = wave * WTM + b * 32 + l32;
           const int at = row * NOUT_T + (((nl >> 3) ^ ctile_swizzle<CPR>(row)) << 3) + (nl & 4);
-          if constexpr (RES) {
+          if constexpr (WIDE) {
+            const floatx4 v = {acc[a][b][q * 4], acc[a][b][q * 4 + 1], acc[a][b][q * 4 + 2], acc[a][b][q * 4 + 3]};
+            half4* slot = (half4*)(lds + at);
+            half4 res_quad = {0, 0, 0, 0};
+            if constexpr (RES) res_quad = *slot;
+            *slot = epilogue_quad4_values<decltype(slow)::value, RES>(v, bias[a & 1](0, q), ep, res_quad);
+          } else if constexpr (RES) {
             half4* slot = (half4*)(lds + at);
             *slot = epilogue_quad_res<decltype(slow)::value>(acc[a][b], q, nl, ep, *slot);
           } else {
@@ -198,6 +214,13 @@ __device__ __forceinline__ void b2b_tile_out(half_t* lds, const floatx16 (&acc)[
           }
         }
       }
+      if constexpr (WIDE) {
+        if (a + 2 < FNO) {
+          bias[a & 1].fetch(ep.bias, ep.bias_on, ep.N, (a + 2) * 32, lane);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    }
   };
   if (ep.act > ACT_RELU) tile_to_lds(std::true_type{});
   else tile_to_lds(std::false_type{});

@@ -352,6 +352,34 @@ def test_streaming_chains_are_compiled_apart_from_the_tiled_ones():
     assert sum(map(len, held)) == 3
 
 
+def test_wide_fused_pairs_request_their_bias_ahead(tmp_path):
+    """The last epilogue of a pair with 129 to 256 output columns has 32 bias quads per lane.  Each loaded where it is used is a round trip of
+    its own (2.5 us per workgroup): a load with a wait for everything behind it and no other load between.  Skipped as above."""
+    import subprocess
+    tools = "/opt/rocm/llvm/bin/"
+    build = os.path.join(ROOT, "paper_2110_15238_amd", "csrc", "_build")
+    objects = [os.path.join(build, o) for o in ("inst_b2b_gemm_dma.o", "inst_b2b_conv_dma.o")]
+    if not all(map(os.path.exists, objects + [tools + "llvm-objdump"])):
+        pytest.skip("no build directory or no disassembler")
+    seen = 0
+    for o in objects:
+        fat, code = str(tmp_path / "fat"), str(tmp_path / "code")
+        subprocess.check_call([tools + "llvm-objcopy", "--dump-section", ".hip_fatbin=" + fat, o, str(tmp_path / "copy")])
+        subprocess.check_call([tools + "clang-offload-bundler", "--type=o", "--unbundle", "--input=" + fat, "--output=" + code,
+                               "--targets=hipv4-amdgcn-amd-amdhsa--gfx950"])
+        listing = subprocess.run([tools + "llvm-objdump", "-d", "-C", "--no-show-raw-insn", code], capture_output=True, text=True, check=True).stdout
+        for part in re.split(r"\n(?=[0-9a-f]+ <)", listing):
+            kernel = re.match(r"[0-9a-f]+ <void bolt::b2b_dma_kernel<\d+, \d+, \d+, \d+, 256, ", part)
+            if not kernel:
+                continue
+            events = re.findall(r"^\s+(global_load_\w+|buffer_load_\w+|s_waitcnt [^\n/]*vmcnt\(\d+\))", part, re.M)
+            alone = sum(1 for before, load, wait in zip(events, events[1:], events[2:])
+                        if "vmcnt(0)" in wait and load.startswith("global_load") and "vmcnt(0)" in before)
+            seen += 1
+            assert alone <= 8, (kernel.group(0), alone)
+    assert seen >= 8
+
+
 def test_pick_rule_counts_the_activations_of_tall_thin_problems():
     """The kernels for small problems may not be estimated below the time that reading the activations takes: thousands of
     rows times a deep reduction, where the tiled kernels are up to 1.4 times faster.  Small problems stay with them."""
