@@ -226,39 +226,35 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_even_kernel(const FpropParams
 #pragma unroll
     for (int b = 0; b < FM; ++b) xf[b] = *(const half8*)(lds_b + (ent[k].x >= 0 ? pix_at[b] + ent[k].x : 0));
     const int nv = ent[k].y & 7;
-    half8 wf[FN];
 #pragma unroll
     for (int a = 0; a < FN; ++a) {
-      uintx4 w = wv[k][a];
 #pragma unroll
-      for (int e = 1; e < 4; ++e) w[e] = e < nv ? w[e] : 0u;  // the halves behind belong to the next tap
-      wf[a] = __builtin_bit_cast(half8, w);
+      for (int e = 1; e < 4; ++e) wv[k][a][e] = e < nv ? wv[k][a][e] : 0u;  // the halves behind belong to the next tap
+#pragma unroll
+      for (int b = 0; b < FM; ++b) acc[a][b] = mfma_16x16x32(__builtin_bit_cast(half8, wv[k][a]), xf[b], acc[a][b]);
     }
-    return [&acc, xf, wf] {
-#pragma unroll
-      for (int a = 0; a < FN; ++a)
-#pragma unroll
-        for (int b = 0; b < FM; ++b) acc[a][b] = mfma_16x16x32(wf[a], xf[b], acc[a][b]);
-    };
   };
   // A request past the wave's last step would bring zeros, and would cost the address unit (16 rows of 64 bytes) as much as any: of
-  // 7 steps per wave D = 3 more.  Whole rounds stand apart so that the waits behind their requests are exact.
+  // 7 steps per wave D = 3 more.  Whole rounds stand apart, and a fence keeps each request behind the step whose registers it takes, so
+  // that a step waits for its own set only.  Weights are masked where they lie and requested behind the products: a copy beside them is 9 to
+  // 13 registers, a workgroup per compute unit for the narrow tiles.  (Requests ahead of the products without the fence, all three of a round behind
+  // its last product as compiled, -> this: 274 images of 32 x 20 x 36, 3 x 3, 32 channels, 17.1 -> 16.4 us, its 6 x 1 fragments on 8 waves 37.6
+  // -> 31.9; 186 of 33 x 36 x 42, 5 x 7, 24 channels 35.7 -> 33.6.  40 problems, best instance: 0.973.)
   int i = 0;
   for (; i + 2 * D <= n_steps; i += D) {
 #pragma unroll
     for (int k = 0; k < D; ++k) {
-      auto products = step(k);
+      step(k);
       fetch(i + k + D, k, true);
-      products();
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
   for (; i < n_steps; i += D) {
 #pragma unroll
     for (int k = 0; k < D; ++k) {
       if (i + k < n_steps) {
-        auto products = step(k);
+        step(k);
         if (i + k + D < n_steps) fetch(i + k + D, k, true);
-        products();
       }
     }
   }

@@ -352,6 +352,19 @@ def test_streaming_chains_are_compiled_apart_from_the_tiled_ones():
     assert sum(map(len, held)) == 3
 
 
+def test_even_channel_kernels_keep_their_workgroups_per_compute_unit():
+    """512 registers per SIMD lane: tiles of up to 12 fragments run on four waves per SIMD, as their estimate in the pick rule counts
+    (128 registers), those of one channel fragment on six (80), of four pixel fragments on eight (64).  Skipped as above."""
+    report = os.path.join(ROOT, "paper_2110_15238_amd", "csrc", "_build", "inst_conv_even.usage")
+    if not os.path.exists(report):
+        pytest.skip("no build directory (library shipped pre-built)")
+    found = re.findall(r"conv_even_kernelILi(\d+)ELi(\d+)ELi(\d+)E\S*\s+VGPRs: (\d+)\s+ScratchSize \[bytes/lane\]: (\d+)", open(report).read())
+    assert len(found) >= 32
+    for _, fm, fn, regs, scratch in (map(int, f) for f in found):
+        most = (64 if fm <= 4 else 80) if fn == 1 else 128 if fm * fn <= 12 else 256
+        assert regs <= most and scratch == 0, (fm, fn, regs, scratch)
+
+
 def test_wide_fused_pairs_request_their_bias_ahead(tmp_path):
     """The last epilogue of a pair with 129 to 256 output columns has 32 bias quads per lane.  Each loaded where it is used is a round trip of
     its own (2.5 us per workgroup): a load with a wait for everything behind it and no other load between.  Skipped as above."""
