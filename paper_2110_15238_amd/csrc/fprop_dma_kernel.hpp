@@ -631,7 +631,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KG) void fprop_dma_kernel(
   const int n_tiles = (kt_end - kt_first + KG - 1) / KG;  // pipeline steps, at least one, the same for every k-group
   dma_main_loop<BM, BN, BK, WAVES_M, WAVES_N, NS, KG, T::G, (T::DEEP || T::NW < 8 ? 2 : 3), WKN>(
       xl, wl, lds + kg * T::GROUP_HALVES, p.cg, kt_begin, n_tiles, wm, wn, lane, acc, [&] {
-        if (kg == 0) bias.fetch(p.bias, p.bias_on, p.N, n0 + wn * WTN, lane);
+        // (partial sums have no epilogue; 611 timings of four-way splits, 0.993 with the request left out, whole sums 1.000)
+        if (kg == 0 && p.split_k == 1) bias.fetch(p.bias, p.bias_on, p.N, n0 + wn * WTN, lane);
       });
 
   // ---- k-groups: sum the accumulators through LDS, group 0 carries on ------------------------------
