@@ -153,7 +153,8 @@ __device__ __forceinline__ float at_least(float v, float lo) {
 //   out = act(alpha * acc + beta * bias[n + e]),  converted to FP16 with round-to-nearest-even.
 // The caller never passes a null bias: without a bias the pointer addresses 8 zero halves and
 // bias_on is 0, which keeps the hot path free of branches (the loads can be scheduled early).
-// Columns beyond N take a zero bias; their results are never stored.
+// Columns beyond N (the padding of a compiled width) are never stored.  Where a fused op reads them again they have to be finite:
+// epilogue_quad* takes a zero bias for them, a caller that brings its own quads (BiasQuads) discards their results.
 // SLOW = false handles "none" and ReLU (at_least); SLOW = true calls the transcendental
 // activations.  The choice between the two is ONE wave-uniform branch around a whole tile.
 struct EpilogueArgs {
@@ -164,7 +165,7 @@ struct EpilogueArgs {
   float gamma = 0.f;  // scale of the residual quad (Eq. 1 with a full matrix C), epilogue_quad_res only
 };
 
-// The arithmetic for a quad whose bias (zeros for columns beyond N) is already in registers.
+// The arithmetic for a quad whose bias is already in registers.
 template <bool SLOW, bool RES>
 __device__ __forceinline__ half4 epilogue_quad4_values(floatx4 a4, half4 hb, const EpilogueArgs& ep, half4 res) {
   half4 o;
@@ -209,7 +210,8 @@ __device__ __forceinline__ half4 epilogue_quad_res(const floatx16& acc, int q, i
 }
 
 // The bias quads of the columns that a lane's accumulators hold (the 32 x 32 layout: registers 4q .. 4q + 3 of fragment a are columns 32a + 8q + 4(lane / 32) .. + 3).  They are requested in
-// front of the last MFMAs: in the epilogue each was a load that nothing covered, up to one round trip after the other.
+// front of the last MFMAs: in the epilogue each was a load that nothing covered, up to one round trip after the other.  Columns beyond N get
+// what the first ones have: fprop_tile_out and b2b_tile_out don't store them, b2b_make_d makes zeros of them.
 // (56 x 56 64 -> 64 and 64 -> 256 with a skip connection, 32 images, best instance: 7.0 -> 6.4 us and 22.4 -> 20.0; 28 x 28 512 -> 256 of 2
 // images 5.4 -> 4.9.  Accumulators that start at the bias are as fast there, but cost problems of few workgroups 0.2 to 0.4 us, which
 // wait for it before the first MFMA.)
@@ -223,7 +225,7 @@ struct BiasQuads {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int n = n_wave + a * 32 + q * 8 + (lane >> 5) * 4;
-        quad[a][q] = *(const half4*)(bias + (n < N ? n : 0) * bias_on);  // (columns beyond N: what the first ones have)
+        quad[a][q] = *(const half4*)(bias + (n < N ? n : 0) * bias_on);
       }
   }
 };
