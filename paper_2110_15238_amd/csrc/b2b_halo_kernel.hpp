@@ -149,7 +149,7 @@ __global__ __launch_bounds__(64 * NW, 2) void b2b_halo_chunked_kernel(const B2bP
     b2b_rf_gemm<N0T, NC, FM>(c < OWN ? own + c * SLOT : stages + (c - OWN) * SLOT, d0, acc1, l32, g);
     // this wave's share of the late chunks has landed; the barrier that opens b2b_tile_out publishes it
     if (c == 0 && NCHUNK > OWN) __builtin_amdgcn_s_waitcnt(0x0F70);
-    const EpilogueArgs ep{p.b1 + c * NC, p.b1_on, p.N1 - c * NC, p.alpha1, p.beta1, p.act1, RES ? p.gamma : 0.f};
+    const EpilogueArgs ep{p.b1 + c * NC * p.b1_on, p.b1_on, p.N1 - c * NC, p.alpha1, p.beta1, p.act1, RES ? p.gamma : 0.f};
     b2b_tile_out<BM, NW, NC, RES>(lds, acc1, ep, p.Y + c * NC, p.ldy, p.M, m0, wave, tid, RES ? p.res + c * NC : nullptr, p.ldr);
   }
 }

@@ -158,7 +158,7 @@ __device__ __forceinline__ void b2b_tile_out_2d(half_t* stage, const floatx16 (&
   static_assert(NT % CPR == 0 && BM % ROWS_PER_PASS == 0, "C tile store mapping");
   const int lane = tid & 63, g = lane >> 5, l32 = lane & 31;
   const int n_valid = p.N1 - n_off;
-  const EpilogueArgs ep{p.b1 + n_off, p.b1_on, n_valid, p.alpha1, p.beta1, p.act1, RES ? p.gamma : 0.f};
+  const EpilogueArgs ep{p.b1 + n_off * p.b1_on, p.b1_on, n_valid, p.alpha1, p.beta1, p.act1, RES ? p.gamma : 0.f};
   __syncthreads();
   auto to_lds = [&](auto slow) {
 #pragma unroll

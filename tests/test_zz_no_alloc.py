@@ -68,3 +68,42 @@ def test_noalloc_rejects_partial_sums_beyond_the_fixed_array(bolt):
     assert e.value.status == 4
     torch.cuda.synchronize()
     assert bool((D == 7.0).all())
+
+
+@pytest.mark.parametrize("shape", [(1, 10, 12, 64, 64, 256), (1, 10, 12, 64, 40, 200)])  # N H W C K0 K1
+def test_pairs_without_a_bias_read_zeros_for_every_column(bolt, shape):
+    """Kernels that take a wide second op some columns at a time: without a bias every chunk has the zeros of the first one, whatever
+    lies behind them (the fixed array, here full of partial sums that are not zero)."""
+    n, h, w_, c, k0, k1 = shape
+    ones = lambda *s: torch.ones(s, dtype=torch.float16, device="cuda")
+    d = bolt.gemm_desc(64, 64, 1024, act="none")
+    kid = [k for k in range(bolt.bolt_num_instances(bolt.OP_GEMM)) if bolt.bolt_instance_supports(bolt.OP_GEMM, k, d)][0]
+    y = ones(64, 64)
+    bolt.bolt_gemm_epilogue_noalloc(d, ones(64, 1024), ones(1024, 64), None, y, {"kernel_id": kid, "split_k": 4})
+    assert float(y.min()) == 1024.0
+    m = n * h * w_
+    x, a = wl.integer_fp16(701, 0, (n, h, w_, c), -1, 1), wl.integer_fp16(701, 1, (m, c), -1, 1)
+    w0, w1 = wl.integer_fp16(701, 2, (k0, 3, 3, c), -1, 1), wl.integer_fp16(701, 3, (k1, 1, 1, k0), -1, 1)
+    # |d0| <= 576 and |d1| <= 64 * 576: sums below 2^24, so both ops round the same exact values
+    want = ref.b2b_conv(x, w0, None, w1, None, stride=1, pad=1)
+    c0, c1 = bolt.conv_desc(n, h, w_, c, k0, 3, 3, 1, 1), bolt.conv_desc(n, h, w_, k0, k1, 1, 1)
+    skip = torch.zeros((n, h, w_, k1), dtype=torch.float16, device="cuda")
+    for kid in range(bolt.bolt_num_instances(bolt.OP_B2B_CONV)):
+        if bolt.bolt_instance_supports(bolt.OP_B2B_CONV, kid, c0, c1):
+            got = torch.full((n, h, w_, k1), float("nan"), dtype=torch.float16, device="cuda")
+            bolt.bolt_b2b_conv(c0, c1, dev(x), dev(w0), None, dev(w1), None, got, {"kernel_id": kid})
+            assert_bit_equal(host(got), want, "conv pair %s instance %d" % (shape, kid))
+        if bolt.bolt_instance_supports(bolt.OP_B2B_CONV_RES, kid, c0, c1):
+            got = torch.full((n, h, w_, k1), float("nan"), dtype=torch.float16, device="cuda")
+            bolt.bolt_b2b_conv_residual(c0, c1, dev(x), dev(w0), None, dev(w1), None, skip, got, 1.0, {"kernel_id": kid})
+            assert_bit_equal(host(got), want, "conv pair %s with a skip, instance %d" % (shape, kid))
+    W0, W1 = np.ascontiguousarray(w0[:, 1, 1].T), np.ascontiguousarray(w1[:, 0, 0].T)
+    want = ref.b2b_gemm(a, W0, None, W1, None)
+    for lay, weights in ((bolt.LAYOUT_KN, (W0, W1)), (bolt.LAYOUT_NK, (w0[:, 1, 1], w1[:, 0, 0]))):
+        g0, g1 = bolt.gemm_desc(m, k0, c, b_layout=lay), bolt.gemm_desc(m, k1, k0, b_layout=lay)
+        wd = [dev(np.ascontiguousarray(v)) for v in weights]
+        for kid in range(bolt.bolt_num_instances(bolt.OP_B2B_GEMM)):
+            if bolt.bolt_instance_supports(bolt.OP_B2B_GEMM, kid, g0, g1):
+                got = torch.full((m, k1), float("nan"), dtype=torch.float16, device="cuda")
+                bolt.bolt_b2b_gemm(g0, g1, dev(a), wd[0], None, wd[1], None, got, {"kernel_id": kid})
+                assert_bit_equal(host(got), want, "gemm pair %s layout %d instance %d" % (shape, lay, kid))
