@@ -352,6 +352,17 @@ def test_streaming_chains_are_compiled_apart_from_the_tiled_ones():
     assert sum(map(len, held)) == 3
 
 
+def test_objects_depend_on_every_header_and_on_the_flags():
+    """make's own plan (nothing is run): each header and the Makefile, whose flags differ by file, send every kernel file to the compiler."""
+    import subprocess
+    csrc = os.path.join(ROOT, "paper_2110_15238_amd", "csrc")
+    sources = sorted(f for f in os.listdir(csrc) if f.endswith(".hip"))
+    for changed in sorted(f for f in os.listdir(csrc) if f.endswith(".hpp")) + ["Makefile"]:
+        plan = subprocess.run(["make", "-n", "-W", changed, "lib"], cwd=csrc, capture_output=True, text=True, check=True).stdout
+        compiled = sorted(set(re.findall(r" -c (\S+\.hip) ", plan)))
+        assert compiled == sources, (changed, set(sources) - set(compiled))
+
+
 def test_even_channel_kernels_keep_their_workgroups_per_compute_unit():
     """512 registers per SIMD lane: tiles of up to 12 fragments run on four waves per SIMD, as their estimate in the pick rule counts
     (128 registers), those of one channel fragment on six (80), of four pixel fragments on eight (64).  Skipped as above."""
