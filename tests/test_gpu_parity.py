@@ -8,7 +8,7 @@ import pytest
 
 import workloads as wl
 from oracle import ref
-from util import assert_bit_equal, assert_close, dev, host
+from util import PATCH_SHARES, assert_bit_equal, assert_close, dev, host, patch_share
 
 pytestmark = pytest.mark.gpu
 
@@ -932,25 +932,32 @@ def test_conv_patch_pairs_and_single_op_integer_bit_exact(bolt, case):
         assert ran >= 3
 
 
-# 1029, 1225, 1519 and 1764 units for 1024 waves: the last ones shared by as many waves as there are column chunks, by four, two and one
-@pytest.mark.parametrize("case", [(21, 28, 56, 8, 24, 3, 1, 1, 256), (25, 28, 56, 8, 24, 3, 1, 1, 256), (25, 28, 56, 16, 40, 1, 1, 0, 136), (31, 28, 56, 8, 24, 3, 1, 1, 200), (36, 28, 56, 8, 24, 1, 1, 0, 256),
-                                  (25, 55, 111, 8, 24, 3, 2, 1, 72)])
-def test_conv_patch_pairs_shared_last_units_integer_bit_exact(bolt, case):
-    test_conv_patch_pairs_and_single_op_integer_bit_exact(bolt, case)
+@pytest.mark.parametrize("case, share", PATCH_SHARES)
+def test_conv_patch_pairs_shared_last_units_integer_bit_exact(bolt, case, share):
     N, H, W, Cc, K0, R, stride, pad, K1 = case
-    x, w0 = wl.integer_fp16(511, 0, (N, H, W, Cc), 0, 1), wl.integer_fp16(511, 1, (K0, R, R, Cc), -1, 1)
-    w1 = wl.integer_fp16(511, 3, (K1, 1, 1, K0), -1, 1)
     c0 = bolt.conv_desc(N, H, W, Cc, K0, R, R, stride, pad)
     P, Q = bolt.conv_out_hw(c0)
-    c1 = bolt.conv_desc(N, P, Q, K0, K1, 1, 1, alpha=0.5)  # the form for any alpha: halves of whole numbers, |sum| < 1024
-    want = ref.b2b_conv(x, w0, None, w1, None, stride=stride, pad=pad, alpha1=0.5)
-    for kid in range(bolt.bolt_num_instances(bolt.OP_B2B_CONV)):
-        cfg = bolt.bolt_instance_config(bolt.OP_B2B_CONV, kid)
-        if cfg.tile_n == 256 and cfg.tile_m == 128 and cfg.stages == 1 and bolt.bolt_instance_supports(bolt.OP_B2B_CONV, kid, c0, c1):
-            y = torch.full((N, P, Q, K1), float("nan"), dtype=torch.float16, device="cuda")
-            bolt.bolt_b2b_conv(c0, c1, dev(x), dev(w0), None, dev(w1), None, y, {"kernel_id": kid})
-            assert_bit_equal(host(y), want, "conv patch pair %s alpha 0.5, instance %d" % (case, kid))
-
+    assert patch_share(N, P, Q, K1) == share  # (that the sharing kernel is launched for these: test_host_launches.py)
+    test_conv_patch_pairs_and_single_op_integer_bit_exact(bolt, case)
+    # the form for any activation and alpha, with a residual in place (without one nothing is shared).  |sum| <= 24 * 9 * 40 here, so the halves
+    # of whole numbers are exact only below 1024: the widest input is compared by the tolerance
+    x, w0 = wl.integer_fp16(511, 0, (N, H, W, Cc), 0, 1), wl.integer_fp16(511, 1, (K0, R, R, Cc), -1, 1)
+    w1, res = wl.integer_fp16(511, 3, (K1, 1, 1, K0), -1, 1), wl.integer_fp16(511, 5, (N, P, Q, K1), -3, 3)
+    d0 = ref.conv2d_nhwc(x, w0, None, stride=stride, pad=pad)
+    for act1 in ("relu", "gelu"):
+        plain, c1 = bolt.conv_desc(N, P, Q, K0, K1, 1, 1), bolt.conv_desc(N, P, Q, K0, K1, 1, 1, alpha=0.5, act=act1)
+        want = ref.conv2d_nhwc(d0, w1, None, alpha=0.5, act=act1)
+        want_res = ref.conv2d_nhwc_residual(d0, w1, None, res, alpha=0.5, gamma=2.0, act=act1)
+        check = assert_bit_equal if act1 == "relu" and R * R * Cc * K0 // 2 + 6 < 1024 else assert_close
+        for kid in range(bolt.bolt_num_instances(bolt.OP_B2B_CONV)):
+            cfg = bolt.bolt_instance_config(bolt.OP_B2B_CONV, kid)
+            if cfg.tile_n == 256 and cfg.tile_m == 128 and cfg.stages == 1 and bolt.bolt_instance_supports(bolt.OP_B2B_CONV, kid, c0, plain):
+                _say("conv patch pair %s alpha 0.5 %s instance %d" % (case, act1, kid))
+                y, r = torch.full((N, P, Q, K1), float("nan"), dtype=torch.float16, device="cuda"), dev(res)
+                bolt.bolt_b2b_conv(c0, c1, dev(x), dev(w0), None, dev(w1), None, y, {"kernel_id": kid})
+                bolt.bolt_b2b_conv_residual(c0, c1, dev(x), dev(w0), None, dev(w1), None, r, r, 2.0, {"kernel_id": kid})
+                check(host(y), want, "conv patch pair %s alpha 0.5 %s, instance %d" % (case, act1, kid))
+                check(host(r), want_res, "conv patch pair %s alpha 0.5 %s residual, instance %d" % (case, act1, kid))
 
 
 @pytest.mark.parametrize("case", [c for c in PATCH_EDGES if c[0] * c[1] * c[2] > 5000 or c[0] in (3, 5)] + [(2, 17, 19, 64, 64, 3, 2, 1, 256), (1, 5, 9, 128, 64, 1, 1, 0, 256)])

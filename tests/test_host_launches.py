@@ -5,6 +5,8 @@ import sys
 
 import pytest
 
+from util import PATCH_SHARES
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 
@@ -102,6 +104,30 @@ for o in others:
         assert s == 0 and "conv_patch" not in kernels[0], (o, kernels)
 assert "conv_patch" in conv(d())[1][0] and "conv_patch" in pair(d(), e())[1][0]
 """)
+
+
+def test_last_units_of_a_pair_are_shared_where_they_leave_waves_idle(run):
+    """The sharing form of conv_patch_kernel, plain and general, is launched for pairs with a residual whose last round is at most half full, on
+    every instance of the family; not without a residual, nor where whole rounds are left."""
+    run("""
+cases = %r
+ran = set()
+for (n, h, w, c, k0, r, stride, pad, k1), share in cases:
+    c0 = b.conv_desc(n, h, w, c, k0, r, r, stride, pad)
+    p, q = b.conv_out_hw(c0)
+    plain = b.conv_desc(n, p, q, k0, k1, 1, 1)
+    for kid in range(b.bolt_num_instances(b.OP_B2B_CONV)):
+        if not b.bolt_instance_supports(b.OP_B2B_CONV, kid, c0, plain): continue
+        cfg = C.byref(b.BoltConfig.from_dict(dict(kernel_id=kid)))
+        for c1, general in ((plain, 0), (b.conv_desc(n, p, q, k0, k1, 1, 1, alpha=0.5), 1)):
+            assert lib.bolt_b2b_conv(C.byref(c0), C.byref(c1), P, P, P, P, P, P, cfg, None, 0, None) == 0
+            assert lib.bolt_b2b_conv_residual(C.byref(c0), C.byref(c1), P, P, P, P, P, P, 1.0, P, cfg, None, 0, None) == 0
+            alone, skip = rec.recorder_launches().decode().split()
+            if "conv_patch_kernel" not in alone: continue
+            assert "ELb1ELb0ELb%%dELb0EEE" %% general in alone and "ELb1ELb1ELb%%dELb%%dEEE" %% (general, share > 1) in skip, (n, h, w, share, alone, skip)
+            ran.add((share, general))
+assert ran == {(s, g) for s in (1, 2, 3, 4) for g in (0, 1)}, ran
+""" % (PATCH_SHARES,))
 
 
 @pytest.mark.parametrize("after_itself", (0.014, 0.020, 0.026, 0.040))

@@ -37,3 +37,23 @@ def assert_bit_equal(gpu, ref, what=""):
         i = tuple(diff[0])
         raise AssertionError("%s: %d elements differ; first at %s gpu=%r oracle=%r" %
                              (what, len(diff), i, np.asarray(gpu)[i], np.asarray(ref)[i]))
+
+
+def patch_share(N, P, Q, K1):
+    """Waves per unit behind the last whole round of a pair with a residual, from the rule of conv_patch_kernel: units of 4 x (6 to 8) pixels
+    for 256 workgroups of four waves, 128 waves on each of eight XCDs, and the columns of op1 in chunks of 64."""
+    units_of = lambda tq: N * -(-P // 4) * -(-Q // tq)
+    units = units_of(min((8, 7, 6), key=lambda tq: (-(-units_of(tq) // 1024) * (8 + tq), -tq)))
+    left, chunks = -(-units // 8) % 128, -(-K1 // 64)
+    if units < 1024 or left == 0 or left * 2 > 128 or chunks < 2:
+        return 1
+    return 4 if left * 4 <= 128 and chunks > 3 else 3 if left * 3 <= 128 and chunks > 2 else 2
+
+
+# 1029 to 2100 units of 8 columns for 1024 waves; and images of 56 columns, whose units have 6 or 7: 1470 to 2016
+# Case: N H W C K0 R stride pad K1 of a pair, and the waves that share a unit behind the last whole round.
+PATCH_SHARES = [
+    ((147, 28, 8, 8, 24, 3, 1, 1, 256), 4), ((192, 28, 8, 8, 24, 3, 1, 1, 256), 3), ((175, 28, 8, 8, 24, 3, 1, 1, 136), 3), ((217, 28, 8, 8, 24, 3, 1, 1, 200), 2),
+    ((175, 28, 8, 40, 24, 3, 1, 1, 72), 2), ((252, 28, 8, 8, 24, 3, 1, 1, 256), 1), ((300, 28, 8, 8, 24, 3, 1, 1, 256), 4), ((175, 55, 15, 8, 24, 3, 2, 1, 136), 3),
+    ((147, 55, 15, 8, 24, 3, 2, 1, 256), 4), ((217, 28, 8, 16, 40, 1, 1, 0, 136), 2), ((192, 28, 8, 16, 40, 1, 1, 0, 256), 3), ((300, 28, 8, 72, 24, 1, 1, 0, 200), 4),
+    ((21, 28, 56, 8, 24, 3, 1, 1, 256), 2), ((25, 28, 56, 16, 40, 1, 1, 0, 136), 1), ((36, 28, 56, 8, 24, 1, 1, 0, 256), 1), ((25, 55, 111, 8, 24, 3, 2, 1, 72), 1)]
