@@ -363,6 +363,20 @@ def test_objects_depend_on_every_header_and_on_the_flags():
         assert compiled == sources, (changed, set(sources) - set(compiled))
 
 
+def test_every_file_with_the_shared_main_loop_keeps_matrix_results_in_vector_registers():
+    """dma_main_loop has several ends; with accumulation registers the compiler copies the accumulators from one to the other, which short
+    reductions don't make up for (NCHW outputs of 1x1 filters over 40 to 200 channels: 3 to 7 %).  Skipped as above."""
+    import subprocess
+    csrc = os.path.join(ROOT, "paper_2110_15238_amd", "csrc")
+    if not os.path.exists(os.path.join(csrc, "_build")):
+        pytest.skip("no build directory (library shipped pre-built)")
+    plan = subprocess.run(["make", "-n", "-W", "Makefile", "lib"], cwd=csrc, capture_output=True, text=True, check=True).stdout
+    lines = {m.group(1): m.group(0) for m in re.finditer(r"^hipcc .* -c (\S+)\.hip .*$", plan, re.M)}
+    held = {f for f in lines if re.search("fprop_dma_kernel|b2b_dma_kernel|b2b_chain_kernel", open(os.path.join(csrc, "_build", f + ".usage")).read())}
+    assert {"inst_conv", "inst_gemm_nk", "inst_b2b_gemm_dma"} <= held
+    assert all("-amdgpu-mfma-vgpr-form=1" in lines[f] for f in held), [f for f in held if "vgpr-form" not in lines[f]]
+
+
 def test_even_channel_kernels_keep_their_workgroups_per_compute_unit():
     """512 registers per SIMD lane: tiles of up to 12 fragments run on four waves per SIMD, as their estimate in the pick rule counts
     (128 registers), those of one channel fragment on six (80), of four pixel fragments on eight (64).  Skipped as above."""
