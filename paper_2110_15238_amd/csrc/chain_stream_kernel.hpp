@@ -13,8 +13,8 @@ namespace bolt {
 // reduction of one or two k-tiles the pipeline of b2b_chain_kernel is all fill and drain, every workgroup loading, computing
 // and storing in lockstep.
 // What bounds it: below 32768 rows the fill (weights and first rows, one round trip) and the chain of the three products;
-// above, issue and latency as much as memory: at 128320 rows and 3.0 TB/s vector instructions take 50 % of the SIMD-cycles, matrix
-// ones 12 %, and waves wait for 40 % of their life.  Two waves per SIMD: at three the prefetched rows spill (56 registers).
+// above, issue and latency as much as memory: at 128320 rows and 3.5 TB/s vector instructions take 45 % of the SIMD-cycles, matrix
+// ones 11 %, and waves wait for 46 % of their life.  Two waves per SIMD: at three the prefetched rows spill (56 registers).
 // Measured, best tiled instance -> this one, ReLU, us (HIP-graph replay): 128320 x 96 -> 32 -> 96 -> 32 13.6 -> 10.8 (3.0 TB/s), 128 -> 64 -> 128 -> 64 27.8 -> 16.5,
 // 104 -> 56 -> 64 -> 128 27.9 -> 15.4, 128 -> 64 -> 64 -> 64 15.7 -> 13.3; 65536 x 104 -> 56 -> 64 -> 128 14.9 -> 10.2, but
 // 65536 x 128 -> 64 -> 64 -> 64 8.5 -> 9.0 and 8192 x 128 -> 64 -> 128 -> 64 7.5 -> 8.5: see the pick rule of the chains.

@@ -14,8 +14,8 @@
 //     without a barrier in the loop;
 //   * sums the waves' partial tiles through LDS in a fixed order, FP32, and applies the epilogue.
 // A table in LDS holds every chunk's offsets (pixel-relative LDS offset, weight offset, valid halves).
-// What bounds it: latency, of the patch, the first weights and the sum over the waves.  On the problem above waves wait for half
-// of their life, vector instructions take 37 % of the SIMD-cycles, matrix ones 12 %, the LDS is active in 21 %, a third of that in
+// What bounds it: latency, of the patch, the first weights and the sum over the waves.  On the problem above waves wait for 41 % of
+// their life, vector instructions take 39 % of the SIMD-cycles, matrix ones 14 %, the LDS is active in 24 %, a third of that in
 // bank conflicts (a fragment's 16 pixels span two tile rows).
 // Measured back to back under the tuner's picks, old -> new: the problem above 28 -> 7.5 us (230 TFLOP/s; the host needs 4
 // per call); 128 images of 20 x 26 x 174, 5 x 5, 64 channels 252 -> 73 us (510 TFLOP/s); over 85 problems of

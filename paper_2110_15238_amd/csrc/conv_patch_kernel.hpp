@@ -15,9 +15,9 @@
 //   * bias in the accumulators from the start, ReLU on packed halves: one vector instruction per output value.  One wave per SIMD
 //     issues one instruction every 4 cycles, so instructions are what the loop is short of (a first form with 1740 per unit
 //     took 13400 cycles for it; 700 are left).
-// What bounds it: the chain of one wave per SIMD, neither memory nor a pipe.  64 -> 64 -> 256 at 56 x 56, batch 32, moves its 64 MB at 3.3 TB/s
-// (a large copy: 4.9; the 1x1 pairs here: 4.5), the matrix cores are busy for 30 % of the SIMDs' cycles, vector instructions for 15 % and
-// LDS for 30 %; a wave waits for loads, LDS and the places of its stores for 43 % of its life, and 3136 units are 3.4 rounds.  Below 8
+// What bounds it: the chain of one wave per SIMD, neither memory nor a pipe.  64 -> 64 -> 256 at 56 x 56, batch 32, moves its 64 MB at 3.3 to 3.5 TB/s
+// (a large copy: 4.9; the 1x1 pairs here: 4.5), the matrix cores are busy for 31 % of the SIMDs' cycles, vector instructions for 16 % and
+// LDS for 31 %; a wave waits for loads, LDS and the places of its stores for 42 % of its life, and its 3584 units of 7 columns are 3.5 rounds.  Below 8
 // images, the fill: weights, first patch and a unit's chain of products take 5 us (64 channels) beside the launch.
 // Its residual: single ops fetch it one unit ahead of the output.  Other activations than ReLU and alpha != 1 run without the overlap (GEN).
 // Measured under a HIP graph, best tiled instance -> this one, us: 3x3 -> 1x1 at 56 x 56, 64 -> 64 -> 256, batch 32 24.4 -> 19.8, with a
@@ -221,8 +221,10 @@ __global__ __launch_bounds__(256, 1) void conv_patch_kernel(const ConvPatchParam
   int u = __builtin_amdgcn_readfirstlane(u_first + wg * NW + wave);
   // SHARE: the units behind the last whole round, where there are some for half of the waves at most, are taken by two to four waves
   // together, each with its share of the columns of op1 (op0 they all compute).  They would be all that runs for a while, and the residual
-  // makes their outputs long: 56 x 56 64 -> 64 -> 256 with a skip connection, 32 images, 3136 units for 1024 waves, 31.7 -> 28.9 us; 112 x 112
-  // 48 -> 48 -> 192 / 2 29.8 -> 29.0.  (Without a residual nothing was won, 21.0 us either way; where no unit is shared the code cost 0 to 3 %.)
+  // makes their outputs long.  64 -> 64 -> 256 with a skip connection, not shared -> shared, us: 56 x 56, 32 images, 3584 units for 1024 waves, by two
+  // 31.3 -> 30.3; 28 x 8, 217 images, 1519 units, by two 16.7 -> 15.2; 192 images, by three 15.7 -> 14.3; 147 and 300 images, by four 13.5 -> 12.1
+  // and 23.8 -> 21.1; stride 2 by four 18.4 -> 16.4; 1 x 1 by four 11.2 -> 9.3.  (Without a residual nothing was won at 56 x 56, by two, 21.0 us either
+  // way; shares of three and four were not measured without one.  Where no unit is shared the code cost 0 to 3 %.)
   constexpr int WAVES = T::MOST_WGS / 8 * NW;  // of an XCD in a launch whose waves have several units
   static_assert((WAVES & (WAVES - 1)) == 0, "whole rounds by a mask");
   const int left = (u_end - u_first) & (WAVES - 1), tail = u_end - left;

@@ -13,13 +13,17 @@
 //   * the waves' partial tiles are summed through LDS in a fixed order, in FP32, and the epilogue is applied once.  Bias and
 //     residual are requested before the loop.
 // Row-major weights ([K][N]) lie in LDS as in memory and are read with the transposing read.
-// What bounds it: launch (2.3 us), one round trip to memory and the sum over the waves (waves wait for 48 to 72 % of their life); with many units per wave the rate
-// at which one compute unit gets operands that come from the memory-side cache (about 60 GB/s).  A wave has few units (1 to 9 in a
+// What bounds it: launch (2.3 us), one round trip to memory and the sum over the waves (waves wait for 46 to 77 % of their life).  With several units per
+// wave it matters how they are requested: the conditions of a request's offsets split the wave, a load stands on either side, and both write
+// the same registers.  As compiled, the forms of 8 and 16 waves (256 and 128 registers, no accumulation registers) wait for everything in flight in
+// between, so their units come one round trip after the other whatever D is; those of 4 waves don't wait.  (Held to 128 registers, 4 waves of
+// 1 x 2 fragments wait so too: 365 x 112 x 4032 8.5 -> 10.3 us, 2 images of 45 x 33 x 832, 3 x 3, 16.0 -> 19.6.)
+// A wave has few units (1 to 9 in a
 // network of one image), so no request is made past the last one: requests that bring only zeros take their turn in the address
-// unit like any other, and D of them per wave cost 0.1 to 0.4 us (1024 -> 256 at 14 x 14 3.99 -> 3.84 us, 3 x 3 256 -> 256 5.94 -> 5.5,
-// 128 -> 512 with a skip connection at 28 x 28 4.3 -> 3.7, 32 x 1000 x 2048 5.8 -> 5.65; the network's 52 layers 248 -> 221).  Deeper prefetch is
-// slower still: D = 4 to 6 2 to 20 %, by registers, and because the first unit then waits for all of them.
-// Measured back to back under the tuner's picks, tiled kernels -> this one: 32 x 1000 x 2048 row-major 8.1 -> 5.0 us,
+// unit like any other, and D of them per wave cost 0.1 to 0.6 us (1024 -> 256 at 14 x 14 3.99 -> 3.84 us, 3 x 3 256 -> 256 5.94 -> 5.5,
+// 128 -> 512 with a skip connection at 28 x 28 4.3 -> 3.7, 32 x 1000 x 2048 row-major 5.8 -> 5.65; the network's 52 layers 248 -> 221).  D = 4 to 6 was 2 to 20 %
+// slower, but measured on requests that wait as described.
+// Measured back to back under the tuner's picks, tiled kernels -> this one (first form): 32 x 1000 x 2048 row-major 8.1 -> 5.0 us,
 // 256 x 256 x 256 4.1 -> 3.2; convolutions of one image: 14 x 14, 3 x 3, 256 -> 256 9.5 -> 5.5, 1024 -> 256 6.1 -> 3.8,
 // 7 x 7, 3 x 3, 512 -> 512 10.5 -> 7.2, 2048 -> 512 8.0 -> 4.5.
 #pragma once
