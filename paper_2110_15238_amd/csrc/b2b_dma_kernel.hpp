@@ -165,8 +165,8 @@ __device__ __forceinline__ void b2b_tile_out(half_t* lds, const floatx16 (&acc)[
   const int lane = tid & 63, g = lane >> 5, l32 = lane & 31;
   // Wide tiles request the bias two fragments ahead, behind a fence: left alone, the compiler may put each quad's load right in front of its use, 32 round
   // trips in turn at the end of every workgroup.  (8648 x 56 -> 24 -> 176 10.8 -> 7.6 us, 105648 x 520 -> 56 -> 168 41.8 -> 37.0, with GELU
-  // 1488 x 40 -> 56 -> 168 22.7 -> 20.0; ten registers short of all quads at once, which the widest chains don't have.)  Narrower tiles it
-  // overlaps by itself, in fewer registers.
+  // 1488 x 40 -> 56 -> 168 22.7 -> 20.0.  All quads at once spill: 64 registers beside 128 accumulators.)  Narrower tiles it overlaps by
+  // itself, in fewer registers.
   constexpr bool WIDE = NOUT_T > 128;
   BiasQuads<1> bias[2];
   if constexpr (WIDE) {
